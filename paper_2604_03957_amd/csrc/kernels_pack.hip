@@ -2,6 +2,8 @@
 // equations; "Instruction-level Parallel Bitpack").  Bandwidth-bound streaming kernels: every
 // lane takes 8 consecutive elements with one 128-bit (fp16) or 64-bit (int8) load, turns them
 // into one byte per plane, and the four lanes of a quad assemble a 32-bit plane word.
+#include <type_traits>
+
 #include "bwta_internal.h"
 
 namespace bwta {
@@ -427,27 +429,175 @@ __global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restri
     }
 }
 
-// One workgroup per token: s[m] = 2 * mean_k |A[m, k]| (exact integer sum, one division, one rounding).
-template <int NG, int NT>
-__global__ __launch_bounds__(NT) void k_act_scale(const uint16_t *__restrict__ A, int64_t lda, int K,
-                                                        uint16_t *__restrict__ s, int whole)
-{
-    __shared__ long long s_ll[NT / 64];
-    const int m = blockIdx.x, c8 = (K + 7) / 8;
-    uint4 x[NG];
-    load_row_groups<NG, NT>(A + (int64_t)m * lda, K, c8, whole != 0, x);
-    double part = 0.0;
+// ---- exact sums of binary16 magnitudes ----------------------------------------------------------
+//
+// The 15 magnitude bits of a binary16 value, put at the same place of a double (exponent field on
+// exponent field), are that value times 2^-1008: exactly, subnormals included, because a double whose
+// exponent field is 0 is scaled by the same rule.  So a magnitude becomes a double with one shift and
+// one mask and joins the sum with one addition, three full-rate instructions, where a conversion
+// through float, the exclusion of non-finite values and a second conversion took seven.  Per-thread
+// sums are exact (at most 128 values, see double_units) with binary64 subnormals on, the HIP default.
+// Non-finite values are noticed from the sum of squares, one dot-product instruction per two
+// values; a thread that holds one adds its values again with the exclusion.
+struct MagnitudeSum {
+    double even = 0.0, odd = 0.0;
+    float squares = 0.0f;
+
+    __device__ __forceinline__ void add(const uint4 &x)
+    {
+        const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {  // elements past K were loaded as +0 and add nothing
-            const uint16_t h = half_of(x[g], i) & 0x7fff;
-            const float f = h < 0x7c00 ? half_bits_to_float(h) : 0.0f;  // NaN / Inf stay out
-            part += (double)f;
+        for (int i = 0; i < 4; ++i) {
+            even += __hiloint2double((int)((w[i] << 10) & 0x01fffc00u), 0);
+            odd += __hiloint2double((int)((w[i] >> 6) & 0x01fffc00u), 0);
+            typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+            half2_t h;
+            __builtin_memcpy(&h, &w[i], 4);
+            squares = __builtin_amdgcn_fdot2(h, h, squares, false);
         }
     }
-    const long long S = block_sum<NT>(double_units(part), s_ll);
-    if (threadIdx.x == 0) s[m] = double_to_half_bits((double)S / ((double)K * 8388608.0));  // 2 S / (K 2^24)
+    __device__ __forceinline__ bool all_finite() const { return squares < __builtin_inff(); }  // false for NaN too
+    __device__ __forceinline__ long long units() const { return (long long)ldexp(even + odd, 1008 + 24); }
+};
+
+// the same count of 2^-24 with NaN and Inf left out
+template <int NG>
+__device__ __forceinline__ long long finite_magnitude_units(const uint4 (&x)[NG])
+{
+    double part = 0.0;
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint16_t h = half_of(x[g], i) & 0x7fff;
+            part += (double)(h < 0x7c00 ? half_bits_to_float(h) : 0.0f);
+        }
+    return double_units(part);
+}
+
+template <int NG>
+__device__ __forceinline__ long long magnitude_units(const uint4 (&x)[NG])
+{
+    MagnitudeSum sum;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) sum.add(x[g]);
+    return sum.all_finite() ? sum.units() : finite_magnitude_units(x);
+}
+
+// 8 halfs of a row from element k0 on, +0 beyond the row's end, in one 128-bit load whatever the
+// row's alignment (global loads need none here).  A group that reaches past the end reads the row's last 8
+// elements instead and drops the ones before k0, so no lane reads outside the row and every lane issues the
+// same load: request_group returns the load, finish_group (after all requests are out) the group.
+__device__ __forceinline__ uint4 request_group(const uint16_t *row, int k0, int K)
+{
+    uint4 q;
+    if (K >= 8) {
+        __builtin_memcpy(&q, row + (k0 <= K - 8 ? k0 : K - 8), 16);
+    } else {  // shorter than one load
+        uint16_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = k0 == 0 && i < K ? row[i] : (uint16_t)0;
+        __builtin_memcpy(&q, v, 16);
+    }
+    return q;
+}
+
+__device__ __forceinline__ uint4 finish_group(uint4 q, int k0, int K)
+{
+    const int drop = k0 + 8 - K;  // elements of the load that lie before k0
+    if (K >= 8 && drop > 0) {
+        if (drop >= 8) return make_uint4(0, 0, 0, 0);
+        unsigned long long lo = q.x | (unsigned long long)q.y << 32, hi = q.z | (unsigned long long)q.w << 32;
+        if (drop & 4) lo = hi, hi = 0;
+        const int s = 16 * (drop & 3);
+        if (s) lo = lo >> s | hi << (64 - s), hi >>= s;
+        q = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    }
+    return q;
+}
+
+// sum over L consecutive lanes (4 <= L <= 64); every lane gets it
+template <int L>
+__device__ __forceinline__ long long lane_group_sum(long long v)
+{
+    auto dpp = [](long long x, auto ctrl) {
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return (long long)((unsigned long long)(uint32_t)hi << 32 | (uint32_t)lo);
+    };
+    v += dpp(v, std::integral_constant<int, 0xb1>{});                 // quad_perm [1,0,3,2]
+    v += dpp(v, std::integral_constant<int, 0x4e>{});                 // quad_perm [2,3,0,1]
+    if (L >= 8) v += dpp(v, std::integral_constant<int, 0x141>{});    // row_half_mirror: lane i <-> 7 - i
+    if (L >= 16) v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror: i <-> 15 - i
+    if (L >= 32) v += __shfl_xor(v, 16);
+    if (L >= 64) v += __shfl_xor(v, 32);
+    return v;
+}
+
+// fp16(2 S / (K 2^24)) of a row whose magnitudes sum to S units of 2^-24
+__device__ __forceinline__ uint16_t scale_bits(long long S, int K)
+{
+    return double_to_half_bits((double)S / ((double)K * 8388608.0));
+}
+
+// s[m] = 2 * mean_k |A[m, k]| (exact integer sum, one division, one rounding).  Bound: HBM, one read of
+// A.  Rows up to 4096 elements: L lanes of one wavefront per row, NG groups of 8 elements per lane, no
+// barrier and no LDS; a wavefront takes R sets of 64 / L rows so that short rows still keep R NG loads
+// per lane in flight and share the reduction's and the division's fixed cost (each of the first R lanes
+// of a row's group finishes one of the R rows).  Measured on an attention block's operands against
+// one workgroup of 256 threads per row (whose barriers, 64-bit shuffles and division a row of 128 or 2048
+// elements cannot pay for): 65536 rows of 128: 61 -> 5.9 us; 65536 rows of 2048 (268 MB): 67 -> 39.5 us =
+// 6.8 TB/s.
+template <int L, int NG, int R>
+__global__ __launch_bounds__(kThreads) void k_act_scale_wave(const uint16_t *__restrict__ A, int64_t lda, int M, int K,
+                                                             uint16_t *__restrict__ s)
+{
+    constexpr int RPW = 64 / L;  // rows side by side in a wavefront
+    static_assert(R <= L, "one lane of a row's group per set");
+    const int lane = threadIdx.x & 63, cl = lane % L;
+    const int64_t row0 = ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * (R * RPW) + lane / L;
+    uint4 x[R][NG];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t m = row0 + r * RPW < M ? row0 + r * RPW : M - 1;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) x[r][g] = request_group(A + m * lda, 8 * (cl + L * g), K);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    long long mine = 0;  // lane r of the group keeps the sum of set r
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) x[r][g] = finish_group(x[r][g], 8 * (cl + L * g), K);
+        const long long S = lane_group_sum<L>(magnitude_units(x[r]));
+        mine = cl == r ? S : mine;
+    }
+    const int64_t m = row0 + cl * RPW;
+    if (cl < R && m < M) s[m] = scale_bits(mine, K);
+}
+
+// longer rows: one workgroup of NT threads per row
+template <int NG, int NT>
+__global__ __launch_bounds__(NT) void k_act_scale(const uint16_t *__restrict__ A, int64_t lda, int K,
+                                                        uint16_t *__restrict__ s)
+{
+    __shared__ long long s_ll[NT / 64];
+    const int64_t m = blockIdx.x;
+    uint4 x[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) x[g] = request_group(A + m * lda, 8 * ((int)threadIdx.x + NT * g), K);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) x[g] = finish_group(x[g], 8 * ((int)threadIdx.x + NT * g), K);
+    const long long part = lane_group_sum<64>(magnitude_units(x));
+    if ((threadIdx.x & 63) == 0) s_ll[threadIdx.x >> 6] = part;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        long long S = 0;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) S += s_ll[i];
+        s[m] = scale_bits(S, K);
+    }
 }
 
 // The same scale and, from the same registers, the ternarised row: one pass over A where
@@ -555,14 +705,25 @@ hipError_t launch_prepare_weights(const void *W, int64_t ldw, int N, int K, uint
 hipError_t launch_act_scale(const void *A, int64_t lda, int M, int K, uint16_t *s, hipStream_t st)
 {
     if (M == 0) return hipSuccess;
-    const int whole = (((uintptr_t)A % 16) == 0 && (lda % 8) == 0 && (K % 8) == 0) ? 1 : 0;
-    const int c8 = (K + 7) / 8;
+    const int c8 = (K + 7) / 8;  // K <= 32768 -> at most 4096
+    // a wavefront per 64 / L rows up to 64 x 8 groups: beyond that the row would need more than 8 loads per
+    // lane and too few wavefronts would share a row's latency
+#define BWTA_SCALE_W(L_, NG_, R_)                                                                              \
+    if (c8 <= L_ * NG_) {                                                                                      \
+        const int64_t rows_per_wg = (kThreads / 64) * (64 / L_) * R_;                                          \
+        hipLaunchKernelGGL((k_act_scale_wave<L_, NG_, R_>), dim3((unsigned)((M + rows_per_wg - 1) / rows_per_wg)), \
+                           dim3(kThreads), 0, st, (const uint16_t *)A, lda, M, K, s);                          \
+        return hipGetLastError();                                                                              \
+    }
+    BWTA_SCALE_W(8, 1, 4) BWTA_SCALE_W(16, 1, 4) BWTA_SCALE_W(32, 1, 4) BWTA_SCALE_W(64, 1, 4)
+    BWTA_SCALE_W(64, 2, 2) BWTA_SCALE_W(64, 4, 1) BWTA_SCALE_W(64, 8, 1)
+#undef BWTA_SCALE_W
 #define BWTA_SCALE(NG_, NT_)                                                                                       \
     if (c8 <= NG_ * NT_) {                                                                                         \
-        hipLaunchKernelGGL((k_act_scale<NG_, NT_>), dim3(M), dim3(NT_), 0, st, (const uint16_t *)A, lda, K, s, whole); \
+        hipLaunchKernelGGL((k_act_scale<NG_, NT_>), dim3(M), dim3(NT_), 0, st, (const uint16_t *)A, lda, K, s);    \
         return hipGetLastError();                                                                                  \
     }
-    BWTA_SCALE(1, 256) BWTA_SCALE(2, 256) BWTA_SCALE(4, 256) BWTA_SCALE(8, 256) BWTA_SCALE(4, 1024)
+    BWTA_SCALE(4, 256) BWTA_SCALE(6, 256) BWTA_SCALE(8, 256) BWTA_SCALE(16, 256)
 #undef BWTA_SCALE
     return hipErrorInvalidValue;
 }

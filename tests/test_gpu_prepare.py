@@ -71,6 +71,36 @@ def test_act_scale_matches_oracle(M, K, lda):
     assert same_half(got, want)
 
 
+# row lengths on both sides of every change of lanes per row, groups per lane and rows per wavefront,
+# rows shorter than one load, and lengths that leave 1..7 elements in the last load
+SCALE_K = [1, 3, 7, 8, 9, 63, 64, 65, 127, 128, 130, 256, 257, 511, 512, 515, 1024, 1029, 2048, 2054, 4096, 4103, 8192,
+           8193, 12288, 12290, 16384, 16390]
+
+
+@pytest.mark.parametrize("K", SCALE_K)
+@pytest.mark.parametrize("M", [1, 67])
+def test_act_scale_at_the_edges_of_its_row_splits(M, K):
+    """Exact at every split: odd leading dimensions (rows start on any 2-byte boundary), a row with
+    NaN and Inf beside finite ones, subnormals, the largest values, an all-zero row.  The row past the
+    last one's end is poisoned with NaN where the matrix has room for it."""
+    _say("act scale edges", M, K)
+    lda = K + 3
+    A = np.ascontiguousarray(synth.gaussian_outlier_activations(300 + K, 1, M, lda))
+    A[:, K:] = np.nan
+    A[0, K - 1] = np.float16(-65504.0)
+    if M > 4:
+        A[1, :K] = np.float16(6e-8)
+        A[2, :K:2] = np.nan
+        A[2, K - 1] = -np.inf
+        A[3, :K] = 0
+        A[4, :K] = np.float16(65504.0)
+    want = oracle.act_scale(np.ascontiguousarray(A[:, :K]))
+    s = torch.full((M,), float("nan"), dtype=torch.float16, device=DEV)
+    B.bwta_act_scale(dev(A), s, M=M, K=K, lda=lda)
+    torch.cuda.synchronize()
+    assert same_half(s.cpu().numpy(), want)
+
+
 def test_prepared_weights_feed_the_linear_layer():
     """fp16 checkpoint -> prepare -> BWTA linear equals the oracle's chain on the same inputs."""
     M, N, K = 70, 130, 1000
