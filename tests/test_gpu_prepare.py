@@ -153,3 +153,27 @@ def test_scale_and_ternarise_in_one_pass(M, N, K, lda, path):
     assert max_rel_err(got_s.reshape(1, -1), s_want.reshape(1, -1)) <= 1e-3
     assert same_half(got_s, s_want)
     assert same_half(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("K", [1, 7, 129, 512, 513, 1024, 1031, 2048, 2050, 4096, 4100, 6144, 6150, 8192, 8195, 11264, 11270,
+                               16384, 16385])
+def test_one_pass_fragments_at_the_edges_of_their_row_splits(K):
+    """Fragments of bwta_prepare_act_autoscale against bwta_act_scale + bwta_prepare_act (both held to the
+    oracle above), bit for bit over the whole padded operand: row lengths around every change of
+    wavefronts and groups per thread, a row count that leaves padding rows, rows on odd addresses."""
+    M, lda = 133, K + 1
+    _say("one-pass fragments", M, K)
+    A = np.ascontiguousarray(synth.gaussian_outlier_activations(400 + K, 1, M, lda))
+    A[:, K:] = np.nan
+    A[1, K - 1] = np.inf
+    A[2, :] = 0
+    dA = dev(A)
+    n = B.prepared_bytes(M, K)
+    one, two = (torch.zeros(n, dtype=torch.uint8, device=DEV) for _ in range(2))
+    s1, s2 = (torch.full((M,), float("nan"), dtype=torch.float16, device=DEV) for _ in range(2))
+    f1 = B.bwta_prepare_act_autoscale(dA, s1, one, M=M, K=K, lda=lda)
+    B.bwta_act_scale(dA, s2, M=M, K=K, lda=lda)
+    f2 = B.bwta_prepare_act(dA, s2, two, M=M, K=K, lda=lda)
+    torch.cuda.synchronize()
+    assert f1 == f2 == B.PREPARED_FP4
+    assert same_half(s1.cpu().numpy(), s2.cpu().numpy()) and torch.equal(one, two)
