@@ -2,8 +2,6 @@
 // equations; "Instruction-level Parallel Bitpack").  Bandwidth-bound streaming kernels: every
 // lane takes 8 consecutive elements with one 128-bit (fp16) or 64-bit (int8) load, turns them
 // into one byte per plane, and the four lanes of a quad assemble a 32-bit plane word.
-#include <type_traits>
-
 #include "bwta_internal.h"
 
 namespace bwta {
@@ -18,8 +16,8 @@ constexpr int64_t kQuadGroupMinThreads = 1024 * kThreads;
 __device__ __forceinline__ uint32_t quad_word(uint32_t byte, int lane)
 {
     uint32_t v = byte << (8 * (lane & 3));
-    v |= __shfl_xor(v, 1);
-    v |= __shfl_xor(v, 2);
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true);  // quad_perm [1,0,3,2]
+    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, true);  // quad_perm [2,3,0,1]
     return v;
 }
 
@@ -251,83 +249,6 @@ __device__ __forceinline__ uint16_t double_to_half_bits(double x)
     return (uint16_t)(((e + 15) << 10) | (int)(q - 1024));
 }
 
-template <int NT, typename T>
-__device__ __forceinline__ T block_sum(T v, T *scratch /* [NT / 64] */)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    __syncthreads();  // scratch may still be read from a previous call
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-    __syncthreads();
-    T r = scratch[0];
-#pragma unroll
-    for (int i = 1; i < NT / 64; ++i) r += scratch[i];
-    return r;
-}
-
-__device__ __forceinline__ void load8_halfs(const uint16_t *row, int k0, int nvalid, bool vec_ok, uint16_t v[8])
-{
-    if (nvalid == 8 && vec_ok) {
-        const uint4 q = *(const uint4 *)(row + k0);
-        v[0] = q.x & 0xffff; v[1] = q.x >> 16; v[2] = q.y & 0xffff; v[3] = q.y >> 16;
-        v[4] = q.z & 0xffff; v[5] = q.z >> 16; v[6] = q.w & 0xffff; v[7] = q.w >> 16;
-    } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = i < nvalid ? row[k0 + i] : (uint16_t)0;
-    }
-}
-
-// two sums at once (one pair of barriers); every thread gets both
-template <int NT>
-__device__ __forceinline__ void block_sum2(long long &a, long long &b, long long *scratch /* [2 * NT / 64] */)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        a += __shfl_xor(a, off);
-        b += __shfl_xor(b, off);
-    }
-    __syncthreads();  // scratch may still be read from a previous call
-    if ((threadIdx.x & 63) == 0) {
-        scratch[2 * (threadIdx.x >> 6)] = a;
-        scratch[2 * (threadIdx.x >> 6) + 1] = b;
-    }
-    __syncthreads();
-    a = scratch[0], b = scratch[1];
-#pragma unroll
-    for (int i = 1; i < NT / 64; ++i) a += scratch[2 * i], b += scratch[2 * i + 1];
-}
-
-// The row of a workgroup of NT threads, 8 halfs per 128-bit register, NG registers per thread (group g
-// of thread t is byte-group t + NT g).  Few, long-lived wavefronts per row: the reductions, the
-// division and the bound are a fixed cost per wavefront that dwarfs the per-element work.  All requests go out before the first value is used; the second
-// pass of the weight preparation reads the registers, not memory.  Padding and out-of-row groups
-// read as +0 (and are kept out of every count by nvalid).
-template <int NG, int NT>
-__device__ __forceinline__ void load_row_groups(const uint16_t *row, int K, int c8, bool whole, uint4 (&x)[NG])
-{
-    if (whole) {  // 16-byte aligned rows, K a multiple of 8: every group is whole or absent
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const int k0 = 8 * ((int)threadIdx.x + NT * g);
-            x[g] = *(const uint4 *)(k0 < K ? row + k0 : row);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int g = 0; g < NG; ++g)
-            if (8 * ((int)threadIdx.x + NT * g) >= K) x[g] = make_uint4(0, 0, 0, 0);
-    } else {
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const int c = (int)threadIdx.x + NT * g, k0 = 8 * c;
-            const int nvalid = c < c8 ? (K - k0 >= 8 ? 8 : (K - k0 > 0 ? K - k0 : 0)) : 0;
-            uint16_t v[8];
-            load8_halfs(row, k0, nvalid, false, v);
-            x[g] = make_uint4(v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16),
-                              v[4] | ((uint32_t)v[5] << 16), v[6] | ((uint32_t)v[7] << 16));
-        }
-    }
-}
-
 __device__ __forceinline__ uint16_t half_of(const uint4 &q, int i)
 {
     const uint32_t w = i < 2 ? q.x : (i < 4 ? q.y : (i < 6 ? q.z : q.w));
@@ -357,78 +278,6 @@ __device__ __forceinline__ float half_grid_ceil(long long c)
     return negative ? -v : v;
 }
 
-// One workgroup per output channel: mean (exact), sign(W - mean) packed like bwta_pack_weights,
-// s_w = mean |W - mean|.  With X the integer count of 2^-24 of an element and S the row's exact sum,
-// "W - mean < 0" is X K < S, i.e. X < ceil(S / K): one float compare against the bound above.  The
-// sum of |X K - S| over the finite elements equals K (S - 2 Sn) - S (n - 2 nn) with Sn, nn the sum
-// and count of the finite elements below the mean and n the count of finite elements, so the second
-// pass needs only exact per-thread sums again; the final combination is done in double (one
-// division, one rounding to binary16).
-template <int NG, int NT>
-__global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restrict__ W, int64_t ldw, int K,
-                                                              int rw, uint32_t *__restrict__ wsign,
-                                                              uint16_t *__restrict__ s_w, int whole)
-{
-    __shared__ long long s_ll[2 * NT / 64];
-    __shared__ float s_bound;
-    const int n = blockIdx.x, c8 = rw * 4, lane = threadIdx.x & 63;
-    uint4 x[NG];
-    load_row_groups<NG, NT>(W + (int64_t)n * ldw, K, c8, whole != 0, x);
-
-    double part = 0.0;
-    int nfin = 0;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {  // elements past K were loaded as +0: finite, and they add nothing
-            const uint16_t h = half_of(x[g], i);
-            const bool fin = (h & 0x7c00) != 0x7c00;
-            part += (double)(fin ? half_bits_to_float(h) : 0.0f);
-            nfin += fin ? 0 : 1;  // counts the non-finite ones
-        }
-    }
-    long long S = double_units(part), NF = nfin;
-    block_sum2<NT>(S, NF, s_ll);
-    NF = K - NF;  // finite elements of the row
-    if (threadIdx.x == 0) {  // one 64-bit division per row, not per wavefront
-        const long long q = S / K, r = S - q * K;
-        s_bound = half_grid_ceil(q + (r > 0 ? 1 : 0));  // ceil(S / K)
-    }
-    __syncthreads();
-    const float bound = s_bound;
-    // The second pass recomputes its per-element predicates from the registers: kept opaque here,
-    // or the compiler carries 64 of them per thread across the barriers in spilled scalar registers.
-#pragma unroll
-    for (int g = 0; g < NG; ++g) asm volatile("" : "+v"(x[g].x), "+v"(x[g].y), "+v"(x[g].z), "+v"(x[g].w));
-
-    double below = 0.0;
-    int nbelow = 0;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        const int c = (int)threadIdx.x + NT * g, k0 = 8 * c;
-        uint32_t bits = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint16_t h = half_of(x[g], i);
-            const float f = half_bits_to_float(h);
-            const bool inside = k0 + i < K;
-            const bool neg = inside && !(f >= bound);  // NaN and -Inf -> -1, +Inf -> +1
-            const bool fin_neg = neg && (h & 0x7c00) != 0x7c00;
-            bits |= (uint32_t)neg << i;
-            below += (double)(fin_neg ? f : 0.0f);
-            nbelow += fin_neg ? 1 : 0;
-        }
-        const uint32_t word = quad_word(bits, lane);  // whole quads stay together: c8 is a multiple of 4
-        if (c < c8 && (lane & 3) == 0) wsign[(int64_t)n * rw + (c >> 2)] = word;
-    }
-    long long SN = double_units(below), NN = nbelow;
-    block_sum2<NT>(SN, NN, s_ll);
-    if (threadIdx.x == 0) {
-        const double T = (double)K * (double)(S - 2 * SN) - (double)S * (double)(NF - 2 * NN);
-        s_w[n] = double_to_half_bits(T / ((double)K * (double)K * 16777216.0));
-    }
-}
-
 // ---- exact sums of binary16 magnitudes ----------------------------------------------------------
 //
 // The 15 magnitude bits of a binary16 value, put at the same place of a double (exponent field on
@@ -439,6 +288,17 @@ __global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restri
 // sums are exact (at most 128 values, see double_units) with binary64 subnormals on, the HIP default.
 // Non-finite values are noticed from the sum of squares, one dot-product instruction per two
 // values; a thread that holds one adds its values again with the exclusion.
+__device__ __forceinline__ float add_squares(uint32_t two, float sum)
+{
+    typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+    half2_t h;
+    __builtin_memcpy(&h, &two, 4);
+    return __builtin_amdgcn_fdot2(h, h, sum, false);
+}
+
+// false for Inf and for NaN; on the bits, because the compiler takes the dot product to be never NaN
+__device__ __forceinline__ bool is_finite_sum(float squares) { return (__float_as_uint(squares) & 0x7f800000u) != 0x7f800000u; }
+
 struct MagnitudeSum {
     double even = 0.0, odd = 0.0;
     float squares = 0.0f;
@@ -450,13 +310,10 @@ struct MagnitudeSum {
         for (int i = 0; i < 4; ++i) {
             even += __hiloint2double((int)((w[i] << 10) & 0x01fffc00u), 0);
             odd += __hiloint2double((int)((w[i] >> 6) & 0x01fffc00u), 0);
-            typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-            half2_t h;
-            __builtin_memcpy(&h, &w[i], 4);
-            squares = __builtin_amdgcn_fdot2(h, h, squares, false);
+            squares = add_squares(w[i], squares);
         }
     }
-    __device__ __forceinline__ bool all_finite() const { return squares < __builtin_inff(); }  // false for NaN too
+    __device__ __forceinline__ bool all_finite() const { return is_finite_sum(squares); }
     __device__ __forceinline__ long long units() const { return (long long)ldexp(even + odd, 1008 + 24); }
 };
 
@@ -488,24 +345,28 @@ __device__ __forceinline__ long long magnitude_units(const uint4 (&x)[NG])
 // row's alignment (global loads need none here).  A group that reaches past the end reads the row's last 8
 // elements instead and drops the ones before k0, so no lane reads outside the row and every lane issues the
 // same load: request_group returns the load, finish_group (after all requests are out) the group.
+// K >= 8; short_row_group stands in for both on shorter rows.
 __device__ __forceinline__ uint4 request_group(const uint16_t *row, int k0, int K)
 {
     uint4 q;
-    if (K >= 8) {
-        __builtin_memcpy(&q, row + (k0 <= K - 8 ? k0 : K - 8), 16);
-    } else {  // shorter than one load
-        uint16_t v[8];
+    __builtin_memcpy(&q, row + (k0 <= K - 8 ? k0 : K - 8), 16);
+    return q;
+}
+
+__device__ __forceinline__ uint4 short_row_group(const uint16_t *row, int k0, int K)
+{
+    uint16_t v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = k0 == 0 && i < K ? row[i] : (uint16_t)0;
-        __builtin_memcpy(&q, v, 16);
-    }
+    for (int i = 0; i < 8; ++i) v[i] = k0 == 0 && i < K ? row[i] : (uint16_t)0;
+    uint4 q;
+    __builtin_memcpy(&q, v, 16);
     return q;
 }
 
 __device__ __forceinline__ uint4 finish_group(uint4 q, int k0, int K)
 {
     const int drop = k0 + 8 - K;  // elements of the load that lie before k0
-    if (K >= 8 && drop > 0) {
+    if (drop > 0) {
         if (drop >= 8) return make_uint4(0, 0, 0, 0);
         unsigned long long lo = q.x | (unsigned long long)q.y << 32, hi = q.z | (unsigned long long)q.w << 32;
         if (drop & 4) lo = hi, hi = 0;
@@ -521,28 +382,41 @@ __device__ __forceinline__ uint4 finish_group(uint4 q, int k0, int K)
 template <int NG>
 __device__ __forceinline__ void load_row(const uint16_t *row, int first, int step, int K, uint4 (&x)[NG])
 {
+    if (K >= 8) {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) x[g] = request_group(row, 8 * (first + step * g), K);
-    __builtin_amdgcn_sched_barrier(0);
-    if (8 * step * NG > K) {
+        for (int g = 0; g < NG; ++g) x[g] = request_group(row, 8 * (first + step * g), K);
+        __builtin_amdgcn_sched_barrier(0);
+        if (8 * step * NG > K) {
 #pragma unroll
-        for (int g = 0; g < NG; ++g) x[g] = finish_group(x[g], 8 * (first + step * g), K);
+            for (int g = 0; g < NG; ++g) x[g] = finish_group(x[g], 8 * (first + step * g), K);
+        }
+    } else {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) x[g] = short_row_group(row, 8 * (first + step * g), K);
     }
 }
 
 // sum over L consecutive lanes (4 <= L <= 64); every lane gets it
-template <int L>
-__device__ __forceinline__ long long lane_group_sum(long long v)
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int x)
 {
-    auto dpp = [](long long x, auto ctrl) {
-        const int lo = __builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xf, 0xf, true);
-        const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
-        return (long long)((unsigned long long)(uint32_t)hi << 32 | (uint32_t)lo);
-    };
-    v += dpp(v, std::integral_constant<int, 0xb1>{});                 // quad_perm [1,0,3,2]
-    v += dpp(v, std::integral_constant<int, 0x4e>{});                 // quad_perm [2,3,0,1]
-    if (L >= 8) v += dpp(v, std::integral_constant<int, 0x141>{});    // row_half_mirror: lane i <-> 7 - i
-    if (L >= 16) v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror: i <-> 15 - i
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true);
+}
+
+template <int CTRL>
+__device__ __forceinline__ long long dpp_move(long long x)
+{
+    return (long long)((unsigned long long)(uint32_t)dpp_move<CTRL>((int)(x >> 32)) << 32 |
+                       (uint32_t)dpp_move<CTRL>((int)x));
+}
+
+template <int L, typename T>
+__device__ __forceinline__ T lane_group_sum(T v)
+{
+    v += dpp_move<0xb1>(v);                 // quad_perm [1,0,3,2]
+    v += dpp_move<0x4e>(v);                 // quad_perm [2,3,0,1]
+    if (L >= 8) v += dpp_move<0x141>(v);    // row_half_mirror: lane i <-> 7 - i
+    if (L >= 16) v += dpp_move<0x140>(v);   // row_mirror: i <-> 15 - i
     if (L >= 32) v += __shfl_xor(v, 16);
     if (L >= 64) v += __shfl_xor(v, 32);
     return v;
@@ -571,17 +445,23 @@ __global__ __launch_bounds__(kThreads) void k_act_scale_wave(const uint16_t *__r
     const int lane = threadIdx.x & 63, cl = lane % L;
     const int64_t row0 = ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * (R * RPW) + lane / L;
     uint4 x[R][NG];
+    auto row_of = [&](int r) { return A + (row0 + r * RPW < M ? row0 + r * RPW : M - 1) * lda; };
+    if (K >= 8) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t m = row0 + r * RPW < M ? row0 + r * RPW : M - 1;
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int g = 0; g < NG; ++g) x[r][g] = request_group(A + m * lda, 8 * (cl + L * g), K);
+            for (int g = 0; g < NG; ++g) x[r][g] = request_group(row_of(r), 8 * (cl + L * g), K);
+        __builtin_amdgcn_sched_barrier(0);
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int g = 0; g < NG; ++g) x[r][g] = short_row_group(row_of(r), 8 * (cl + L * g), K);
     }
-    __builtin_amdgcn_sched_barrier(0);
     long long mine = 0;  // lane r of the group keeps the sum of set r
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (8 * L * NG > K) {
+        if (K >= 8 && 8 * L * NG > K) {
 #pragma unroll
             for (int g = 0; g < NG; ++g) x[r][g] = finish_group(x[r][g], 8 * (cl + L * g), K);
         }
@@ -609,6 +489,173 @@ __global__ __launch_bounds__(NT) void k_act_scale(const uint16_t *__restrict__ A
 #pragma unroll
         for (int i = 0; i < NT / 64; ++i) S += s_ll[i];
         s[m] = scale_bits(S, K);
+    }
+}
+
+// One group of NT threads (a wavefront or a workgroup of 256) per output channel: mean (exact),
+// sign(W - mean) packed like bwta_pack_weights, s_w = mean |W - mean|.  With X the integer count of 2^-24
+// of an element and S the row's exact sum, "W - mean < 0" is X K < S, i.e. X < ceil(S / K): a compare of
+// binary16 values against the smallest one that is not below that bound.  The sum of |X K - S| over the
+// finite elements equals K (S - 2 Sn) - S (n - 2 nn) with Sn, nn the sum and count of the finite elements
+// below the mean and n the count of finite elements, so the second pass needs only exact per-thread
+// sums again; the final combination is done in double (one division, one rounding to binary16).
+// Bound: HBM.  The row stays in registers between the passes.  Both sums use the double form of a
+// binary16 value (MagnitudeSum above, here with its sign), the compare is one packed subtraction whose
+// sign survives rounding (ternary_thresholds) and one packed minimum per two elements, and a masked
+// element adds zero: about 11 instructions per element in all.  Wavefronts that hold a NaN or an Inf go
+// through their elements one by one instead.  A row of up to 4096 elements takes one wavefront and no barrier.
+// Measured on fp16 [4096, 11008], with two conversions and three selects per element and pass and a
+// padded 2048 groups per row before: 48.7 -> 24.0 us (4.0 TB/s), the vector ALU still ahead of HBM; one or
+// two wavefronts per row there are 4 to 15 % slower (registers), at K = 4096 one is 20 % ahead of four.
+struct SignedSum {
+    double even = 0.0, odd = 0.0;
+
+    __device__ __forceinline__ void add(uint32_t two)
+    {
+        int low;  // the low half's sign-extended bits << 10, in one instruction
+        asm("v_mad_i32_i16 %0, %1, %2, 0" : "=v"(low) : "v"(two), "s"(1024));
+        even += __hiloint2double(low & (int)0x81fffc00u, 0);
+        odd += __hiloint2double((int)two >> 6 & (int)0x81fffc00u, 0);
+    }
+    __device__ __forceinline__ long long units() const { return (long long)ldexp(even + odd, 1008 + 24); }
+};
+
+// the wavefront's sums; lane 0 of every wavefront leaves them in LDS when a row has several
+template <int NT>
+__device__ __forceinline__ void wave_sums(long long &a, int &b, long long *scratch /* [2 * NT / 64] */)
+{
+    a = lane_group_sum<64>(a);
+    if (__any(b != 0)) b = lane_group_sum<64>(b);
+    if constexpr (NT > 64) {
+        if ((threadIdx.x & 63) == 0) {
+            scratch[2 * (threadIdx.x >> 6)] = a;
+            scratch[2 * (threadIdx.x >> 6) + 1] = b;
+        }
+    }
+}
+
+template <int NT>
+__device__ __forceinline__ void row_sums(long long &a, int &b, const long long *scratch)
+{
+    if constexpr (NT > 64) {
+        a = scratch[0], b = (int)scratch[1];
+#pragma unroll
+        for (int i = 1; i < NT / 64; ++i) a += scratch[2 * i], b += (int)scratch[2 * i + 1];
+    }
+}
+
+template <int NG, int NT>
+__global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restrict__ W, int64_t ldw, int K, int rw,
+                                                        uint32_t *__restrict__ wsign, uint16_t *__restrict__ s_w)
+{
+    __shared__ long long s_mean[2 * NT / 64], s_below[2 * NT / 64];
+    const int64_t n = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const uint16_t *row = W + n * ldw;
+    uint4 x[NG];
+    load_row<NG>(row, threadIdx.x, NT, K, x);
+
+    SignedSum sum;
+    float squares = 0.0f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            sum.add(w[i]);
+            squares = add_squares(w[i], squares);
+        }
+    }
+    long long S = sum.units();
+    int NF = 0;  // non-finite elements
+    const bool finite = __all(is_finite_sum(squares));
+    if (!finite) {  // one by one, from memory again
+        double part = 0.0;
+#pragma unroll 1
+        for (int c = threadIdx.x; 8 * c < K; c += NT)
+#pragma unroll 1
+            for (int k = 8 * c; k < 8 * c + 8 && k < K; ++k) {
+                const uint16_t h = row[k];
+                const bool fin = (h & 0x7c00) != 0x7c00;
+                part += (double)(fin ? half_bits_to_float(h) : 0.0f);
+                NF += fin ? 0 : 1;
+            }
+        S = double_units(part);
+    }
+    wave_sums<NT>(S, NF, s_mean);
+    if constexpr (NT > 64) __syncthreads();
+    row_sums<NT>(S, NF, s_mean);
+    NF = K - NF;  // finite elements of the row
+    // ceil(S / K): the quotient in double is off by less than one, its remainder says which way
+    long long q = (long long)floor((double)S / (double)K);
+    long long r = S - q * K;
+    if (r < 0) --q, r += K;
+    if (r >= K) ++q, r -= K;
+    const float bound = half_grid_ceil(q + (r > 0 ? 1 : 0));
+    const _Float16 bound16 = (_Float16)bound;  // exact
+    uint16_t bbits;
+    __builtin_memcpy(&bbits, &bound16, 2);
+    const uint32_t bound2 = bbits * 0x10001u, one2 = 0x00010001u;
+    // The second pass works on the registers again: kept opaque here, or the compiler carries what the
+    // first one derived from them across the reduction.
+#pragma unroll
+    for (int g = 0; g < NG; ++g) asm volatile("" : "+v"(x[g].x), "+v"(x[g].y), "+v"(x[g].z), "+v"(x[g].w));
+
+    int NN = 0;
+    long long SN;
+    uint32_t *dst = wsign + n * rw;
+    auto finish = [&](int c, uint32_t bits) {
+        const int left = K - 8 * c;  // elements from here to the row's end
+        if (8 * NT * NG > K) bits &= (1u << (left >= 8 ? 8 : (left > 0 ? left : 0))) - 1u;  // +0 was loaded beyond it
+        NN += __popc(bits);
+        const uint32_t word = quad_word(bits, lane);  // whole quads stay together: rw is a multiple of 4
+        if (c < 4 * rw && (lane & 3) == 0) dst[c >> 2] = word;
+    };
+    if (finite) {
+        SignedSum low;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
+            uint32_t V = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t d, flag, keep;
+                asm("v_pk_add_f16 %0, %1, %2 neg_lo:[0,1] neg_hi:[0,1] clamp" : "=v"(d) : "v"(bound2), "v"(w[i]));
+                asm("v_pk_min_u16 %0, %1, %2" : "=v"(flag) : "v"(d), "v"(one2));  // 1 where x < bound
+                asm("v_pk_sub_i16 %0, 0, %1" : "=v"(keep) : "v"(flag));           // 0xffff there
+                V = flag << (2 * i) | V;
+                low.add(w[i] & keep);
+            }
+            int c = (int)threadIdx.x + NT * g;
+            asm volatile("" : "+v"(c));  // its conditions are evaluated here, not carried through the kernel
+            finish(c, (V & 0x55u) | (V >> 15 & 0xaau));
+        }
+        SN = low.units();
+    } else {
+        double low = 0.0;
+#pragma unroll 1
+        for (int c = threadIdx.x; c < NT * NG; c += NT) {
+            uint32_t bits = 0;
+#pragma unroll 1
+            for (int i = 0; i < 8 && 8 * c + i < K; ++i) {
+                const uint16_t h = row[8 * c + i];
+                const float f = half_bits_to_float(h);
+                const bool neg = !(f >= bound);  // NaN and -Inf -> -1, +Inf -> +1
+                const bool fin_neg = neg && (h & 0x7c00) != 0x7c00;
+                bits |= (uint32_t)neg << i;
+                low += (double)(fin_neg ? f : 0.0f);
+                NN -= neg && !fin_neg ? 1 : 0;  // counted with the others
+            }
+            finish(c, bits);
+        }
+        SN = double_units(low);
+    }
+    wave_sums<NT>(SN, NN, s_below);
+    if constexpr (NT > 64) __syncthreads();
+    if (threadIdx.x == 0) {
+        row_sums<NT>(SN, NN, s_below);
+        const double T = (double)K * (double)(S - 2 * SN) - (double)S * (double)(NF - 2 * NN);
+        s_w[n] = double_to_half_bits(T / ((double)K * (double)K * 16777216.0));
     }
 }
 
@@ -737,15 +784,15 @@ hipError_t launch_prepare_weights(const void *W, int64_t ldw, int N, int K, uint
 {
     if (N == 0) return hipSuccess;
     const int rw = 4 * ((K + 127) / 128);
-    const int whole = (((uintptr_t)W % 16) == 0 && (ldw % 8) == 0 && (K % 8) == 0) ? 1 : 0;
     const int c8 = rw * 4;  // 128-bit groups per row; K <= 32768 -> at most 4096
 #define BWTA_PREP(NG_, NT_)                                                                                   \
     if (c8 <= NG_ * NT_) {                                                                                    \
         hipLaunchKernelGGL((k_prepare_weights<NG_, NT_>), dim3(N), dim3(NT_), 0, st, (const uint16_t *)W, ldw, K, rw, \
-                           wsign, s_w, whole);                                                                \
+                           wsign, s_w);                                                                       \
         return hipGetLastError();                                                                             \
     }
-    BWTA_PREP(1, 256) BWTA_PREP(2, 256) BWTA_PREP(4, 256) BWTA_PREP(8, 256) BWTA_PREP(4, 1024)
+    BWTA_PREP(1, 64) BWTA_PREP(2, 64) BWTA_PREP(4, 64) BWTA_PREP(8, 64)
+    BWTA_PREP(4, 256) BWTA_PREP(6, 256) BWTA_PREP(8, 256) BWTA_PREP(16, 256)
 #undef BWTA_PREP
     return hipErrorInvalidValue;
 }

@@ -42,6 +42,29 @@ def test_prepare_weights_matches_oracle(N, K, ldw):
     assert same_half(sw, s)
 
 
+@pytest.mark.parametrize("K", [1, 5, 8, 127, 512, 515, 1024, 1025, 2048, 2055, 4096, 4098, 8192, 8200, 12288, 12290, 16384,
+                               16391])
+def test_prepare_weights_at_the_edges_of_its_row_splits(K):
+    """Row lengths around every change of threads per row and groups per thread, rows on odd addresses:
+    plain rows, a row with NaN / +-Inf in it (its wavefronts go element by element), rows whose mean is
+    positive (zeros beyond the row's end must not count as below it), subnormals, the largest values."""
+    N, ldw = 7, K + 1
+    _say("prepare weights edges", K)
+    W = (synth.gaussian(500 + K, 1, N * ldw) * 0.03).astype(np.float16).reshape(N, ldw)
+    W[1] += np.float16(0.05)
+    W[2, ::3] = [np.inf, -np.inf, np.nan][K % 3]
+    W[2, K - 1] = -np.inf
+    W[6, K // 2] = np.nan
+    W[3] = np.float16(6e-8) * synth.binary_pm1(500, K, (ldw,)).astype(np.float16)
+    W[4] = np.float16(65504.0)
+    W[5, ::2] = np.float16(-65504.0)
+    W[:, K:] = np.nan
+    w, s = oracle.prepare_weights(np.ascontiguousarray(W[:, :K]))
+    planes, sw = gpu_prepare(W, K)
+    assert np.array_equal(planes, oracle.pack_weights(w))
+    assert same_half(sw, s)
+
+
 def test_prepare_weights_special_rows():
     K = 300
     W = (synth.laplace(60, 1, 6 * K) * 0.02).astype(np.float16).reshape(6, K)
@@ -92,6 +115,7 @@ def test_act_scale_at_the_edges_of_its_row_splits(M, K):
         A[1, :K] = np.float16(6e-8)
         A[2, :K:2] = np.nan
         A[2, K - 1] = -np.inf
+        A[5, K // 2] = np.nan
         A[3, :K] = 0
         A[4, :K] = np.float16(65504.0)
     want = oracle.act_scale(np.ascontiguousarray(A[:, :K]))
