@@ -164,6 +164,70 @@ __device__ __forceinline__ uint32_t fragment_dword(const uint4 &x, const Ternary
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
+// the same predicates as one bit per element: bit i of `nz` for element i non-zero, of `neg` for negative.
+// BOOL: the bool function instead (1 iff x >= T): nz only.
+template <bool BOOL>
+__device__ __forceinline__ void ternary_flags(const uint4 &x, const TernaryThr &t, uint32_t &nz, uint32_t &neg)
+{
+    uint32_t w[4] = {x.x, x.y, x.z, x.w};
+    if (t.twice) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) asm("v_pk_add_f16 %0, %1, %1" : "=v"(w[d]) : "v"(w[d]));
+    }
+    uint32_t one2 = 0x00010001u, P = 0, N = 0;  // element 2 d in bit 2 d, element 2 d + 1 in bit 16 + 2 d
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        uint32_t p, n, gp, gn;
+        asm("v_pk_add_f16 %0, %1, %2 clamp" : "=v"(p) : "v"(w[d]), "v"(t.cp));
+        asm("v_pk_min_u16 %0, %1, %2" : "=v"(gp) : "v"(p), "v"(one2));
+        P = gp << (2 * d) | P;
+        if (!BOOL) {
+            asm("v_pk_add_f16 %0, %1, %2 neg_lo:[1,0] neg_hi:[1,0] clamp" : "=v"(n) : "v"(w[d]), "v"(t.cn));
+            asm("v_pk_min_u16 %0, %1, %2" : "=v"(gn) : "v"(n), "v"(one2));
+            N = gn << (2 * d) | N;
+        }
+    }
+    if (!BOOL) P |= N;
+    nz = (P & 0x55u) | (P >> 15 & 0xaau);
+    neg = BOOL ? 0u : (N & 0x55u) | (N >> 15 & 0xaau);
+}
+
+// 8 halfs of a row from element k0 on, +0 beyond the row's end, in one 128-bit load whatever the
+// row's alignment (global loads need none here).  A group that reaches past the end reads the row's last 8
+// elements instead and drops the ones before k0, so no lane reads outside the row and every lane issues the
+// same load: request_group returns the load, finish_group (after all requests are out) the group.
+// K >= 8; short_row_group stands in for both on shorter rows.
+__device__ __forceinline__ uint4 request_group(const uint16_t *row, int k0, int K)
+{
+    uint4 q;
+    __builtin_memcpy(&q, row + (k0 <= K - 8 ? k0 : K - 8), 16);
+    return q;
+}
+
+__device__ __forceinline__ uint4 short_row_group(const uint16_t *row, int k0, int K)
+{
+    uint16_t v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = k0 == 0 && i < K ? row[i] : (uint16_t)0;
+    uint4 q;
+    __builtin_memcpy(&q, v, 16);
+    return q;
+}
+
+__device__ __forceinline__ uint4 finish_group(uint4 q, int k0, int K)
+{
+    const int drop = k0 + 8 - K;  // elements of the load that lie before k0
+    if (drop > 0) {
+        if (drop >= 8) return make_uint4(0, 0, 0, 0);
+        unsigned long long lo = q.x | (unsigned long long)q.y << 32, hi = q.z | (unsigned long long)q.w << 32;
+        if (drop & 4) lo = hi, hi = 0;
+        const int s = 16 * (drop & 3);
+        if (s) lo = lo >> s | hi << (64 - s), hi >>= s;
+        q = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    }
+    return q;
+}
+
 __device__ __forceinline__ float load_scale(const ScaleArg &s, int row)
 {
     if (s.mode == 0 || s.ptr == nullptr) return 1.0f;

@@ -21,36 +21,12 @@ __device__ __forceinline__ uint32_t quad_word(uint32_t byte, int lane)
     return v;
 }
 
-struct TernaryBits {
-    uint32_t nz, neg;
-};
-
-// 8 fp16 values against the exact thresholds +-h (h = 0.5 * s in fp32, exact).
-__device__ __forceinline__ TernaryBits ternary_bits_fp16(const uint16_t v[8], int nvalid, float h, bool ok)
-{
-    TernaryBits r{0u, 0u};
-    // an invalid scale becomes a NaN threshold (every compare fails); elements past nvalid were
-    // loaded as +0 and fail both compares too, h being positive
-    (void)nvalid;
-    const float hp = ok ? h : __builtin_nanf(""), hn = -hp;
-    uint32_t both = 0;  // bits 0..7 non-zero flags, bits 8..15 negative flags
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float a = half_bits_to_float(v[i]);
-        uint32_t sel = a >= hp ? 1u : 0u;  // NaN fails both compares
-        sel = a < hn ? 0x101u : sel;
-        both = (sel << i) | both;
-    }
-    r.nz = both & 0xffu;
-    r.neg = both >> 8;
-    return r;
-}
-
+// One group of 8 elements per thread: small launches, rows of fewer than 8 elements, int8 input.
 template <int DTYPE>  // 0 = fp16 -> ternary, 1 = int8 ternary, 2 = fp16 -> boolean (the bool function: 1 iff a >= 0.5 s)
 __global__ __launch_bounds__(kThreads) void k_quantize_pack(const void *__restrict__ A, int64_t lda,
                                                             ScaleArg s_a, int M, int K, int rw,
                                                             uint32_t *__restrict__ mask,
-                                                            uint32_t *__restrict__ sign, int vec_ok)
+                                                            uint32_t *__restrict__ sign)
 {
     const int c8 = rw * 4;  // byte-groups (8 elements) per packed row, a multiple of 16
     const int64_t total = (int64_t)M * c8;
@@ -59,60 +35,52 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack(const void *__restri
     const int m = (int)(gid / c8);
     const int c = (int)(gid - (int64_t)m * c8);
     const int k0 = c * 8;
-    const int nvalid = K - k0 >= 8 ? 8 : (K - k0 > 0 ? K - k0 : 0);
-    TernaryBits tb{0u, 0u};
+    uint32_t nz = 0, neg = 0;
     if (DTYPE == 0 || DTYPE == 2) {
         // the scale is requested before the data and by every lane (without a scale: a dropped read
         // of the first element), so the two requests share one memory round trip
         const bool have_scale = s_a.mode != 0 && s_a.ptr != nullptr;
         const uint16_t s_bits = *(have_scale ? s_a.ptr + (s_a.mode == 1 ? 0 : m) : (const uint16_t *)A);
         const uint16_t *row = (const uint16_t *)A + (int64_t)m * lda;
-        uint16_t v[8];
-        if (nvalid == 8 && vec_ok) {
-            uint4 q = *(const uint4 *)(row + k0);
-            v[0] = q.x & 0xffff; v[1] = q.x >> 16; v[2] = q.y & 0xffff; v[3] = q.y >> 16;
-            v[4] = q.z & 0xffff; v[5] = q.z >> 16; v[6] = q.w & 0xffff; v[7] = q.w >> 16;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = i < nvalid ? row[k0 + i] : (uint16_t)0;
-        }
-        const float s = have_scale ? half_bits_to_float(s_bits) : 1.0f;
-        const bool ok = (s > 0.0f) && (s < __builtin_inff());
-        tb = ternary_bits_fp16(v, nvalid, 0.5f * s, ok);
-        if (DTYPE == 2) tb.nz &= ~tb.neg;  // boolean: only a >= 0.5 s counts, and there is no sign plane
+        const uint4 x = K >= 8 ? finish_group(request_group(row, k0, K), k0, K) : short_row_group(row, k0, K);
+        ternary_flags<DTYPE == 2>(x, ternary_thresholds(have_scale ? s_bits : 0x3c00u, true), nz, neg);
     } else {
         const int8_t *row = (const int8_t *)A + (int64_t)m * lda;
-        int8_t v[8];
-        if (nvalid == 8 && vec_ok) {
-            uint2 q = *(const uint2 *)(row + k0);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[i] = (int8_t)(q.x >> (8 * i));
-                v[4 + i] = (int8_t)(q.y >> (8 * i));
-            }
+        unsigned long long v = 0;
+        if (K >= 8) {  // as request_group / finish_group
+            __builtin_memcpy(&v, row + (k0 <= K - 8 ? k0 : K - 8), 8);
+            const int drop = k0 + 8 - K;
+            if (drop > 0) v = drop >= 8 ? 0 : v >> (8 * drop);
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = i < nvalid ? row[k0 + i] : (int8_t)0;
+            for (int i = 0; i < 8; ++i)
+                if (k0 == 0 && i < K) v |= (unsigned long long)(uint8_t)row[i] << (8 * i);
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            tb.nz |= (uint32_t)(v[i] != 0) << i;
-            tb.neg |= (uint32_t)(v[i] < 0) << i;
+            const int8_t e = (int8_t)(v >> (8 * i));
+            nz |= (uint32_t)(e != 0) << i;
+            neg |= (uint32_t)(e < 0) << i;
         }
     }
     const int lane = threadIdx.x & 63;
-    uint32_t wm = quad_word(tb.nz, lane);
-    uint32_t ws = quad_word(tb.neg, lane);
+    uint32_t wm = quad_word(nz, lane);
+    uint32_t ws = quad_word(neg, lane);
     const int64_t widx = (int64_t)m * rw + (c >> 2);
     if ((lane & 3) == 0) mask[widx] = wm;
     if (DTYPE != 2 && (lane & 3) == 1) sign[widx] = ws;
 }
 
-// The same operation for 16-byte aligned fp16 rows whose K is a multiple of 8 (every group of 8 is
-// whole or entirely padding): a thread takes four groups of one row, a quarter row apart, and
-// issues its scale request and all four 128-bit loads before anything is used, so four times the
-// bytes are in flight per wavefront.  Index space: row m, word w0 in the first quarter of the row,
-// quad lane q; group u is byte-group 4 (w0 + u rw / 4) + q.
+// The same operation for fp16 rows of at least 8 elements (any alignment): a thread takes four groups of
+// one row, a quarter row apart, and issues its scale request and all four 128-bit loads before anything is
+// used, so four times the bytes are in flight per wavefront.  Index space: row m, word w0 in the first
+// quarter of the row, quad lane q; group u is byte-group 4 (w0 + u rw / 4) + q.
+// Bound: HBM.  The thresholds are compared in packed half precision (ternary_flags: 1.5 instructions per
+// element for the bool function, 3 for the ternary one; converting and comparing in fp32 took 7 and kept
+// the vector ALU busy for as long as the memory): 65536 rows of 2048 (268 MB) 40 us = 6.7 TB/s either way,
+// 8192 rows (34 MB, in the L2) 4.7 us.  Workgroups take the rows in order: from the last to the first, to
+// meet in the memory-side cache what a scale pass just left there, loses the L2 of the own XCD and gains
+// nothing beyond it (scale + boolean pack of 34 MB: 14.2 against 10.1 us).
 template <int DTYPE>  // 0 = ternary, 2 = boolean
 __global__ __launch_bounds__(kThreads) void k_quantize_pack_vec(const uint16_t *__restrict__ A, int64_t lda,
                                                                 ScaleArg s_a, int M, int K, int rw,
@@ -130,24 +98,17 @@ __global__ __launch_bounds__(kThreads) void k_quantize_pack_vec(const uint16_t *
     const uint16_t *row = A + (int64_t)m * lda;
     uint4 x[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int k0 = 8 * (4 * (w0 + u * qw) + q);
-        x[u] = *(const uint4 *)(k0 < K ? row + k0 : A);  // padding groups re-read the first bytes and drop them
-    }
+    for (int u = 0; u < 4; ++u) x[u] = request_group(row, 8 * (4 * (w0 + u * qw) + q), K);
     __builtin_amdgcn_sched_barrier(0);
-    const float s = have_scale ? half_bits_to_float(s_bits) : 1.0f;
-    const bool ok = (s > 0.0f) && (s < __builtin_inff());
+    const TernaryThr thr = ternary_thresholds(have_scale ? s_bits : 0x3c00u, true);
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int w = w0 + u * qw, k0 = 8 * (4 * w + q);
-        const uint4 xv = k0 < K ? x[u] : make_uint4(0, 0, 0, 0);
-        const uint16_t v[8] = {(uint16_t)xv.x, (uint16_t)(xv.x >> 16), (uint16_t)xv.y, (uint16_t)(xv.y >> 16),
-                               (uint16_t)xv.z, (uint16_t)(xv.z >> 16), (uint16_t)xv.w, (uint16_t)(xv.w >> 16)};
-        TernaryBits tb = ternary_bits_fp16(v, 8, 0.5f * s, ok);
-        if (DTYPE == 2) tb.nz &= ~tb.neg;
-        const uint32_t wm = quad_word(tb.nz, lane);
-        const uint32_t ws = DTYPE == 2 ? 0u : quad_word(tb.neg, lane);
+        const int w = w0 + u * qw;
+        uint32_t nz, neg;
+        ternary_flags<DTYPE == 2>(finish_group(x[u], 8 * (4 * w + q), K), thr, nz, neg);
+        const uint32_t wm = quad_word(nz, lane);
+        const uint32_t ws = DTYPE == 2 ? 0u : quad_word(neg, lane);
         const int64_t widx = (int64_t)m * rw + w;
         if (live && q == 0) mask[widx] = wm;
         if (DTYPE != 2 && live && q == 1) sign[widx] = ws;
@@ -339,42 +300,6 @@ __device__ __forceinline__ long long magnitude_units(const uint4 (&x)[NG])
 #pragma unroll
     for (int g = 0; g < NG; ++g) sum.add(x[g]);
     return sum.all_finite() ? sum.units() : finite_magnitude_units(x);
-}
-
-// 8 halfs of a row from element k0 on, +0 beyond the row's end, in one 128-bit load whatever the
-// row's alignment (global loads need none here).  A group that reaches past the end reads the row's last 8
-// elements instead and drops the ones before k0, so no lane reads outside the row and every lane issues the
-// same load: request_group returns the load, finish_group (after all requests are out) the group.
-// K >= 8; short_row_group stands in for both on shorter rows.
-__device__ __forceinline__ uint4 request_group(const uint16_t *row, int k0, int K)
-{
-    uint4 q;
-    __builtin_memcpy(&q, row + (k0 <= K - 8 ? k0 : K - 8), 16);
-    return q;
-}
-
-__device__ __forceinline__ uint4 short_row_group(const uint16_t *row, int k0, int K)
-{
-    uint16_t v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = k0 == 0 && i < K ? row[i] : (uint16_t)0;
-    uint4 q;
-    __builtin_memcpy(&q, v, 16);
-    return q;
-}
-
-__device__ __forceinline__ uint4 finish_group(uint4 q, int k0, int K)
-{
-    const int drop = k0 + 8 - K;  // elements of the load that lie before k0
-    if (drop > 0) {
-        if (drop >= 8) return make_uint4(0, 0, 0, 0);
-        unsigned long long lo = q.x | (unsigned long long)q.y << 32, hi = q.z | (unsigned long long)q.w << 32;
-        if (drop & 4) lo = hi, hi = 0;
-        const int s = 16 * (drop & 3);
-        if (s) lo = lo >> s | hi << (64 - s), hi >>= s;
-        q = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
-    }
-    return q;
 }
 
 // groups first, first + step, ..: all requested before any is used; the row's end is only looked at by
@@ -686,8 +611,6 @@ __global__ __launch_bounds__(NT) void k_act_scale_quantize(const uint16_t *__res
     const uint16_t s_bits = m < M ? scale_bits(S, K) : (uint16_t)0;  // 0: an invalid scale, the row ternarises to zero
     if (threadIdx.x == 0 && m < M) s_out[m] = s_bits;
     // an all-zero (or all non-finite) row has s = 0, an invalid scale: the row ternarises to zero
-    const float sc = half_bits_to_float(s_bits);
-    const bool ok = sc > 0.0f && sc < __builtin_inff();
     const TernaryThr thr = ternary_thresholds(s_bits, true);
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -700,11 +623,9 @@ __global__ __launch_bounds__(NT) void k_act_scale_quantize(const uint16_t *__res
             if (step < s_pad)
                 frag[(((int64_t)(m >> 5) * s_pad + step) * 64 + half * 32 + (m & 31)) * 4 + j] = D;
         } else {
-            uint16_t v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = half_of(x[g], i);
-            const TernaryBits tb = ternary_bits_fp16(v, 8, 0.5f * sc, ok);
-            const uint32_t mw = quad_word(tb.nz, lane), sw = quad_word(tb.neg, lane);
+            uint32_t nz, neg;
+            ternary_flags<false>(x[g], thr, nz, neg);
+            const uint32_t mw = quad_word(nz, lane), sw = quad_word(neg, lane);
             if (q < rw && j == 0) {
                 mask[(int64_t)m * rw + q] = mw;
                 sign[(int64_t)m * rw + q] = sw;
@@ -864,17 +785,15 @@ hipError_t launch_quantize_pack(const void *A, int dtype, int64_t lda, ScaleArg 
     const int64_t total = (int64_t)M * rw * 4;
     if (total == 0) return hipSuccess;
     const unsigned grid = (unsigned)((total + kThreads - 1) / kThreads);
-    const int elt = dtype == 0 ? 2 : 1;
-    const int vec_ok = (((uintptr_t)A % (8 * elt)) == 0 && (lda % 8) == 0) ? 1 : 0;
-    if (dtype == 0 && vec_ok && (K % 8) == 0 && (int64_t)M * rw >= kQuadGroupMinThreads)
+    if (dtype == 0 && K >= 8 && (int64_t)M * rw >= kQuadGroupMinThreads)
         hipLaunchKernelGGL(k_quantize_pack_vec<0>, dim3((unsigned)(((int64_t)M * rw + kThreads - 1) / kThreads)),
                            dim3(kThreads), 0, st, (const uint16_t *)A, lda, s_a, M, K, rw, mask, sign);
     else if (dtype == 0)
         hipLaunchKernelGGL(k_quantize_pack<0>, dim3(grid), dim3(kThreads), 0, st, A, lda, s_a, M, K, rw,
-                           mask, sign, vec_ok);
+                           mask, sign);
     else
         hipLaunchKernelGGL(k_quantize_pack<1>, dim3(grid), dim3(kThreads), 0, st, A, lda, s_a, M, K, rw,
-                           mask, sign, vec_ok);
+                           mask, sign);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nnz == nullptr) return e;
     hipLaunchKernelGGL(k_row_popcount, dim3((M + 3) / 4), dim3(kThreads), 0, st, mask, M, rw, nnz);
@@ -888,13 +807,12 @@ hipError_t launch_quantize_pack_bool(const void *A, int64_t lda, ScaleArg s_a, i
     const int64_t total = (int64_t)M * rw * 4;
     if (total == 0) return hipSuccess;
     const unsigned grid = (unsigned)((total + kThreads - 1) / kThreads);
-    const int vec_ok = (((uintptr_t)A % 16) == 0 && (lda % 8) == 0) ? 1 : 0;
-    if (vec_ok && (K % 8) == 0 && (int64_t)M * rw >= kQuadGroupMinThreads)
+    if (K >= 8 && (int64_t)M * rw >= kQuadGroupMinThreads)
         hipLaunchKernelGGL(k_quantize_pack_vec<2>, dim3((unsigned)(((int64_t)M * rw + kThreads - 1) / kThreads)),
                            dim3(kThreads), 0, st, (const uint16_t *)A, lda, s_a, M, K, rw, mask, (uint32_t *)nullptr);
     else
         hipLaunchKernelGGL(k_quantize_pack<2>, dim3(grid), dim3(kThreads), 0, st, A, lda, s_a, M, K, rw, mask,
-                           (uint32_t *)nullptr, vec_ok);
+                           (uint32_t *)nullptr);
     return hipGetLastError();
 }
 

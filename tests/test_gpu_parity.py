@@ -70,6 +70,36 @@ def test_quantize_pack_fp16_large_aligned_rows(M, K, lda):
     assert all(np.array_equal(w, g) for w, g in zip(want, got))
 
 
+@pytest.mark.parametrize("M,K,lda,shift", [(3, 7, 7, 1), (5, 8, 9, 1), (4, 129, 131, 3), (2300, 3717, 3719, 1),
+                                           (40000, 200, 203, 5), (33000, 252, 252, 0)])
+def test_quantize_pack_rows_on_any_address(M, K, lda, shift):
+    """Rows that start on any element and end inside a group of 8, in the kernels of one and of four
+    groups per thread: ternary and boolean planes of fp16, ternary planes of int8.  What lies past a
+    row's end is NaN (fp16) or non-zero (int8) and must not show."""
+    _say("quantize rows on any address", M, K, lda, shift)
+    A, s = _activation_case(500 + K, M, K, lda)
+    A[:, K:] = np.nan
+    t = oracle.ternarize(np.ascontiguousarray(A[:, :K]), s)
+    mask, sign, _ = oracle.pack_act(t)
+    rw = B.plane_row_words(K)
+    m, g = (torch.full((M, rw), -1, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    flat = torch.full((shift + A.size,), float("nan"), dtype=torch.float16, device="cuda:0")
+    flat[shift:] = dev(A).reshape(-1)
+    B.bwta_quantize_pack_act(flat[shift:], dev(s), m, g, None, M=M, K=K, lda=lda)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_u32(m), mask) and np.array_equal(host_u32(g), sign)
+    B.bwta_quantize_pack_bool(flat[shift:], dev(s), m, M=M, K=K, lda=lda)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_u32(m), mask & ~sign)
+    t8 = np.full((M, lda), 1, np.int8)
+    t8[:, :K] = t
+    flat8 = torch.full((shift + t8.size,), 1, dtype=torch.int8, device="cuda:0")
+    flat8[shift:] = dev(t8).reshape(-1)
+    B.bwta_quantize_pack_act(flat8[shift:], None, m, g, None, M=M, K=K, lda=lda, a_dtype=B.DTYPE_INT8)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_u32(m), mask) and np.array_equal(host_u32(g), sign)
+
+
 def test_quantize_pack_scale_modes_and_bad_scales():
     M, K = 9, 200
     A, _ = _activation_case(7, M, K)
