@@ -207,7 +207,7 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
                          {(const uint16_t *)s_a, s_a ? a_scale_mode : BWTA_SCALE_NONE},
                          {(const uint16_t *)s_w, s_w ? w_scale_mode : BWTA_SCALE_NONE},
                          nullptr, (uint16_t *)out, ldo};
-        if (bwta::linear_fused_supported(A, lda, g))
+        if (bwta::linear_fused_supported(g))
             return hip_result(bwta::launch_linear_fused(A, lda, g, (hipStream_t)stream));
     }
     int format = 0;
@@ -525,11 +525,10 @@ int bwta_linear_launches(int M, int N, int K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
     if (resolve_path(M, N, K) != BWTA_PATH_FP4) return 2;
-    alignas(16) static const uint16_t dense[8] = {};  // stands for an aligned input; never read
     uint16_t sink = 0;
     bwta::GemmArgs g{nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
                      {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &sink, N};
-    return bwta::linear_fused_supported(dense, K, g) ? 1 : 2;
+    return bwta::linear_fused_supported(g) ? 1 : 2;
 }
 
 int bwta_planned_kernel(int operand, int M, int N, int K)

@@ -93,11 +93,8 @@ __device__ __forceinline__ void store_tile_fp16(const v16f (&acc)[WN][WM], const
                 typedef unsigned v4u __attribute__((ext_vector_type(4)));
                 const v4u qv = {q.x, q.y, q.z, q.w};
                 __builtin_nontemporal_store(qv, (v4u *)dst);  // streamed once, never re-read here
-            } else if (mo < g.M && n < g.N) {
-                const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (n + e < g.N) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            } else if (mo < g.M) {
+                store_halfs(dst, q, g.N - n);
             }
         }
         __builtin_amdgcn_wave_barrier();

@@ -537,9 +537,8 @@ __global__ __launch_bounds__(64 * NWV) void k_linear_fused(const uint16_t *__res
     uint4 x[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-        const int q = WPI * it + (quad >> 5), k0 = 32 * q + 8 * j;
-        const bool inb = m < g.M && k0 < g.K;  // lanes outside re-read the first bytes and drop them
-        x[it] = *(const uint4 *)(A + (inb ? (int64_t)m * lda + k0 : 0));
+        const int q = WPI * it + (quad >> 5);
+        x[it] = request_group(A + (int64_t)mc * lda, 32 * q + 8 * j, g.K);  // rows past M: row 0, ternarised to zero
     }
     const int r32 = lane & 31, h = lane >> 5;
     uint4 wq[NCH][FL_CB];
@@ -571,8 +570,7 @@ __global__ __launch_bounds__(64 * NWV) void k_linear_fused(const uint16_t *__res
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
         const int q = WPI * it + (quad >> 5), k0 = 32 * q + 8 * j;
-        uint4 v = x[it];
-        if (!(m < g.M && k0 < g.K)) v = make_uint4(0, 0, 0, 0);
+        const uint4 v = 256 * NCH > g.K ? finish_group(x[it], k0, g.K) : x[it];
         const uint32_t D = fragment_dword(v, thr, j);
         const int jw = q & 7, step = 4 * (q >> 3) + (jw & 3), half = jw >> 2;
         sA[(step * 64 + half * 32 + row) * 4 + j] = D;
@@ -652,14 +650,15 @@ hipError_t launch_quantize_to_fp4(const void *A, int64_t lda, ScaleArg s_a, int 
 // faster with K than the two-kernel form's, while its fixed cost is 2 us lower.  Measured over
 // M = 512 .. 16384, N = 768 .. 11008, K = 256 .. 1024 it is ahead everywhere for K <= 768 (by 5 to
 // 40 %: 13.1 -> 10.4 us at 4096 x 3072 x 768, 17.8 -> 11.3 us at 16384 x 768 x 768) and for K = 1024
-// up to N = 4096 and M = 8192; beyond, the two kernels win.
-bool linear_fused_supported(const void *A, int64_t lda, const GemmArgs &g)
+// up to N = 4096 and M = 8192; beyond, the two kernels win.  Rows of any address and length from 8
+// elements (one 128-bit request) are taken: 500 x 1001 x 515 10.2 -> 6.2 us, 3000 x 1537 x 700 21.3 -> 9.1 us
+// against the two kernels and their 2-byte stores into rows of odd length.
+bool linear_fused_supported(const GemmArgs &g)
 {
     const int mode = g_linear_fused.load(std::memory_order_relaxed);
     if (mode == 0) return false;
     const bool pays = g.K <= 768 || (g.N <= 4096 && g.M <= 8192);
-    return (pays || mode == 2) && g.K <= 1024 && g.N >= 128 && g.out != nullptr &&
-           g.acc == nullptr && ((uintptr_t)A % 16) == 0 && (lda % 8) == 0 && (g.K % 8) == 0;
+    return (pays || mode == 2) && g.K >= 8 && g.K <= 1024 && g.N >= 128 && g.out != nullptr && g.acc == nullptr;
 }
 
 hipError_t launch_linear_fused(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st)

@@ -377,11 +377,8 @@ __global__ __launch_bounds__(256, 2) void k_matmul_tt_fp4(MatmulTTArgs g)
                 if (full) {
                     const v4u qv = {qd.x, qd.y, qd.z, qd.w};
                     __builtin_nontemporal_store(qv, (v4u *)dst);  // streamed once, never re-read here
-                } else if (mo < g.M && n < g.N) {
-                    const uint32_t w[4] = {qd.x, qd.y, qd.z, qd.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (n + e < g.N) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                } else if (mo < g.M) {
+                    store_halfs(dst, qd, g.N - n);
                 }
             }
             __builtin_amdgcn_wave_barrier();

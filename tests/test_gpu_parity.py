@@ -519,6 +519,35 @@ def test_linear_one_launch_scale_modes_and_strides():
         B.set_tile(0)
 
 
+@pytest.mark.parametrize("M,N,K,tile", [(33, 129, 9, 0), (70, 131, 257, 0), (40, 200, 1023, 0), (300, 650, 768, 0),
+                                        (5, 130, 1500, 0), (300, 131, 1029, 0), (300, 261, 1100, 243), (150, 131, 1100, 223)])
+def test_linear_rows_on_any_address(M, N, K, tile):
+    """bwta_linear with input and output rows that start on odd elements, lengths that end inside a group
+    of 8 on both sides: the one-launch kernel, the decode kernel and the tiled kernels.  NaN lies
+    between the input rows; what lies between the output rows stays."""
+    _say("linear on any address", M, N, K, tile)
+    lda, ldo = K + 3, N + 2
+    A, s = _activation_case(900 + K, M, K, lda)
+    A[:, K:] = np.nan
+    w = synth.binary_pm1(901 + K, 2, (N, K))
+    s_w = synth.scales(901 + K, 3, N)
+    _, _, want = oracle.linear(np.ascontiguousarray(A[:, :K]), s, w, s_w)
+    a = torch.zeros(1 + A.size, dtype=torch.float16, device="cuda:0")
+    a[1:] = dev(A).reshape(-1)
+    out = torch.full((1 + M * ldo,), 7.0, dtype=torch.float16, device="cuda:0")
+    ws = torch.empty(B.workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda:0")
+    B.set_tile(tile)
+    try:
+        B.bwta_linear(a[1:], dev(s), gpu_pack_weights(w), dev(s_w), out[1:], ws, M=M, N=N, K=K, lda=lda, ldo=ldo)
+        torch.cuda.synchronize()
+    finally:
+        B.set_tile(0)
+    got = out.cpu().numpy()
+    rows = got[1:].reshape(M, ldo)
+    assert same_half(np.ascontiguousarray(rows[:, :N]), want)
+    assert got[0] == 7 and (rows[:, N:] == 7).all()
+
+
 def test_linear_strided_input_and_output():
     M, N, K, lda, ldo = 50, 72, 520, 528, 80
     A, s = _activation_case(9, M, lda)
