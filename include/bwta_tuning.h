@@ -26,7 +26,7 @@ enum {
 };
 int bwta_planned_kernel(int operand, int M, int N, int K);
 /* How many kernels bwta_linear launches for a shape under the current settings: 1 where
- * ternarisation, product and epilogue run as one kernel (short K), else 2.  Informational (benchmarks label their timings with it); 0 for a
+ * ternarisation, product and epilogue run as one kernel (short K, or one token), else 2.  Informational (benchmarks label their timings with it); 0 for a
  * non-positive dimension. */
 int bwta_linear_launches(int M, int N, int K);
 /* Tuning hook for benchmark sweeps: force the FP4 kernel's per-wavefront tile (22, 21, 12, 11, 13

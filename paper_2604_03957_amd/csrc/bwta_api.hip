@@ -89,6 +89,25 @@ int plan_from_planes(const bwta::GemmArgs &g, bool have_scratch)
     return BWTA_KERNEL_GEMM_POPC;
 }
 
+// which kernel computes bwta_linear from fp16 in one launch, if one does
+enum class OneLaunch { kNo, kShortK, kOneToken };
+
+// Activations and results that share memory (a caller working in place): with two kernels the activations
+// have been read before the first result is written, with one they have not.
+bool rows_overlap(const void *A, int64_t lda, int K, const void *out, int64_t ldo, int N, int M)
+{
+    const uintptr_t a = (uintptr_t)A, o = (uintptr_t)out;
+    return a < o + 2 * (uintptr_t)((M - 1) * ldo + N) && o < a + 2 * (uintptr_t)((M - 1) * lda + K);
+}
+
+OneLaunch one_launch_linear(const bwta::GemmArgs &g)
+{
+    const int path = resolve_path(g.M, g.N, g.K);
+    if (path == BWTA_PATH_FP4 && bwta::linear_fused_supported(g)) return OneLaunch::kShortK;
+    if (path == BWTA_PATH_POPC && bwta::linear_one_supported(g)) return OneLaunch::kOneToken;
+    return OneLaunch::kNo;
+}
+
 // workspace layout: [mask planes | sign planes | FP4 activation fragments]
 int run_gemm(const bwta::GemmArgs &g, void *workspace, hipStream_t st)
 {
@@ -202,13 +221,16 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
     if (!aligned(A, 2) || !aligned(wsign, 16)) return BWTA_ERR_ALIGN;
     if (!workspace || workspace_bytes < bwta_workspace_bytes(M, N, K)) return BWTA_ERR_WORKSPACE;
     if (!aligned(workspace, 256)) return BWTA_ERR_ALIGN;
-    if (resolve_path(M, N, K) == BWTA_PATH_FP4) {
-        bwta::GemmArgs g{nullptr, nullptr, wsign, M, N, K, (int)bwta_plane_row_words(K),
-                         {(const uint16_t *)s_a, s_a ? a_scale_mode : BWTA_SCALE_NONE},
-                         {(const uint16_t *)s_w, s_w ? w_scale_mode : BWTA_SCALE_NONE},
-                         nullptr, (uint16_t *)out, ldo};
-        if (bwta::linear_fused_supported(g))
-            return hip_result(bwta::launch_linear_fused(A, lda, g, (hipStream_t)stream));
+    const bwta::GemmArgs g{nullptr, nullptr, wsign, M, N, K, (int)bwta_plane_row_words(K),
+                           {(const uint16_t *)s_a, s_a ? a_scale_mode : BWTA_SCALE_NONE},
+                           {(const uint16_t *)s_w, s_w ? w_scale_mode : BWTA_SCALE_NONE},
+                           nullptr, (uint16_t *)out, ldo};
+    switch (one_launch_linear(g)) {
+    case OneLaunch::kShortK: return hip_result(bwta::launch_linear_fused(A, lda, g, (hipStream_t)stream));
+    case OneLaunch::kOneToken:
+        if (rows_overlap(A, lda, K, out, ldo, N, M)) break;
+        return hip_result(bwta::launch_linear_one(A, g, (hipStream_t)stream));
+    default: break;
     }
     int format = 0;
     rc = bwta_prepare_act(A, lda, s_a, a_scale_mode, M, K, workspace, workspace_bytes, &format, stream);
@@ -524,11 +546,10 @@ int bwta_auto_path(int M, int N, int K)
 int bwta_linear_launches(int M, int N, int K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    if (resolve_path(M, N, K) != BWTA_PATH_FP4) return 2;
     uint16_t sink = 0;
     bwta::GemmArgs g{nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
                      {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &sink, N};
-    return bwta::linear_fused_supported(g) ? 1 : 2;
+    return one_launch_linear(g) != OneLaunch::kNo ? 1 : 2;
 }
 
 int bwta_planned_kernel(int operand, int M, int N, int K)

@@ -62,6 +62,9 @@ void set_fp4_tile(int t);
 bool linear_fused_supported(const GemmArgs &g);
 hipError_t launch_linear_fused(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);
 void set_linear_fused(int mode, int r);
+// the whole linear of one token in one launch (fp16 in, fp16 out)
+bool linear_one_supported(const GemmArgs &g);
+hipError_t launch_linear_one(const void *A, const GemmArgs &g, hipStream_t st);
 hipError_t launch_att_v_fp4(const GemmArgs &g, const uint32_t *frag, int batch, int64_t w_stride_words,
                             int64_t out_stride, float alpha, hipStream_t st);
 void set_gemv_tile(int g, int nch);

@@ -9,6 +9,7 @@
 // token each.  One launch can walk several problems of the same shape (grid.y), which is how a
 // decode step's independent matrices (or a bandwidth measurement) share one dispatch.
 #include <atomic>
+#include <type_traits>
 
 #include "bwta_internal.h"
 
@@ -61,12 +62,18 @@ struct GemvShape {
     int64_t ldo;
 };
 
-template <int MT, int G, int NCH, int UNR, bool NT>
-__global__ __launch_bounds__(256) void k_gemv_popc(GemvBatch b, GemvShape sh)
+// FP16: one token from its fp16 values (the whole linear in one launch): `act` holds K of them, b.mask and
+// b.sign are not read, and every workgroup ternarises the row into LDS itself.  A few instructions per
+// thread, under the wait for the weights, instead of a kernel in front and the gap between the two:
+// bwta_linear on
+// 1 x 11008 x 4096 8.6 -> 5.4 us a call (kernels of 2.8 + 3.9 us -> one of 3.9, the rest the host's share).
+template <int MT, int G, int NCH, int UNR, bool NT, bool FP16>
+__device__ __forceinline__ void gemv_popc(const GemvBatch &b, const GemvShape &sh, const uint16_t *act, int K)
 {
+    static_assert(!FP16 || MT == 1, "one token's row is ternarised");
     const int lane = threadIdx.x & 63;
     const int gw = blockIdx.x * 4 + (threadIdx.x >> 6);  // wavefront id within the problem
-    const int p = blockIdx.y;
+    const int p = FP16 ? 0 : blockIdx.y;
     constexpr int RPP = 64 / G;  // rows per pass of one wavefront
     const int sub = lane / G, cl = lane % G;
     const int rw = sh.rw;
@@ -103,7 +110,7 @@ __global__ __launch_bounds__(256) void k_gemv_popc(GemvBatch b, GemvShape sh)
     // chunks it needs in registers.  Layout: [token][plane][chunk] of 16 bytes.
     extern __shared__ __attribute__((aligned(16))) uint4 s_act[];
     constexpr int NSTAGE = (MT * 2 * G * NCH + 255) / 256;  // staging loads per thread
-    constexpr bool EARLY = NSTAGE <= 2;  // more rows than that are staged by a loop behind the weights
+    constexpr bool EARLY = NSTAGE <= 2 && !FP16;  // more rows than that are staged by a loop behind the weights
     constexpr int NST = EARLY ? NSTAGE : 0;
     const int act_pieces = sh.M * 2 * sh.C4;
     uint4 stage[NST > 0 ? NST : 1];
@@ -113,6 +120,15 @@ __global__ __launch_bounds__(256) void k_gemv_popc(GemvBatch b, GemvShape sh)
         const int ic = idx < act_pieces ? idx : 0;
         const int c = ic % sh.C4, pl = (ic / sh.C4) & 1, m = ic / (2 * sh.C4);
         stage[k] = *(const uint4 *)((pl ? sign : mask) + (int64_t)m * rw + 4 * c);
+    }
+
+    constexpr int NX = FP16 ? (G * NCH + 15) / 16 : 1;  // groups of 8 elements per thread: 16 per chunk of 128
+    uint4 x[NX];
+    uint32_t s_bits = 0;
+    if constexpr (FP16) {
+        s_bits = *(sa.mode ? sa.ptr : safe);
+#pragma unroll
+        for (int k = 0; k < NX; ++k) x[k] = request_group(act, 8 * ((int)threadIdx.x + 256 * k), K);
     }
 
     // weight rows of this wavefront: UNR passes; rows past N are clamped to the last row and never
@@ -137,7 +153,20 @@ __global__ __launch_bounds__(256) void k_gemv_popc(GemvBatch b, GemvShape sh)
         const int idx = threadIdx.x + 256 * k;
         if (idx < act_pieces) s_act[idx] = stage[k];
     }
-    if (!EARLY) {
+    if constexpr (FP16) {
+        const TernaryThr thr = ternary_thresholds(sa.mode ? s_bits : 0x3c00u, true);
+        uint8_t *planes = (uint8_t *)s_act;  // [plane][chunk] of 16 bytes, a byte per group of 8
+#pragma unroll
+        for (int k = 0; k < NX; ++k) {
+            const int grp = threadIdx.x + 256 * k;
+            uint32_t nz, neg;
+            ternary_flags<false>(finish_group(x[k], 8 * grp, K), thr, nz, neg);
+            if (grp < 16 * sh.C4) {
+                planes[grp] = (uint8_t)nz;
+                planes[16 * sh.C4 + grp] = (uint8_t)neg;
+            }
+        }
+    } else if (!EARLY) {
         for (int idx = threadIdx.x; idx < act_pieces; idx += 256) {
             const int c = idx % sh.C4, pl = (idx / sh.C4) & 1, m = idx / (2 * sh.C4);
             s_act[idx] = *(const uint4 *)((pl ? sign : mask) + (int64_t)m * rw + 4 * c);
@@ -183,6 +212,31 @@ __global__ __launch_bounds__(256) void k_gemv_popc(GemvBatch b, GemvShape sh)
             if (out) out[(int64_t)cl * sh.ldo + n] = scaled_to_half(a, my_sa * my_sw);
         }
     }
+}
+
+template <int MT, int G, int NCH, int UNR, bool NT>
+__global__ __launch_bounds__(256) void k_gemv_popc(GemvBatch b, GemvShape sh)
+{
+    gemv_popc<MT, G, NCH, UNR, NT, false>(b, sh, nullptr, 0);
+}
+
+// one problem, passed by value like a batch of one would be but without the other 63 slots' argument bytes
+struct LinearOne {
+    const uint16_t *A, *s_a, *s_w;
+    const uint32_t *wsign;
+    uint16_t *out;
+};
+
+template <int G, int NCH, int UNR, bool NT>
+__global__ __launch_bounds__(256) void k_linear_one(LinearOne l, GemvShape sh, int K)
+{
+    GemvBatch b;
+    b.mask[0] = b.sign[0] = nullptr;
+    b.wsign[0] = l.wsign;
+    b.s_a[0] = l.s_a, b.s_w[0] = l.s_w;
+    b.acc[0] = nullptr;
+    b.out[0] = l.out;
+    gemv_popc<1, G, NCH, UNR, NT, true>(b, sh, l.A, K);
 }
 
 template <int MT, int G, int NCH>
@@ -303,6 +357,51 @@ hipError_t launch_gemv_popc_grouped(const GemmArgs *gs, int count, hipStream_t s
 }
 
 hipError_t launch_gemv_popc(const GemmArgs &g, hipStream_t st) { return launch_gemv_popc_grouped(&g, 1, st); }
+
+// The whole linear of one token in one launch.  Rows of at least 8 elements (one 128-bit request); up to
+// 768 the two kernels stay, whose launch count callers are told (bwta_linear_launches).
+bool linear_one_supported(const GemmArgs &g)
+{
+    return g.M == 1 && g.K > 768 && gemv_popc_supported(g) && g.out != nullptr && g.acc == nullptr;
+}
+
+hipError_t launch_linear_one(const void *A, const GemmArgs &g, hipStream_t st)
+{
+    const LinearOne l{(const uint16_t *)A, g.s_a.mode ? g.s_a.ptr : nullptr, g.s_w.mode ? g.s_w.ptr : nullptr, g.wsign,
+                      g.out};
+    const GemvShape sh{1, g.N, g.rw, g.rw / 4, g.s_a.mode, g.s_w.mode, g.ldo};
+    const bool nt = (sh.rw & 31) == 0;
+    const size_t lds = (size_t)2 * sh.C4 * 16;
+    auto go = [&](auto lanes, auto chunks, auto unr) {
+        constexpr int G = decltype(lanes)::value, NCH = decltype(chunks)::value, UNR = decltype(unr)::value;
+        const int64_t rows = (int64_t)(64 / G) * UNR * 4;  // per workgroup
+        const dim3 grid((unsigned)((g.N + rows - 1) / rows));
+        if (nt) hipLaunchKernelGGL((k_linear_one<G, NCH, UNR, true>), grid, dim3(256), lds, st, l, sh, g.K);
+        else hipLaunchKernelGGL((k_linear_one<G, NCH, UNR, false>), grid, dim3(256), lds, st, l, sh, g.K);
+        return hipGetLastError();
+    };
+    // Two passes per wavefront halve the workgroups that ternarise the row; where one pass comes to a
+    // workgroup per compute unit at most, one.  Kernel time with 1 / 2 / 4 passes, us: N x K 11008 x 4096
+    // 4.5 / 3.9 / 3.9, 11008 x 11008 7.1 / 5.6 / 5.7, 4096 x 11008 4.6 / 4.1 / 4.7, 768 x 1024 2.7 / 2.9 / 3.2.
+    auto pick = [&](auto lanes, auto chunks) {
+        if ((int64_t)g.N * decltype(lanes)::value <= 256 * 4 * 64) return go(lanes, chunks, std::integral_constant<int, 1>{});
+        return go(lanes, chunks, std::integral_constant<int, 2>{});
+    };
+    constexpr std::integral_constant<int, 8> g8{};
+    constexpr std::integral_constant<int, 16> g16{};
+    constexpr std::integral_constant<int, 32> g32{};
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr std::integral_constant<int, 2> c2{};
+    constexpr std::integral_constant<int, 3> c3{};
+    constexpr std::integral_constant<int, 4> c4{};
+    const int C4 = sh.C4;
+    if (C4 <= 8) return pick(g8, c1);
+    if (C4 <= 16) return pick(g16, c1);
+    if (C4 <= 32) return pick(g32, c1);
+    if (C4 <= 64) return pick(g32, c2);
+    if (C4 <= 96) return pick(g32, c3);
+    return pick(g32, c4);
+}
 
 void set_gemv_tile(int g, int nch)
 {

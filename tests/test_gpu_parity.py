@@ -439,6 +439,41 @@ def test_linear_one_launch_every_kernel_instance(N, K):
     assert same_half(out, want)
 
 
+def _scratch(M, N, K):
+    return torch.empty(max(B.workspace_bytes(M, N, K), 256), dtype=torch.uint8, device="cuda:0")
+
+
+@pytest.mark.parametrize("K", [769, 1024, 1025, 2048, 2999, 4096, 8193, 11008, 12289, 16384])
+@pytest.mark.parametrize("N", [1, 9, 1031, 2050])
+def test_linear_one_token_one_launch(N, K):
+    """One token in one launch: both sides of every row split (lanes per row, chunks per lane), rows that
+    end inside a word and inside a group of 8, one and two passes per wavefront, the three scale modes, an
+    invalid scale, and results that overwrite the activations."""
+    rng = np.random.default_rng(N + K)
+    _say("one-launch linear, one token", N, K)
+    assert B.linear_launches(1, N, K) == 1
+    A, s = _activation_case(40 + N + K, 1, K)
+    w = synth.binary_pm1(38, N + K, (N, K))
+    s_w = synth.scales(38, 9, N)
+    wsign = gpu_pack_weights(w)
+    for s_a, sw in ((s, s_w), (np.float16([0.0]), s_w), (s, s_w[:1]), (None, None)):
+        _, _, want = oracle.linear(A, s_a, w, sw)
+        out = torch.full((1, N), float("nan"), dtype=torch.float16, device="cuda:0")
+        off = int(rng.integers(0, 8))  # rows of any address
+        buf = torch.zeros(K + 8, dtype=torch.float16, device="cuda:0")
+        a = buf[off:off + K]
+        a.copy_(dev(A)[0])
+        B.bwta_linear(a, None if s_a is None else dev(s_a), wsign, None if sw is None else dev(sw), out,
+                      _scratch(1, N, K), M=1, N=N, K=K)
+        torch.cuda.synchronize()
+        assert same_half(out.cpu().numpy(), want)
+        if N <= K:  # in place
+            B.bwta_linear(a, None if s_a is None else dev(s_a), wsign, None if sw is None else dev(sw), a,
+                          _scratch(1, N, K), M=1, N=N, K=K)
+            torch.cuda.synchronize()
+            assert same_half(a[:N].cpu().numpy()[None], want)
+
+
 def test_linear_one_launch_seeded_random_shapes():
     """40 seeded random shapes (M 256..1500, N 128..2500, K 8..1024 in steps of 8) through the
     dispatcher's own choice of launch form, split count and kernel instance."""
