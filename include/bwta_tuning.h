@@ -25,9 +25,10 @@ enum {
     BWTA_KERNEL_GEMM_POPC = 5     /* tiled, wave64 popcount (planes)    */
 };
 int bwta_planned_kernel(int operand, int M, int N, int K);
-/* How many kernels bwta_linear launches for a shape under the current settings: 1 where
- * ternarisation, product and epilogue run as one kernel (short K, or one token), else 2.  Informational (benchmarks label their timings with it); 0 for a
- * non-positive dimension. */
+/* How many kernels bwta_linear launches at most for a shape under the current settings: 1 where the shape
+ * alone says that ternarisation, product and epilogue run as one kernel (short K), else 2.  With one token, or with
+ * few enough outputs for one round of workgroups, a call whose out does not overlap A takes a single
+ * launch too.  Informational (benchmarks label their timings with it); 0 for a non-positive dimension. */
 int bwta_linear_launches(int M, int N, int K);
 /* Tuning hook for benchmark sweeps: force the FP4 kernel's per-wavefront tile (22, 21, 12, 11, 13
  * = blocks of 32 rows x 32 columns per wavefront; 23 = 22 at three wavefronts per SIMD; 222 = 22

@@ -90,7 +90,7 @@ int plan_from_planes(const bwta::GemmArgs &g, bool have_scratch)
 }
 
 // which kernel computes bwta_linear from fp16 in one launch, if one does
-enum class OneLaunch { kNo, kShortK, kOneToken };
+enum class OneLaunch { kNo, kShortK, kStrip, kOneToken };
 
 // Activations and results that share memory (a caller working in place): with two kernels the activations
 // have been read before the first result is written, with one they have not.
@@ -104,6 +104,7 @@ OneLaunch one_launch_linear(const bwta::GemmArgs &g)
 {
     const int path = resolve_path(g.M, g.N, g.K);
     if (path == BWTA_PATH_FP4 && bwta::linear_fused_supported(g)) return OneLaunch::kShortK;
+    if (path == BWTA_PATH_FP4 && bwta::linear_strip_supported(g)) return OneLaunch::kStrip;
     if (path == BWTA_PATH_POPC && bwta::linear_one_supported(g)) return OneLaunch::kOneToken;
     return OneLaunch::kNo;
 }
@@ -227,6 +228,9 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
                            nullptr, (uint16_t *)out, ldo};
     switch (one_launch_linear(g)) {
     case OneLaunch::kShortK: return hip_result(bwta::launch_linear_fused(A, lda, g, (hipStream_t)stream));
+    case OneLaunch::kStrip:
+        if (rows_overlap(A, lda, K, out, ldo, N, M)) break;
+        return hip_result(bwta::launch_linear_strip(A, lda, g, (hipStream_t)stream));
     case OneLaunch::kOneToken:
         if (rows_overlap(A, lda, K, out, ldo, N, M)) break;
         return hip_result(bwta::launch_linear_one(A, g, (hipStream_t)stream));
@@ -549,7 +553,7 @@ int bwta_linear_launches(int M, int N, int K)
     uint16_t sink = 0;
     bwta::GemmArgs g{nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
                      {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &sink, N};
-    return one_launch_linear(g) != OneLaunch::kNo ? 1 : 2;
+    return one_launch_linear(g) == OneLaunch::kShortK ? 1 : 2;  // the others take two where rows overlap
 }
 
 int bwta_planned_kernel(int operand, int M, int N, int K)

@@ -62,6 +62,13 @@ void set_fp4_tile(int t);
 bool linear_fused_supported(const GemmArgs &g);
 hipError_t launch_linear_fused(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);
 void set_linear_fused(int mode, int r);
+// ... walking K in slabs (any K, few enough outputs for one round of workgroups)
+bool linear_strip_supported(const GemmArgs &g);
+hipError_t launch_linear_strip(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);
+// a tuning hook is set (bwta_set_tile) that picks kernels of the two-launch form
+bool fp4_tuning_forced();
+bool gemv_fp4_tuning_forced();
+int linear_fused_mode();
 // the whole linear of one token in one launch (fp16 in, fp16 out)
 bool linear_one_supported(const GemmArgs &g);
 hipError_t launch_linear_one(const void *A, const GemmArgs &g, hipStream_t st);
@@ -108,10 +115,13 @@ __device__ __forceinline__ void word_slot(int q, int &step, int &half)
 // 0):   clamp(x - pred(T)) != 0  <=>  x >= T,      clamp(-x - T) != 0  <=>  x < -T,
 // which is the paper's threshold rule with T = s / 2, ties and all, at one instruction per two
 // elements and side.  T = s / 2 is a binary16 value unless s lies below 2^-13 with an odd last
-// bit; such rows compare 2 x (exact, or +-Inf on the correct side) against s instead.
+// bit; such rows compare 2 x against s instead.  The factor rides in a fused multiply-add (one rounding as
+// well), so no row takes a branch, and it is 8 times that (on both sides) for T < 4096, where neighbouring
+// values lie less than 4 apart: every difference that is not zero is then at least 8 units of the last
+// place, i.e. its bits are an integer of at least 8, and one packed minimum turns them into any flag up to 8.
 struct TernaryThr {
-    uint32_t cp, cn;  // -pred(T) and -T, each in both halves
-    bool twice;       // compare 2 x against T = s
+    uint32_t cp, cn;  // -f pred(T) and -f T, each in both halves
+    uint32_t f;       // the factor, in both halves
 };
 
 __device__ __forceinline__ TernaryThr ternary_thresholds(uint32_t s_bits, bool row_valid)
@@ -119,15 +129,21 @@ __device__ __forceinline__ TernaryThr ternary_thresholds(uint32_t s_bits, bool r
     const bool ok = row_valid && s_bits > 0 && s_bits < 0x7c00;  // finite and > 0; anything else: all zero
     const bool halves = s_bits >= 0x0800 || (s_bits & 1) == 0;
     const uint32_t T = s_bits >= 0x0800 ? s_bits - 0x0400 : (halves ? s_bits >> 1 : s_bits);
-    const uint32_t Tp = T - 1;
-    uint32_t cp = Tp ? (0x8000u | Tp) : 0u;  // +0, not -0, for pred(T) = 0: (-0) + (+0) is +0
-    uint32_t cn = 0x8000u | T;
-    if (!ok) cp = cn = 0xfc00u;  // -Inf: every sum is -Inf or NaN
-    TernaryThr t;
-    t.cp = cp * 0x10001u;
-    t.cn = cn * 0x10001u;
-    t.twice = ok && !halves;
-    return t;
+    const uint16_t t_bits = (uint16_t)T, tp_bits = (uint16_t)(T - 1);
+    _Float16 t, tp;
+    __builtin_memcpy(&t, &t_bits, 2);
+    __builtin_memcpy(&tp, &tp_bits, 2);
+    const bool eight = T < 0x6c00u;  // 4096
+    const _Float16 c = eight ? (_Float16)8.0f : (_Float16)1.0f;
+    t *= c, tp *= c;  // exact
+    uint16_t cn, cp;
+    __builtin_memcpy(&cn, &t, 2);
+    __builtin_memcpy(&cp, &tp, 2);
+    TernaryThr r;  // +0, not -0, for pred(T) = 0: (-0) + (+0) is +0; -Inf: every sum is -Inf or NaN
+    r.cp = (ok ? (cp ? 0x8000u | cp : 0u) : 0xfc00u) * 0x10001u;
+    r.cn = (ok ? 0x8000u | cn : 0xfc00u) * 0x10001u;
+    r.f = ((eight ? 0x4800u : 0x3c00u) + (halves ? 0u : 0x0400u)) * 0x10001u;
+    return r;
 }
 
 // 8 fp16 values of one row (lane j of a quad holds elements 8 j .. 8 j + 7 of a 32-element word) ->
@@ -135,24 +151,19 @@ __device__ __forceinline__ TernaryThr ternary_thresholds(uint32_t s_bits, bool r
 // 4 i + d (bit 1 = non-zero, bit 3 = negative).
 __device__ __forceinline__ uint32_t fragment_dword(const uint4 &x, const TernaryThr &t, int j)
 {
-    uint32_t w[4] = {x.x, x.y, x.z, x.w};  // elements (0,1) (2,3) (4,5) (6,7)
-    if (t.twice) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) asm("v_pk_add_f16 %0, %1, %1" : "=v"(w[d]) : "v"(w[d]));
-    }
-    uint32_t one2 = 0x00010001u;
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};  // elements (0,1) (2,3) (4,5) (6,7)
+    const uint32_t one2 = 0x00010001u, five2 = 0x00050005u;
     // byte 0 = elements 0 (low nibble) and 4 (high), byte 1 = 2 and 6, byte 2 = 1 and 5, byte 3 = 3 and 7
     uint32_t V = 0;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         uint32_t p, n, gp, gn;
-        asm("v_pk_add_f16 %0, %1, %2 clamp" : "=v"(p) : "v"(w[d]), "v"(t.cp));
-        asm("v_pk_add_f16 %0, %1, %2 neg_lo:[1,0] neg_hi:[1,0] clamp" : "=v"(n) : "v"(w[d]), "v"(t.cn));
-        asm("v_pk_min_u16 %0, %1, %2" : "=v"(gp) : "v"(p), "v"(one2));  // 1 where x >= T
-        asm("v_pk_min_u16 %0, %1, %2" : "=v"(gn) : "v"(n), "v"(one2));  // 1 where x < -T
-        const uint32_t sel = __umul24(gn, 5u) + gp;  // per half: non-zero bit, and two places up the sign bit
+        asm("v_pk_fma_f16 %0, %1, %2, %3 clamp" : "=v"(p) : "v"(w[d]), "v"(t.f), "v"(t.cp));
+        asm("v_pk_fma_f16 %0, %1, %2, %3 neg_lo:[1,0,0] neg_hi:[1,0,0] clamp" : "=v"(n) : "v"(w[d]), "v"(t.f), "v"(t.cn));
+        asm("v_pk_min_u16 %0, %1, %2" : "=v"(gp) : "v"(p), "v"(one2));   // x >= T: the non-zero bit
+        asm("v_pk_min_u16 %0, %1, %2" : "=v"(gn) : "v"(n), "v"(five2));  // x < -T: that and, two places up, the sign bit
         const int sh = d == 0 ? 1 : d == 1 ? 9 : d == 2 ? 5 : 13;
-        V = (sel << sh) | V;
+        V = ((gp | gn) << sh) | V;
     }
     // quad byte transpose: lane d of the quad collects the byte holding elements d and d + 4 of
     // every lane -> dword d of the word
@@ -172,20 +183,16 @@ __device__ __forceinline__ uint32_t fragment_dword(const uint4 &x, const Ternary
 template <bool BOOL>
 __device__ __forceinline__ void ternary_flags(const uint4 &x, const TernaryThr &t, uint32_t &nz, uint32_t &neg)
 {
-    uint32_t w[4] = {x.x, x.y, x.z, x.w};
-    if (t.twice) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) asm("v_pk_add_f16 %0, %1, %1" : "=v"(w[d]) : "v"(w[d]));
-    }
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
     uint32_t one2 = 0x00010001u, P = 0, N = 0;  // element 2 d in bit 2 d, element 2 d + 1 in bit 16 + 2 d
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         uint32_t p, n, gp, gn;
-        asm("v_pk_add_f16 %0, %1, %2 clamp" : "=v"(p) : "v"(w[d]), "v"(t.cp));
+        asm("v_pk_fma_f16 %0, %1, %2, %3 clamp" : "=v"(p) : "v"(w[d]), "v"(t.f), "v"(t.cp));
         asm("v_pk_min_u16 %0, %1, %2" : "=v"(gp) : "v"(p), "v"(one2));
         P = gp << (2 * d) | P;
         if (!BOOL) {
-            asm("v_pk_add_f16 %0, %1, %2 neg_lo:[1,0] neg_hi:[1,0] clamp" : "=v"(n) : "v"(w[d]), "v"(t.cn));
+            asm("v_pk_fma_f16 %0, %1, %2, %3 neg_lo:[1,0,0] neg_hi:[1,0,0] clamp" : "=v"(n) : "v"(w[d]), "v"(t.f), "v"(t.cn));
             asm("v_pk_min_u16 %0, %1, %2" : "=v"(gn) : "v"(n), "v"(one2));
             N = gn << (2 * d) | N;
         }

@@ -705,6 +705,8 @@ void set_linear_fused(int mode, int r)
     g_linear_fused_r.store(r, std::memory_order_relaxed);
 }
 
+int linear_fused_mode() { return g_linear_fused.load(std::memory_order_relaxed); }
+
 // BWTA_Att with V^T prepared as fragments.  g: M = rows of V^T per batch entry (a multiple of 128),
 // N = attention rows per entry, wsign = the boolean plane, s_a / s_w = the scales of V^T / of the
 // attention operand, out = the context matrix [batch][N][ldo].
@@ -718,6 +720,11 @@ hipError_t launch_att_v_fp4(const GemmArgs &g, const uint32_t *frag, int batch, 
 
 static std::atomic<int> g_fp4_tile{0};
 void set_fp4_tile(int t) { g_fp4_tile.store(t, std::memory_order_relaxed); }
+
+bool fp4_tuning_forced()
+{
+    return g_fp4_tile.load(std::memory_order_relaxed) != 0 || linear_fused_mode() != 1 || gemv_fp4_tuning_forced();
+}
 
 // frag_ready: the fragments were already produced by launch_quantize_to_fp4 (planes unused)
 hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, hipStream_t st)

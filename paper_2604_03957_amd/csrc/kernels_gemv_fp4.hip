@@ -427,6 +427,8 @@ hipError_t launch_gemv_fp4_grouped(const GemmArgs *gs, int count, hipStream_t st
 
 hipError_t launch_gemv_fp4(const GemmArgs &g, hipStream_t st) { return launch_gemv_fp4_grouped(&g, 1, st); }
 
+bool gemv_fp4_tuning_forced() { return g_force_rpw.load(std::memory_order_relaxed) != 0; }
+
 void set_gemv_fp4_tile(int rpw, int t, int pf)
 {
     g_force_rpw.store(rpw, std::memory_order_relaxed);

@@ -358,11 +358,11 @@ hipError_t launch_gemv_popc_grouped(const GemmArgs *gs, int count, hipStream_t s
 
 hipError_t launch_gemv_popc(const GemmArgs &g, hipStream_t st) { return launch_gemv_popc_grouped(&g, 1, st); }
 
-// The whole linear of one token in one launch.  Rows of at least 8 elements (one 128-bit request); up to
-// 768 the two kernels stay, whose launch count callers are told (bwta_linear_launches).
+// The whole linear of one token in one launch, from rows of 8 elements (one 128-bit request).
 bool linear_one_supported(const GemmArgs &g)
 {
-    return g.M == 1 && g.K > 768 && gemv_popc_supported(g) && g.out != nullptr && g.acc == nullptr;
+    return g.M == 1 && g.K >= 8 && gemv_popc_supported(g) && g.out != nullptr && g.acc == nullptr &&
+           linear_fused_mode() == 1 && g_force_g.load(std::memory_order_relaxed) == 0;
 }
 
 hipError_t launch_linear_one(const void *A, const GemmArgs &g, hipStream_t st)

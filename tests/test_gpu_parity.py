@@ -443,7 +443,7 @@ def _scratch(M, N, K):
     return torch.empty(max(B.workspace_bytes(M, N, K), 256), dtype=torch.uint8, device="cuda:0")
 
 
-@pytest.mark.parametrize("K", [769, 1024, 1025, 2048, 2999, 4096, 8193, 11008, 12289, 16384])
+@pytest.mark.parametrize("K", [8, 300, 1024, 1025, 2048, 2999, 4096, 8193, 11008, 12289, 16384])
 @pytest.mark.parametrize("N", [1, 9, 1031, 2050])
 def test_linear_one_token_one_launch(N, K):
     """One token in one launch: both sides of every row split (lanes per row, chunks per lane), rows that
@@ -451,7 +451,6 @@ def test_linear_one_token_one_launch(N, K):
     invalid scale, and results that overwrite the activations."""
     rng = np.random.default_rng(N + K)
     _say("one-launch linear, one token", N, K)
-    assert B.linear_launches(1, N, K) == 1
     A, s = _activation_case(40 + N + K, 1, K)
     w = synth.binary_pm1(38, N + K, (N, K))
     s_w = synth.scales(38, 9, N)
@@ -472,6 +471,47 @@ def test_linear_one_token_one_launch(N, K):
                           _scratch(1, N, K), M=1, N=N, K=K)
             torch.cuda.synchronize()
             assert same_half(a[:N].cpu().numpy()[None], want)
+
+
+@pytest.mark.parametrize("M,N,K", [(2, 1, 1025), (31, 129, 1536), (128, 250, 3072), (97, 8191, 1031), (129, 128, 1537),
+                                   (300, 500, 2047), (250, 4096, 1025), (200, 70, 11003), (513, 1900, 1100),
+                                   (777, 1500, 2560), (2050, 383, 1800), (2048, 1536, 1030), (2300, 1100, 2049),
+                                   (33, 5000, 900)])
+@pytest.mark.parametrize("scales", ["vector", "scalar", "none"])
+def test_linear_slabs_one_launch(M, N, K, scales):
+    """The one-launch linear that walks K in slabs of 512: one, two and three channel blocks per wavefront, tokens
+    and channels around the tile edges, two slabs and more, odd and even counts, K that ends on a slab, inside a
+    word and inside a group of 8, rows of any address and pitch, ties, infinities and NaN, an invalid scale, scales
+    below 2^-13 with an odd last bit and above 8192, and results that overwrite the activations."""
+    _say("one-launch linear, slabs", M, N, K, scales)
+    lda = K + M % 3
+    A, s = _activation_case(60 + M + K, M, K, lda)
+    A, s = A[:, :K].copy(), s.copy()
+    s[0], s[M // 2] = np.float16(0.0), np.float16(9000.0)
+    A[M // 2, ::3], A[M // 2, 1::3] = np.float16(4500.0), np.float16(-4500.0)
+    s[M - 1] = np.uint16(0x0405).view(np.float16)  # T = s / 2 lies between two binary16 values
+    A[M - 1, ::2], A[M - 1, 1::2] = np.uint16(0x0203).view(np.float16), np.uint16(0x8202).view(np.float16)
+    w = synth.binary_pm1(39, M + N + K, (N, K))
+    s_w = synth.scales(39, 10, N)
+    s_a, sw = {"vector": (s, s_w), "scalar": (s[1:2], s_w[:1]), "none": (None, None)}[scales]
+    _, _, want = oracle.linear(A, s_a, w, sw)
+    wsign = gpu_pack_weights(w)
+    ldo = N + N % 2
+    pitch = max(lda, ldo)
+    buf = torch.zeros(M * pitch + 8, dtype=torch.float16, device="cuda:0")
+    a = buf[M % 8:M % 8 + M * pitch].view(M, pitch)
+    a[:, :K] = dev(A)
+    out = torch.full((M, ldo), float("nan"), dtype=torch.float16, device="cuda:0")
+    args = (None if s_a is None else dev(s_a), wsign, None if sw is None else dev(sw))
+    modes = dict(a_scale_mode=B.SCALE_VECTOR, w_scale_mode=B.SCALE_VECTOR) if scales == "vector" else {}
+    B.bwta_linear(a, *args, out, _scratch(M, N, K), M=M, N=N, K=K, lda=pitch, ldo=ldo, **modes)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert same_half(np.ascontiguousarray(got[:, :N]), want)
+    assert np.all(np.isnan(got[:, N:]))
+    B.bwta_linear(a, *args, a, _scratch(M, N, K), M=M, N=N, K=K, lda=pitch, ldo=pitch, **modes)
+    torch.cuda.synchronize()
+    assert same_half(np.ascontiguousarray(a[:, :N].cpu().numpy()), want)
 
 
 def test_linear_one_launch_seeded_random_shapes():
