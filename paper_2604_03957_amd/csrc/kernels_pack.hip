@@ -424,14 +424,15 @@ __global__ __launch_bounds__(NT) void k_act_scale(const uint16_t *__restrict__ A
 // finite elements equals K (S - 2 Sn) - S (n - 2 nn) with Sn, nn the sum and count of the finite elements
 // below the mean and n the count of finite elements, so the second pass needs only exact per-thread
 // sums again; the final combination is done in double (one division, one rounding to binary16).
-// Bound: HBM.  The row stays in registers between the passes.  Both sums use the double form of a
-// binary16 value (MagnitudeSum above, here with its sign), the compare is one packed subtraction whose
+// Bound: HBM.  The row stays in registers between the passes.  Both sums are exact: in fp32 by groups of 8 where
+// the values are small enough (SmallSum below: weights, as a rule), else on the double form of a binary16
+// value (MagnitudeSum above, here with its sign).  The compare is one packed subtraction whose
 // sign survives rounding (ternary_thresholds) and one packed minimum per two elements, and a masked
-// element adds zero: about 11 instructions per element in all.  Wavefronts that hold a NaN or an Inf go
-// through their elements one by one instead.  A row of up to 4096 elements takes one wavefront and no barrier.
-// Measured on fp16 [4096, 11008], with two conversions and three selects per element and pass and a
-// padded 2048 groups per row before: 48.7 -> 24.0 us (4.0 TB/s), the vector ALU still ahead of HBM; one or
-// two wavefronts per row there are 4 to 15 % slower (registers), at K = 4096 one is 20 % ahead of four.
+// element adds zero: about 5 instructions per element in all, 9 with the double form.  Wavefronts that hold a
+// NaN or an Inf go through their elements one by one instead.  A row of up to 4096 elements takes one wavefront and
+// no barrier.  Measured on fp16 [4096, 11008]: two conversions and three selects per element and pass 48.7 us, the
+// double form 24.0, fp32 by groups 21.1 us (4.5 TB/s); with the double form one or two wavefronts per row were
+// 4 to 15 % slower there (registers), at K = 4096 one is 20 % ahead of four.
 struct SignedSum {
     double even = 0.0, odd = 0.0;
 
@@ -443,6 +444,27 @@ struct SignedSum {
         odd += __hiloint2double((int)two >> 6 & (int)0x81fffc00u, 0);
     }
     __device__ __forceinline__ long long units() const { return (long long)ldexp(even + odd, 1008 + 24); }
+};
+
+// The same sum where every group of 8 has squares that add to less than 1/8, at one instruction per element
+// instead of three.  By Cauchy-Schwarz any partial sum of a group then lies below sqrt(8 / 8) = 1, so it is less
+// than 2^24 units of 2^-24 and exact in fp32; the groups' sums are added as integers.  (Weights of a standard
+// deviation up to 0.08 or so pass; any others take the double form.)
+struct SmallSum {
+    int units = 0;  // at most 24 groups: below 2^29
+
+    __device__ __forceinline__ void add(const uint32_t (&w)[4])
+    {
+        float s = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            asm("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel_hi:[1,0,0]" : "+v"(s) : "v"(w[i]));
+            asm("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(s) : "v"(w[i]));
+        }
+        units += (int)(s * 16777216.0f);
+    }
+    // squares: the bits of a sum of squares, which Inf and NaN fail; 0.12 leaves room for its rounding
+    static __device__ __forceinline__ bool exact_below(uint32_t squares) { return squares < __float_as_uint(0.12f); }
 };
 
 // the wavefront's sums; lane 0 of every wavefront leaves them in LDS when a row has several
@@ -480,20 +502,27 @@ __global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restri
     uint4 x[NG];
     load_row<NG>(row, threadIdx.x, NT, K, x);
 
-    SignedSum sum;
-    float squares = 0.0f;
+    uint32_t squares = 0;  // the largest sum of a group's squares, as its bits
+    SmallSum small_sum;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
         const uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
+        small_sum.add(w);
+        float sq = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            sum.add(w[i]);
-            squares = add_squares(w[i], squares);
-        }
+        for (int i = 0; i < 4; ++i) sq = add_squares(w[i], sq);
+        squares = max(squares, __float_as_uint(sq));
     }
-    long long S = sum.units();
+    const bool small = __all(SmallSum::exact_below(squares));
+    long long S = small_sum.units;
+    if (!small) {
+        SignedSum sum;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) sum.add(x[g].x), sum.add(x[g].y), sum.add(x[g].z), sum.add(x[g].w);
+        S = sum.units();
+    }
     int NF = 0;  // non-finite elements
-    const bool finite = __all(is_finite_sum(squares));
+    const bool finite = __all(squares < 0x7f800000u);
     if (!finite) {  // one by one, from memory again
         double part = 0.0;
 #pragma unroll 1
@@ -536,11 +565,11 @@ __global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restri
         const uint32_t word = quad_word(bits, lane);  // whole quads stay together: rw is a multiple of 4
         if (c < 4 * rw && (lane & 3) == 0) dst[c >> 2] = word;
     };
-    if (finite) {
-        SignedSum low;
+    // the signs of the registers' groups; low(w) gets each group's elements below the bound, the others zero
+    auto signs = [&](auto low) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            const uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
+            uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
             uint32_t V = 0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -549,12 +578,21 @@ __global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restri
                 asm("v_pk_min_u16 %0, %1, %2" : "=v"(flag) : "v"(d), "v"(one2));  // 1 where x < bound
                 asm("v_pk_sub_i16 %0, 0, %1" : "=v"(keep) : "v"(flag));           // 0xffff there
                 V = flag << (2 * i) | V;
-                low.add(w[i] & keep);
+                w[i] &= keep;
             }
+            low(w);
             int c = (int)threadIdx.x + NT * g;
             asm volatile("" : "+v"(c));  // its conditions are evaluated here, not carried through the kernel
             finish(c, (V & 0x55u) | (V >> 15 & 0xaau));
         }
+    };
+    if (small) {
+        SmallSum low;
+        signs([&](const uint32_t (&w)[4]) { low.add(w); });
+        SN = low.units;
+    } else if (finite) {
+        SignedSum low;
+        signs([&](const uint32_t (&w)[4]) { low.add(w[0]), low.add(w[1]), low.add(w[2]), low.add(w[3]); });
         SN = low.units();
     } else {
         double low = 0.0;

@@ -65,6 +65,28 @@ def test_prepare_weights_at_the_edges_of_its_row_splits(K):
     assert same_half(sw, s)
 
 
+@pytest.mark.parametrize("K", [8, 509, 4096, 4100, 11008, 12288])
+def test_prepare_weights_around_the_limit_of_the_fp32_sums(K):
+    """Rows whose groups of 8 have squares adding to just below and just above the 0.12 up to which their sums
+    are taken in fp32, all of one sign (the largest partial sums) and with subnormals among them; one such
+    group in a row of small ones; one large or non-finite value in a row of small ones."""
+    _say("prepare weights, fp32 limit", K)
+    N = 8
+    W = (synth.gaussian(700 + K, 1, N * K) * 0.02).astype(np.float16).reshape(N, K)
+    W[0], W[1], W[2] = np.float16(0.1224), np.float16(-0.1226), np.float16(0.16)
+    W[0, ::7] = np.float16(6e-8)
+    W[1, ::5] = np.float16(-3e-6)
+    W[3, K - 8:] = np.float16(0.35)
+    W[4, K // 2] = np.float16(40.0)
+    W[5, K // 3] = np.nan
+    W[6] = (synth.gaussian(701 + K, 1, K) * 1e-6).astype(np.float16)
+    W[7] += np.float16(0.1)
+    w, s = oracle.prepare_weights(W)
+    planes, sw = gpu_prepare(W, K)
+    assert np.array_equal(planes, oracle.pack_weights(w))
+    assert same_half(sw, s)
+
+
 def test_prepare_weights_special_rows():
     K = 300
     W = (synth.laplace(60, 1, 6 * K) * 0.02).astype(np.float16).reshape(6, K)
