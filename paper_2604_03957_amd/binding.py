@@ -6,6 +6,7 @@ Importing this module without the compiled library raises -- there is no fallbac
 """
 import ctypes
 import os
+import struct
 
 # torch ships its own HIP runtime; load it first so that libbwta.so binds to the same runtime
 # (same SONAME) instead of bringing a second one into the process.
@@ -54,6 +55,11 @@ _lib.bwta_gemm.argtypes = [_P, _P, _P, _c.c_int, _c.c_int, _c.c_int, _P, _c.c_in
 _lib.bwta_linear.restype = _c.c_int
 _lib.bwta_linear.argtypes = [_P, _c.c_int64, _P, _c.c_int, _P, _P, _c.c_int, _c.c_int, _c.c_int,
                              _c.c_int, _P, _c.c_int64, _P, _c.c_size_t, _P]
+# the same call with its arguments packed into one block: 15 ctypes conversions cost more than packing them
+_linear_call = _lib.bwta_linear_call
+_linear_call.restype = _c.c_int
+_linear_call.argtypes = [_c.c_char_p]
+_linear_pack = struct.Struct("=QqQQQQqQQQiiiiii").pack
 _lib.bwta_linear_static.restype = _c.c_int
 _lib.bwta_linear_static.argtypes = [_P, _c.c_int64, _P, _c.c_int, _P, _P, _c.c_int, _c.c_int, _c.c_int,
                                     _c.c_int, _P, _c.c_int64, _P]
@@ -218,7 +224,7 @@ def bwta_gemm(mask, sign, wsign, s_a, s_w, acc, out, workspace, *, M, N, K, ldo=
               a_scale_mode=None, w_scale_mode=None, workspace_bytes=None, stream=None):
     ldo = N if ldo is None else ldo
     if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.numel() * workspace.element_size()
+        workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.nbytes
     _check(_lib.bwta_gemm(_ptr(mask), _ptr(sign), _ptr(wsign), M, N, K, _ptr(s_a), _mode(s_a, a_scale_mode),
                           _ptr(s_w), _mode(s_w, w_scale_mode), _ptr(acc), _ptr(out), ldo,
                           _ptr(workspace), workspace_bytes, _stream(stream)))
@@ -229,10 +235,12 @@ def bwta_linear(A, s_a, wsign, s_w, out, workspace, *, M, N, K, lda=None, ldo=No
     lda = K if lda is None else lda
     ldo = N if ldo is None else ldo
     if workspace_bytes is None:
-        workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.numel() * workspace.element_size()
-    _check(_lib.bwta_linear(_ptr(A), lda, _ptr(s_a), _mode(s_a, a_scale_mode), _ptr(wsign), _ptr(s_w),
-                            _mode(s_w, w_scale_mode), M, N, K, _ptr(out), ldo, _ptr(workspace),
-                            workspace_bytes, _stream(stream)))
+        workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.nbytes
+    code = _linear_call(_linear_pack(_ptr(A) or 0, lda, _ptr(s_a) or 0, _ptr(wsign) or 0, _ptr(s_w) or 0,
+                                     _ptr(out) or 0, ldo, _ptr(workspace) or 0, workspace_bytes, _stream(stream),
+                                     _mode(s_a, a_scale_mode), _mode(s_w, w_scale_mode), M, N, K, 0))
+    if code != OK:
+        _check(code)
 
 
 def static_scratch_bytes():
@@ -282,7 +290,7 @@ def bwta_act_scale(A, s, *, M, K, lda=None, stream=None):
 def _nbytes(buf, given):
     if given is not None:
         return given
-    return 0 if buf is None or isinstance(buf, int) else buf.numel() * buf.element_size()
+    return 0 if buf is None or isinstance(buf, int) else buf.nbytes
 
 
 def prepared_bytes(M, K):

@@ -3,6 +3,7 @@
 #include "../../include/bwta.h"
 #include "../../include/bwta_tuning.h"
 
+#include <string.h>
 #include <atomic>
 #include <mutex>
 
@@ -241,6 +242,32 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
     if (rc != BWTA_OK) return rc;
     return bwta_gemm_prepared(workspace, workspace_bytes, format, wsign, M, N, K, s_a, a_scale_mode, s_w,
                               w_scale_mode, nullptr, out, ldo, stream);
+}
+
+// bwta_linear with its arguments in one block of memory, for callers whose foreign-function calls cost by the
+// argument (the Python binding: 15 conversions took longer than everything else on the host side of a small
+// layer).  Not part of the headers: the block's layout belongs to this library's own binding.
+struct LinearCall {
+    const void *A;
+    int64_t lda;
+    const void *s_a;
+    const uint32_t *wsign;
+    const void *s_w;
+    void *out;
+    int64_t ldo;
+    void *workspace;
+    uint64_t workspace_bytes;
+    bwta_stream_t stream;
+    int32_t a_scale_mode, w_scale_mode, M, N, K, reserved;
+};
+static_assert(sizeof(LinearCall) == 10 * 8 + 6 * 4, "the binding packs ten 64-bit and six 32-bit fields");
+
+int bwta_linear_call(const void *call)
+{
+    LinearCall c;
+    memcpy(&c, call, sizeof c);
+    return bwta_linear(c.A, c.lda, c.s_a, c.a_scale_mode, c.wsign, c.s_w, c.w_scale_mode, c.M, c.N, c.K, c.out, c.ldo,
+                       c.workspace, (size_t)c.workspace_bytes, c.stream);
 }
 
 int bwta_prepared_format(int M, int K)
