@@ -758,6 +758,15 @@ hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, h
     if (forced == 0 && g.acc == nullptr && g.K >= 1024 && gemm_fp4_lds_supported(g)) {
         const int64_t tm = (g.M + 127) / 128;
         const int64_t tiles256 = tm * ((g.N + 255) / 256), tiles128 = tm * ((g.N + 127) / 128);
+        // Tiles of 64 x 128 at three wavefronts per SIMD where 128 x 128 ones fill one round badly and K is short
+        // enough that their second fetch of the weights is not what counts: just above 256 (a second round of
+        // a few: bwta_linear 300 x 11008 x 2048 12.3 -> 10.3 us, 1600 x 2500 x 3072 18.2 -> 15.9), or 129 to 223 of which
+        // 128 x 96 ones make no single round (1200 x 2500 x 2048 13.1 -> 11.5) or K <= 1536 (600 x 4096 x 1100
+        // 10.2 -> 8.8, 160 x 11008 x 1536 9.6 -> 8.4).  Level or behind outside: 600 x 8192 x 2048 (320) 12.8 / 13.1,
+        // 400 x 4096 x 1536 (128) 7.8 / 8.6, 900 x 2500 x 3072 (160) 13.2 / 13.7.
+        const bool spills = tiles128 > 256 && tiles128 <= 288;
+        const bool between = tiles128 > 128 && tiles128 < 224 && (g.K <= 1536 || tm * ((g.N + 95) / 96) > 256);
+        if ((spills || between) && g.K <= 3072 && tiles256 < 160) return launch<1, 2, 2, 2, 3, false>(g, frag, s_pad, st);
         if (tiles256 >= (g.K >= 2048 ? 160 : 224)) return launch_gemm_fp4_lds(g, frag, 243, st);
         if (tiles128 >= 224) return launch_gemm_fp4_lds(g, frag, 223, st);
     }
