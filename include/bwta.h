@@ -127,7 +127,8 @@ int bwta_gemm(const uint32_t *mask, const uint32_t *sign, const uint32_t *wsign,
  * (at most 1024), for one token and for few outputs, as one kernel that never
  * touches the workspace;
  * the result is the same bit for bit (see bwta_linear_launches).  The workspace is required
- * either way.
+ * either way.  out may overlap A (rows that hold their own layer's results): such a call runs as
+ * two kernels, the first of which has read all of A.
  */
 int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode,
                 const uint32_t *wsign, const void *s_w, int w_scale_mode, int M, int N, int K,

@@ -94,11 +94,17 @@ int plan_from_planes(const bwta::GemmArgs &g, bool have_scratch)
 enum class OneLaunch { kNo, kShortK, kStrip, kOneToken };
 
 // Activations and results that share memory (a caller working in place): with two kernels the activations
-// have been read before the first result is written, with one they have not.
+// have been read before the first result is written, with one they have not.  Rows of one pitch that lie side by
+// side (a buffer [activations | results]) share a range of addresses but no element, which the offset modulo the
+// pitch tells; different pitches over one range count as sharing.
 bool rows_overlap(const void *A, int64_t lda, int K, const void *out, int64_t ldo, int N, int M)
 {
     const uintptr_t a = (uintptr_t)A, o = (uintptr_t)out;
-    return a < o + 2 * (uintptr_t)((M - 1) * ldo + N) && o < a + 2 * (uintptr_t)((M - 1) * lda + K);
+    if (a >= o + 2 * (uintptr_t)((M - 1) * ldo + N) || o >= a + 2 * (uintptr_t)((M - 1) * lda + K)) return false;
+    if (lda != ldo) return true;
+    int64_t col = ((int64_t)o - (int64_t)a) / 2 % lda;  // column of the activations' rows at which a row of results starts
+    if (col < 0) col += lda;
+    return col < K || col + N > lda;
 }
 
 OneLaunch one_launch_linear(const bwta::GemmArgs &g)
@@ -227,15 +233,11 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
                            {(const uint16_t *)s_a, s_a ? a_scale_mode : BWTA_SCALE_NONE},
                            {(const uint16_t *)s_w, s_w ? w_scale_mode : BWTA_SCALE_NONE},
                            nullptr, (uint16_t *)out, ldo};
-    switch (one_launch_linear(g)) {
+    switch (rows_overlap(A, lda, K, out, ldo, N, M) ? OneLaunch::kNo : one_launch_linear(g)) {
     case OneLaunch::kShortK: return hip_result(bwta::launch_linear_fused(A, lda, g, (hipStream_t)stream));
-    case OneLaunch::kStrip:
-        if (rows_overlap(A, lda, K, out, ldo, N, M)) break;
-        return hip_result(bwta::launch_linear_strip(A, lda, g, (hipStream_t)stream));
-    case OneLaunch::kOneToken:
-        if (rows_overlap(A, lda, K, out, ldo, N, M)) break;
-        return hip_result(bwta::launch_linear_one(A, g, (hipStream_t)stream));
-    default: break;
+    case OneLaunch::kStrip: return hip_result(bwta::launch_linear_strip(A, lda, g, (hipStream_t)stream));
+    case OneLaunch::kOneToken: return hip_result(bwta::launch_linear_one(A, g, (hipStream_t)stream));
+    case OneLaunch::kNo: break;
     }
     int format = 0;
     rc = bwta_prepare_act(A, lda, s_a, a_scale_mode, M, K, workspace, workspace_bytes, &format, stream);

@@ -528,6 +528,36 @@ def test_linear_slabs_one_launch(M, N, K, scales):
     assert same_half(np.ascontiguousarray(a[:, :N].cpu().numpy()), want)
 
 
+@pytest.mark.parametrize("M,N,K,pitch,start", [
+    (300, 515, 515, 515, 0), (300, 768, 768, 768, 0),     # in place, ragged and aligned rows, several channel splits
+    (64, 500, 515, 515, 0), (2050, 1000, 1023, 1024, 0), (33, 130, 9, 131, 0),
+    (200, 400, 768, 768, 300),                            # results start inside the activations' rows ..
+    (200, 700, 700, 704, -704 * 3),                       # .. three rows above them
+    (500, 300, 515, 900, 520), (500, 256, 512, 768, 512),  # side by side in rows of one pitch: no element shared
+    (500, 300, 515, 815, -300)])
+def test_linear_results_share_memory_with_the_activations(M, N, K, pitch, start):
+    """Short K, where every workgroup of a strip of tokens reads the strip's whole rows: results written over the
+    activations, over part of them, and between their rows.  The elements are the oracle's on the original
+    activations, and what belongs to neither stays."""
+    _say("linear, results in the activations' rows", M, N, K, pitch, start)
+    A, s = _activation_case(970 + M + K, M, K)
+    w = synth.binary_pm1(40, M + N + K, (N, K))
+    s_w = synth.scales(40, 11, N)
+    _, _, want = oracle.linear(A, s, w, s_w)
+    front = max(0, -start)
+    front += front % 8
+    flat = np.full(front + M * pitch + pitch + max(0, start), 7.0, np.float16)
+    rows = np.arange(M)[:, None] * pitch
+    at_a, at_o = front + rows + np.arange(K), front + start + rows + np.arange(N)
+    flat[at_a] = A
+    buf = dev(flat)
+    B.bwta_linear(buf[front:], dev(s), gpu_pack_weights(w), dev(s_w), buf[front + start:], _scratch(M, N, K), M=M, N=N, K=K,
+                  lda=pitch, ldo=pitch, a_scale_mode=B.SCALE_VECTOR, w_scale_mode=B.SCALE_VECTOR)
+    torch.cuda.synchronize()
+    flat[at_o] = want
+    assert same_half(buf.cpu().numpy(), flat)
+
+
 def test_linear_one_launch_seeded_random_shapes():
     """40 seeded random shapes (M 256..1500, N 128..2500, K 8..1024 in steps of 8) through the
     dispatcher's own choice of launch form, split count and kernel instance."""
