@@ -113,13 +113,13 @@ __device__ __forceinline__ void gemv_popc(const GemvBatch &b, const GemvShape &s
     constexpr bool EARLY = NSTAGE <= 2 && !FP16;  // more rows than that are staged by a loop behind the weights
     constexpr int NST = EARLY ? NSTAGE : 0;
     const int act_pieces = sh.M * 2 * sh.C4;
-    uint4 stage[NST > 0 ? NST : 1];
+    v4u_t stage[NST > 0 ? NST : 1];  // a plain vector: as a struct its guarded copy to LDS went through scratch
 #pragma unroll
     for (int k = 0; k < NST; ++k) {
         const int idx = threadIdx.x + 256 * k;
         const int ic = idx < act_pieces ? idx : 0;
         const int c = ic % sh.C4, pl = (ic / sh.C4) & 1, m = ic / (2 * sh.C4);
-        stage[k] = *(const uint4 *)((pl ? sign : mask) + (int64_t)m * rw + 4 * c);
+        stage[k] = *(const v4u_t *)((pl ? sign : mask) + (int64_t)m * rw + 4 * c);
     }
 
     constexpr int NX = FP16 ? (G * NCH + 15) / 16 : 1;  // groups of 8 elements per thread: 16 per chunk of 128
@@ -151,7 +151,7 @@ __device__ __forceinline__ void gemv_popc(const GemvBatch &b, const GemvShape &s
 #pragma unroll
     for (int k = 0; k < NST; ++k) {
         const int idx = threadIdx.x + 256 * k;
-        if (idx < act_pieces) s_act[idx] = stage[k];
+        if (idx < act_pieces) *(v4u_t *)(s_act + idx) = stage[k];
     }
     if constexpr (FP16) {
         const TernaryThr thr = ternary_thresholds(sa.mode ? s_bits : 0x3c00u, true);
@@ -173,7 +173,6 @@ __device__ __forceinline__ void gemv_popc(const GemvBatch &b, const GemvShape &s
         }
     }
     __syncthreads();
-    const uint4 zero4 = make_uint4(0, 0, 0, 0);
     uint4 am[MT][NCH], as[MT][NCH];
     int my_nnz = 0;  // nnz of token cl (the token this lane writes)
 #pragma unroll
@@ -182,7 +181,11 @@ __device__ __forceinline__ void gemv_popc(const GemvBatch &b, const GemvShape &s
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             const bool live = (m < sh.M) && (cl + G * j < sh.C4);
-            am[m][j] = live ? s_act[(2 * m) * sh.C4 + (coff[j] >> 2)] : zero4;
+            // Read always, then masked: a choice between an LDS element and a zero in a variable became a choice
+            // between two addresses, the zero's in scratch, and its flat load waited for every weight in flight.
+            const uint4 v = s_act[(m < sh.M ? 2 * m : 0) * sh.C4 + (coff[j] >> 2)];
+            const uint32_t keep = live ? 0xffffffffu : 0u;
+            am[m][j] = make_uint4(v.x & keep, v.y & keep, v.z & keep, v.w & keep);
             as[m][j] = s_act[(m < sh.M ? 2 * m + 1 : 1) * sh.C4 + (coff[j] >> 2)];
             c = popc_acc(am[m][j].x, popc_acc(am[m][j].y, popc_acc(am[m][j].z, popc_acc(am[m][j].w, c))));
         }

@@ -1,0 +1,25 @@
+"""What the compiler reports of the built kernels' resources (no GPU needed)."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2604_03957_amd import build
+
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_the_popcount_decode_kernels_use_no_scratch():
+    """A decode kernel's wavefront keeps all its weight loads in flight; any access to scratch waits for them
+    (they complete in order), which cost a fifth of the bandwidth of one token at K > 8192."""
+    src = os.path.join(build.CSRC, "kernels_gemv_popc.hip")
+    cmd = [HIPCC] + build.HIPCC_FLAGS + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c", src,
+                                         "-o", os.devnull]
+    report = subprocess.run(cmd, stderr=subprocess.PIPE, text=True, check=True).stderr
+    names = re.findall(r"Function Name: (\S+)", report)
+    scratch = [int(b) for b in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", report)]
+    assert len(names) == len(scratch) > 100
+    assert any("k_gemv_popc" in n for n in names) and any("k_linear_one" in n for n in names)
+    assert [(n, b) for n, b in zip(names, scratch) if b] == []
