@@ -279,7 +279,7 @@ def run_c2(args, torch, B, synth):
     # host's launch rate, the bound); a loop over the 3-7 us ternarise kernel alone would time the
     # host (about 8 us per call through Python), so its figure is the two-kernel bwta_linear minus
     # the product.
-    kern, contraction_ms = [], []
+    kern, contraction_ms, names = [], [], []
     for L, c in zip(layers, cfgs):
         launches = B.linear_launches(L.M, L.N, L.K)
         tl = _event_ms(torch, lambda: L.linear(B), args.steps, args.warmup)
@@ -291,12 +291,15 @@ def run_c2(args, torch, B, synth):
         finally:
             B.set_tile(0)
         k["two_kernel_form_us"] = round(t2 * 1e3, 2)
+        name = {B.KERNEL_LINEAR_FUSED: "k_linear_fused", B.KERNEL_LINEAR_STRIP: "k_linear_strip"}.get(
+            B.planned_kernel(B.OPERAND_FP16, L.M, L.N, L.K), "k_gemm_fp4")
+        names.append(name)
         if launches == 1:
-            k["kernel"] = "k_linear_fused (ternarise + FP4 MFMA product + scale epilogue)"
+            k["kernel"] = name + (" (ternarise + FP4 MFMA product + scale epilogue); ternarize_us and gemm_us are the "
+                                  "two-kernel form's")
             contraction_ms.append(tl)
         else:
-            k["kernel"] = ("k_linear_strip (one launch) for few outputs, else k_quantize_to_fp4, then k_gemm_fp4; "
-                           "ternarize_us and gemm_us are the two-kernel form's")
+            k["kernel"] = "k_quantize_to_fp4, then k_gemm_fp4 (FP4 MFMA product + scale epilogue)"
             contraction_ms.append(tg)
         tq = max(t2 - tg, 1e-6)
         k.update({"ternarize_us": round(tq * 1e3, 2), "gemm_us": round(tg * 1e3, 2),
@@ -304,8 +307,7 @@ def run_c2(args, torch, B, synth):
                   "gemm_TOPS": round(L.ops / (tg * 1e-3) / 1e12, 2), "path": _kernel_path_name(B, L.M, L.N, L.K)})
         kern.append(k)
     # the kernels that hold the contraction: per layer, the one-launch linear or the product kernel;
-    # the dominant one is the longer of the two (the up layer's: it writes 25 MB of fp16)
-    names = ["k_linear_fused" if k["launches"] == 1 else "k_gemm_fp4" for k in kern]
+    # the dominant one is the longer of the two
     dom = max(range(len(layers)), key=lambda i: contraction_ms[i])
     L = layers[dom]
     achieved = L.ops / (contraction_ms[dom] * 1e-3) / 1e12
@@ -325,7 +327,6 @@ def run_c2(args, torch, B, synth):
                                                                 contraction_ms[dom] * 1e3),
                 "achieved": round(achieved, 2), "peak": PEAK_FP4_TOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_FP4_TOPS, 4), "frac_of_int8_peak": round(achieved / PEAK_INT8_TOPS, 4),
-                # this layer mostly stores: 25 MB of fp16 out of a 19 Gflop product
                 "algorithmic_bytes": alg_bytes,
                 "frac_of_hbm_peak": round(alg_bytes / (contraction_ms[dom] * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
                 # HBM/fabric bytes per launch of this kernel from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE

@@ -14,7 +14,10 @@ extern "C" {
 int bwta_auto_path(int M, int N, int K);
 /* Which contraction kernel a product of this shape is dispatched to under the current path setting
  * (a pure host function: nothing is launched).  operand = 0: canonical planes with a workspace
- * (bwta_gemm); BWTA_PREPARED_PLANES or BWTA_PREPARED_FP4: bwta_gemm_prepared with that format.
+ * (bwta_gemm); BWTA_PREPARED_PLANES or BWTA_PREPARED_FP4: bwta_gemm_prepared with that format;
+ * BWTA_OPERAND_FP16: bwta_linear on fp16 rows that its results do not overlap, one of the
+ * BWTA_KERNEL_LINEAR_* where ternarisation, product and epilogue are one launch, else the product
+ * kernel behind the ternarise launch.
  * Prepared planes never resolve to BWTA_KERNEL_GEMM_FP4: that kernel needs scratch for its
  * fragments and bwta_gemm_prepared has none.  0 for a non-positive dimension or an unknown operand. */
 enum {
@@ -22,13 +25,17 @@ enum {
     BWTA_KERNEL_GEMV_FP4 = 2,     /* decode, FP4 matrix cores           */
     BWTA_KERNEL_GEMM_FP4 = 3,     /* tiled, FP4 matrix cores            */
     BWTA_KERNEL_GEMM_MFMA_I8 = 4, /* tiled, int8 matrix cores (planes)  */
-    BWTA_KERNEL_GEMM_POPC = 5     /* tiled, wave64 popcount (planes)    */
+    BWTA_KERNEL_GEMM_POPC = 5,    /* tiled, wave64 popcount (planes)    */
+    BWTA_KERNEL_LINEAR_FUSED = 6, /* whole linear, all of a short K     */
+    BWTA_KERNEL_LINEAR_STRIP = 7, /* whole linear, K in slabs           */
+    BWTA_KERNEL_LINEAR_ONE = 8    /* whole linear, one token            */
 };
+enum { BWTA_OPERAND_FP16 = 3 };
 int bwta_planned_kernel(int operand, int M, int N, int K);
-/* How many kernels bwta_linear launches at most for a shape under the current settings: 1 where the shape
- * alone says that ternarisation, product and epilogue run as one kernel (short K), else 2.  With one token, or with
- * few enough outputs for one round of workgroups, a call whose out does not overlap A takes a single
- * launch too.  Informational (benchmarks label their timings with it); 0 for a non-positive dimension. */
+/* How many kernels bwta_linear launches for a shape under the current settings, given results that do
+ * not overlap the activations (a call that works in place always takes two): 1 where ternarisation,
+ * product and epilogue run as one kernel (bwta_planned_kernel says which), else 2.  Informational
+ * (benchmarks label their timings with it); 0 for a non-positive dimension. */
 int bwta_linear_launches(int M, int N, int K);
 /* Tuning hook for benchmark sweeps: force the FP4 kernel's per-wavefront tile (22, 21, 12, 11, 13
  * = blocks of 32 rows x 32 columns per wavefront; 23 = 22 at three wavefronts per SIMD; 222 = 22

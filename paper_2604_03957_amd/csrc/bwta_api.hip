@@ -576,18 +576,31 @@ int bwta_auto_path(int M, int N, int K)
     return M > 1 ? BWTA_PATH_FP4 : BWTA_PATH_POPC;
 }
 
-int bwta_linear_launches(int M, int N, int K)
+static OneLaunch planned_linear(int M, int N, int K)
 {
-    if (M <= 0 || N <= 0 || K <= 0) return 0;
     uint16_t sink = 0;
     bwta::GemmArgs g{nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
                      {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &sink, N};
-    return one_launch_linear(g) == OneLaunch::kShortK ? 1 : 2;  // the others take two where rows overlap
+    return one_launch_linear(g);
+}
+
+int bwta_linear_launches(int M, int N, int K)
+{
+    if (M <= 0 || N <= 0 || K <= 0) return 0;
+    return planned_linear(M, N, K) == OneLaunch::kNo ? 2 : 1;
 }
 
 int bwta_planned_kernel(int operand, int M, int N, int K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
+    if (operand == BWTA_OPERAND_FP16) {
+        switch (planned_linear(M, N, K)) {
+        case OneLaunch::kShortK: return BWTA_KERNEL_LINEAR_FUSED;
+        case OneLaunch::kStrip: return BWTA_KERNEL_LINEAR_STRIP;
+        case OneLaunch::kOneToken: return BWTA_KERNEL_LINEAR_ONE;
+        case OneLaunch::kNo: operand = bwta_prepared_format(M, K); break;
+        }
+    }
     if (operand == BWTA_PREPARED_FP4) return BWTA_KERNEL_GEMM_FP4;
     if (operand != 0 && operand != BWTA_PREPARED_PLANES) return 0;
     bwta::GemmArgs g{};

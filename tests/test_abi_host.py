@@ -46,17 +46,42 @@ def test_path_selection():
     assert e.value.code == B.ERR_UNSUPPORTED
     assert B.auto_path(1, 11008, 4096) == B.PATH_POPC and B.auto_path(16, 11008, 4096) == B.PATH_FP4
     assert B.auto_path(2048, 4096, 4096) in (B.PATH_MFMA, B.PATH_FP4)
-    # launches of bwta_linear: one kernel for short K on prefill shapes, two otherwise; the hook turns it off
-    assert B.linear_launches(4096, 3072, 768) == 1 and B.linear_launches(4096, 768, 3072) == 2
-    assert B.linear_launches(1, 768, 768) == 2 and B.linear_launches(16384, 11008, 1024) == 2
-    assert B.linear_launches(16, 768, 768) == 1
+    # launches of bwta_linear: one kernel for short K, for few outputs and for one token; two otherwise; the hook
+    # turns it off
+    assert B.linear_launches(4096, 3072, 768) == 1 and B.linear_launches(4096, 768, 3072) == 1
+    assert B.linear_launches(1, 768, 768) == 1 and B.linear_launches(16384, 11008, 1024) == 2
+    assert B.linear_launches(16, 768, 768) == 1 and B.linear_launches(2048, 11008, 4096) == 2
     assert B.linear_launches(0, 8, 8) == 0 and B.linear_launches(8, 8, -1) == 0
     B.set_tile(900)
     try:
-        assert B.linear_launches(4096, 3072, 768) == 2
+        for M, N, K in ((4096, 3072, 768), (4096, 768, 3072), (1, 768, 768)):
+            assert B.linear_launches(M, N, K) == 2
     finally:
         B.set_tile(0)
     assert B.linear_launches(4096, 3072, 768) == 1
+
+
+def test_planned_kernel_of_the_linear():
+    """Which kernel bwta_linear takes on fp16 rows: the three one-launch kernels each where its rule says, the product
+    kernel behind a ternarise launch elsewhere; the launch count follows."""
+    def plan(M, N, K):
+        k = B.planned_kernel(B.OPERAND_FP16, M, N, K)
+        one = k in (B.KERNEL_LINEAR_FUSED, B.KERNEL_LINEAR_STRIP, B.KERNEL_LINEAR_ONE)
+        assert B.linear_launches(M, N, K) == (1 if one else 2), (M, N, K)
+        return k
+
+    assert plan(4096, 3072, 768) == plan(2, 128, 8) == plan(300, 515, 515) == B.KERNEL_LINEAR_FUSED
+    assert plan(4096, 768, 3072) == plan(64, 1536, 2048) == plan(300, 100, 768) == B.KERNEL_LINEAR_STRIP
+    assert plan(1, 11008, 4096) == plan(1, 1, 8) == plan(1, 128, 16384) == B.KERNEL_LINEAR_ONE
+    assert plan(1, 128, 7) == B.KERNEL_GEMV_POPC and plan(16, 11008, 4096) == B.KERNEL_GEMV_FP4
+    assert plan(2048, 11008, 4096) == B.KERNEL_GEMM_FP4
+    assert B.planned_kernel(B.OPERAND_FP16, 0, 8, 8) == 0
+    try:
+        for path, want in ((B.PATH_POPC, B.KERNEL_GEMM_POPC), (B.PATH_MFMA, B.KERNEL_GEMM_MFMA_I8)):
+            B.set_path(path)
+            assert plan(4096, 768, 3072) == want
+    finally:
+        B.set_path(B.PATH_AUTO)
 
 
 def _code(fn, *a, **k):

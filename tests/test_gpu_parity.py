@@ -465,6 +465,7 @@ def test_linear_one_token_one_launch(N, K):
     invalid scale, and results that overwrite the activations."""
     rng = np.random.default_rng(N + K)
     _say("one-launch linear, one token", N, K)
+    assert B.planned_kernel(B.OPERAND_FP16, 1, N, K) == B.KERNEL_LINEAR_ONE
     A, s = _activation_case(40 + N + K, 1, K)
     w = synth.binary_pm1(38, N + K, (N, K))
     s_w = synth.scales(38, 9, N)
@@ -498,6 +499,7 @@ def test_linear_slabs_one_launch(M, N, K, scales):
     word and inside a group of 8, rows of any address and pitch, ties, infinities and NaN, an invalid scale, scales
     below 2^-13 with an odd last bit and above 8192, and results that overwrite the activations."""
     _say("one-launch linear, slabs", M, N, K, scales)
+    assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == B.KERNEL_LINEAR_STRIP
     lda = K + M % 3
     A, s = _activation_case(60 + M + K, M, K, lda)
     A, s = A[:, :K].copy(), s.copy()
@@ -540,6 +542,7 @@ def test_linear_results_share_memory_with_the_activations(M, N, K, pitch, start)
     activations, over part of them, and between their rows.  The elements are the oracle's on the original
     activations, and what belongs to neither stays."""
     _say("linear, results in the activations' rows", M, N, K, pitch, start)
+    assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == B.KERNEL_LINEAR_FUSED
     A, s = _activation_case(970 + M + K, M, K)
     w = synth.binary_pm1(40, M + N + K, (N, K))
     s_w = synth.scales(40, 11, N)
