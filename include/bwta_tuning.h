@@ -6,9 +6,31 @@
 #ifndef BWTA_TUNING_H
 #define BWTA_TUNING_H
 
+#include <stdint.h>
+
 #ifdef __cplusplus
 extern "C" {
 #endif
+
+/* bwta_linear with its arguments in one block of memory, for callers whose foreign-function calls cost by
+ * the argument (the Python binding: 15 conversions took longer than everything else on the host side of a
+ * small layer).  size = sizeof(bwta_linear_args): a block of another layout is refused with
+ * BWTA_ERR_UNSUPPORTED, NULL with BWTA_ERR_NULL; everything else is bwta_linear's.  The block may have any
+ * alignment and is not kept. */
+typedef struct bwta_linear_args {
+    const void *A;
+    int64_t lda;
+    const void *s_a;
+    const uint32_t *wsign;
+    const void *s_w;
+    void *out;
+    int64_t ldo;
+    void *workspace;
+    uint64_t workspace_bytes;
+    void *stream;
+    int32_t a_scale_mode, w_scale_mode, M, N, K, size;
+} bwta_linear_args;
+int bwta_linear_call(const void *args);
 
 /* Which family AUTO resolves to for a shape: BWTA_PATH_POPC, BWTA_PATH_MFMA or BWTA_PATH_FP4. */
 int bwta_auto_path(int M, int N, int K);

@@ -29,7 +29,8 @@ OPERAND_FP16 = 3
 EXPORTS = ["bwta_plane_row_words", "bwta_workspace_bytes", "bwta_quantize_pack_act",
            "bwta_pack_weights", "bwta_gemm", "bwta_linear", "bwta_linear_static", "bwta_static_scratch_bytes",
            "bwta_static_scratch_init", "bwta_strerror", "bwta_last_hip_error",
-           "bwta_build_id", "bwta_set_path", "bwta_get_path", "bwta_auto_path", "bwta_linear_launches", "bwta_version", "bwta_set_tile",
+           "bwta_build_id", "bwta_set_path", "bwta_get_path", "bwta_auto_path", "bwta_linear_launches", "bwta_linear_call", "bwta_version",
+           "bwta_set_tile",
            "bwta_prepared_bytes", "bwta_prepared_format", "bwta_planned_kernel", "bwta_prepare_act", "bwta_gemm_prepared", "bwta_gemm_grouped",
            "bwta_quantize_pack_bool", "bwta_matmul_tt", "bwta_prepare_weights", "bwta_act_scale",
            "bwta_prepare_act_autoscale", "bwta_matmul_bool_prepared"]
@@ -61,7 +62,8 @@ _lib.bwta_linear.argtypes = [_P, _c.c_int64, _P, _c.c_int, _P, _P, _c.c_int, _c.
 _linear_call = _lib.bwta_linear_call
 _linear_call.restype = _c.c_int
 _linear_call.argtypes = [_c.c_char_p]
-_linear_pack = struct.Struct("=QqQQQQqQQQiiiiii").pack
+_linear_args = struct.Struct("=QqQQQQqQQQiiiiii")  # bwta_linear_args of bwta_tuning.h
+_linear_pack, _LINEAR_ARGS_SIZE = _linear_args.pack, _linear_args.size
 _lib.bwta_linear_static.restype = _c.c_int
 _lib.bwta_linear_static.argtypes = [_P, _c.c_int64, _P, _c.c_int, _P, _P, _c.c_int, _c.c_int, _c.c_int,
                                     _c.c_int, _P, _c.c_int64, _P]
@@ -238,9 +240,14 @@ def bwta_linear(A, s_a, wsign, s_w, out, workspace, *, M, N, K, lda=None, ldo=No
     ldo = N if ldo is None else ldo
     if workspace_bytes is None:
         workspace_bytes = 0 if workspace is None or isinstance(workspace, int) else workspace.nbytes
-    code = _linear_call(_linear_pack(_ptr(A) or 0, lda, _ptr(s_a) or 0, _ptr(wsign) or 0, _ptr(s_w) or 0,
-                                     _ptr(out) or 0, ldo, _ptr(workspace) or 0, workspace_bytes, _stream(stream),
-                                     _mode(s_a, a_scale_mode), _mode(s_w, w_scale_mode), M, N, K, 0))
+    try:
+        code = _linear_call(_linear_pack(_ptr(A) or 0, lda, _ptr(s_a) or 0, _ptr(wsign) or 0, _ptr(s_w) or 0,
+                                         _ptr(out) or 0, ldo, _ptr(workspace) or 0, workspace_bytes, _stream(stream),
+                                         _mode(s_a, a_scale_mode), _mode(s_w, w_scale_mode), M, N, K, _LINEAR_ARGS_SIZE))
+    except struct.error:  # no integer, or one outside its field: what the other calls' conversions make of it
+        code = _lib.bwta_linear(_ptr(A), lda, _ptr(s_a), _mode(s_a, a_scale_mode), _ptr(wsign), _ptr(s_w),
+                                _mode(s_w, w_scale_mode), M, N, K, _ptr(out), ldo, _ptr(workspace), workspace_bytes,
+                                _stream(stream))
     if code != OK:
         _check(code)
 

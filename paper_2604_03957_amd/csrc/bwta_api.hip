@@ -246,28 +246,12 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
                               w_scale_mode, nullptr, out, ldo, stream);
 }
 
-// bwta_linear with its arguments in one block of memory, for callers whose foreign-function calls cost by the
-// argument (the Python binding: 15 conversions took longer than everything else on the host side of a small
-// layer).  Not part of the headers: the block's layout belongs to this library's own binding.
-struct LinearCall {
-    const void *A;
-    int64_t lda;
-    const void *s_a;
-    const uint32_t *wsign;
-    const void *s_w;
-    void *out;
-    int64_t ldo;
-    void *workspace;
-    uint64_t workspace_bytes;
-    bwta_stream_t stream;
-    int32_t a_scale_mode, w_scale_mode, M, N, K, reserved;
-};
-static_assert(sizeof(LinearCall) == 10 * 8 + 6 * 4, "the binding packs ten 64-bit and six 32-bit fields");
-
 int bwta_linear_call(const void *call)
 {
-    LinearCall c;
-    memcpy(&c, call, sizeof c);
+    bwta_linear_args c;
+    if (!call) return BWTA_ERR_NULL;
+    memcpy(&c, call, sizeof c);  // any alignment
+    if (c.size != (int32_t)sizeof c) return BWTA_ERR_UNSUPPORTED;
     return bwta_linear(c.A, c.lda, c.s_a, c.a_scale_mode, c.wsign, c.s_w, c.w_scale_mode, c.M, c.N, c.K, c.out, c.ldo,
                        c.workspace, (size_t)c.workspace_bytes, c.stream);
 }

@@ -1,5 +1,6 @@
 """Host-side checks of the C ABI that need no GPU: the library loads, exports every function
 the header declares, and rejects bad arguments before anything could be enqueued."""
+import ctypes
 import os
 import re
 
@@ -132,6 +133,35 @@ def test_gemm_and_linear_reject_bad_arguments():
     assert _code(lin, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, **dict(kw, lda=100)) == B.ERR_SHAPE
     assert _code(lin, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, **dict(kw, workspace_bytes=0)) == B.ERR_WORKSPACE
     lin(FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, **dict(kw, M=0))
+
+
+def test_linear_converts_its_arguments_like_the_other_calls():
+    """bwta_linear's arguments travel in one packed block; integers outside a field's range wrap and what is no integer
+    is refused by ctypes, as in the calls that pass them one by one."""
+    lin = B.bwta_linear
+    kw = dict(M=8, N=8, K=128, stream=0, workspace_bytes=B.workspace_bytes(8, 8, 128), a_scale_mode=B.SCALE_VECTOR,
+              w_scale_mode=B.SCALE_VECTOR)
+    bad_ws = (FAKE, FAKE, FAKE, FAKE, FAKE, FAKE + 16)      # a workspace on no 256-byte boundary: the last check
+    assert _code(lin, *bad_ws, **kw) == B.ERR_ALIGN
+    assert _code(lin, *bad_ws, **dict(kw, workspace_bytes=-1)) == B.ERR_ALIGN        # the largest size_t
+    assert _code(lin, *bad_ws, **dict(kw, M=2 ** 32 + 8)) == B.ERR_ALIGN
+    assert _code(lin, *bad_ws, **dict(kw, M=2 ** 31)) == B.ERR_SHAPE                 # negative as an int
+    assert _code(lin, -256, *bad_ws[1:], **kw) == B.ERR_ALIGN
+    lin(*bad_ws, **dict(kw, M=2 ** 32))                                              # no rows: nothing to do
+    for bad in (dict(K=128.0), dict(K="128"), dict(M=None), dict(lda=128.5), dict(workspace_bytes="x")):
+        with pytest.raises(ctypes.ArgumentError):
+            lin(*bad_ws, **dict(kw, **bad))
+        if "lda" not in bad and "workspace_bytes" not in bad:
+            with pytest.raises(ctypes.ArgumentError):
+                B.bwta_linear_static(*bad_ws[:5], **{k: v for k, v in dict(kw, **bad).items() if k != "workspace_bytes"})
+
+
+def test_the_block_of_linear_arguments_states_its_size():
+    call = B.raw().bwta_linear_call
+    good = B._linear_pack(*[0] * 15, B._LINEAR_ARGS_SIZE)
+    assert len(good) == B._LINEAR_ARGS_SIZE == 104
+    assert call(good) == B.OK                                                        # M = N = 0
+    assert call(B._linear_pack(*[0] * 16)) == B.ERR_UNSUPPORTED and call(None) == B.ERR_NULL
 
 
 def test_prepare_and_gemm_prepared_reject_bad_arguments():
