@@ -494,9 +494,11 @@ hipError_t launch(const GemmArgs &g, const uint32_t *frag, int s_pad, hipStream_
 constexpr int FL_STRIP_HALFS = 32 * (32 * 2 + 8);  // room for the widest group
 
 // word j of a 256-k chunk feeds k step j % 4 of the chunk on lane half j / 4
-template <int NCH, int FL_CB, int NWV>  // 256-k chunks of K (1..4); channel blocks (of 32) per group: 1 or 2; wavefronts: 4 or 8
+// SPREAD: how the strips beyond the last whole round of 8 are dealt to the XCDs (below)
+template <int NCH, int FL_CB, int NWV, bool SPREAD>  // 256-k chunks of K (1..4); channel blocks (of 32) per group: 1 or 2; wavefronts: 4 or 8
 __global__ __launch_bounds__(64 * NWV) void k_linear_fused(const uint16_t *__restrict__ A, int64_t lda, GemmArgs g, int R,
-                                                      int cbw /* channel blocks per workgroup, a multiple of NWV FL_CB */)
+                                                      int cbw /* channel blocks per workgroup, a multiple of NWV FL_CB */,
+                                                      uint32_t recip /* 2^32 / R, rounded down */)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     constexpr int NSTEP = 4 * NCH;
@@ -506,11 +508,27 @@ __global__ __launch_bounds__(64 * NWV) void k_linear_fused(const uint16_t *__res
     float *s_sw = s_sa + 32;                               // [32 cbw] channel scales
     uint16_t *strips = (uint16_t *)(s_sw + 32 * cbw);      // [NWV wavefronts][FL_STRIP_HALFS]
 
-    // the R workgroups of a strip sit 8 ids apart: same XCD, so the strip's second reader hits its L2
+    // The R workgroups of a strip sit 8 ids apart: ids are dealt to the 8 XCDs in turn, so the strip's later readers
+    // hit one L2.  Strips beyond the last whole round of 8 either go on like that (in a grid padded to the round) or
+    // share their workgroups out over all XCDs: see launch_linear_fused.
     const int nstrips = (g.M + 31) >> 5;
-    const int id = blockIdx.x, kq = id >> 3;
-    const int split = kq % R, strip_id = (kq / R) * 8 + (id & 7);
-    if (strip_id >= nstrips) return;  // the grid is padded to rounds of 8 strips
+    const int id = blockIdx.x;
+    int split, strip_id;
+    if (!SPREAD) {
+        const int kq = id >> 3;
+        split = kq % R, strip_id = (kq / R) * 8 + (id & 7);
+        if (strip_id >= nstrips) return;
+    } else {
+        const int whole = nstrips & ~7, tail = id - whole * R, rest = (nstrips - whole) * R;
+        const int xcd = id & 7, in_round = tail >> 31;  // all ones or zero: masks, as a branch here delays the requests
+        const int spread = xcd * (rest >> 3) + (xcd < (rest & 7) ? xcd : rest & 7) + (tail >> 3);
+        const int in_turn = (in_round & (id >> 3)) | (~in_round & spread);
+        int q = (int)__umulhi((uint32_t)in_turn, recip);  // in_turn / R or one less
+        split = in_turn - q * R;
+        const int over = ~((split - R) >> 31);
+        q -= over, split -= over & R;
+        strip_id = (in_round & (8 * q + xcd)) | (~in_round & (whole + q));
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rw = g.rw;
     const int m0 = 32 * strip_id;
@@ -650,7 +668,10 @@ hipError_t launch_quantize_to_fp4(const void *A, int64_t lda, ScaleArg s_a, int 
 // faster with K than the two-kernel form's, while its fixed cost is 2 us lower.  Measured over
 // M = 512 .. 16384, N = 768 .. 11008, K = 256 .. 1024 it is ahead everywhere for K <= 768 (by 5 to
 // 40 %: 13.1 -> 10.4 us at 4096 x 3072 x 768, 17.8 -> 11.3 us at 16384 x 768 x 768) and for K = 1024
-// up to N = 4096 and M = 8192; beyond, the two kernels win.  Rows of any address and length from 8
+// up to N = 4096 and M = 8192; beyond, the two kernels win.  At 2 .. 128 tokens (the
+// decode kernel on the other side) it is ahead for K <= 768; 0 to 8 % behind at K = 900 where calls are
+// replayed from a graph and 20 to 30 % ahead where they are made one by one (64 x 1536: 5.9 against 5.8 us, 5.7
+// against 7.6).  Rows of any address and length from 8
 // elements (one 128-bit request) are taken: 500 x 1001 x 515 10.2 -> 6.2 us, 3000 x 1537 x 700 21.3 -> 9.1 us
 // against the two kernels and their 2-byte stores into rows of odd length.
 bool linear_fused_supported(const GemmArgs &g)
@@ -684,18 +705,25 @@ hipError_t launch_linear_fused(const void *A, int64_t lda, const GemmArgs &g, hi
     R = (ncb + cbw - 1) / cbw;
     const int nch = (g.rw + 7) / 8;
     const size_t smem = (size_t)nch * 4 * 1024 + (32 + 32 * cbw) * 4 + (size_t)NWV * FL_STRIP_HALFS * 2;
-    const dim3 grid((unsigned)((nstrips + 7) / 8 * 8 * R)), block(64 * NWV);
-#define BWTA_FL(N_, C_)                                                                                          \
-    if (nch == N_ && CB == C_ && NWV == 4) {                                                                     \
-        hipLaunchKernelGGL((k_linear_fused<N_, C_, 4>), grid, block, smem, st, (const uint16_t *)A, lda, g, R, cbw); \
-        return hipGetLastError();                                                                                \
-    }                                                                                                            \
-    if (nch == N_ && CB == C_ && NWV == 8) {                                                                     \
-        hipLaunchKernelGGL((k_linear_fused<N_, C_, 8>), grid, block, smem, st, (const uint16_t *)A, lda, g, R, cbw); \
+    // A strip of the last, partial round of 8 to an XCD each gives some XCDs more workgroups than their 32 compute
+    // units while others have none: up to 32 tokens ran on one XCD alone.  There the strips of that round share
+    // their workgroups out over all of them.  us: 2 x 28000 x 700 13.9 -> 5.5 (two kernels 6.7), 513 x 11008 x 515
+    // 11.7 -> 8.5 (10.2), 300 x 3072 x 515 7.6 -> 6.1 (9.3); with fewer workgroups the one L2 is worth more:
+    // 64 x 768 x 768 4.82 against 4.97 spread out.
+    const bool spread = nstrips % 8 != 0 && (nstrips + 7) / 8 * R > 32;
+    const uint32_t recip = R == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (unsigned)R);
+    const dim3 grid((unsigned)((spread ? nstrips : (nstrips + 7) / 8 * 8) * R)), block(64 * NWV);
+#define BWTA_FL_S(N_, C_, W_, S_)                                                                                \
+    if (nch == N_ && CB == C_ && NWV == W_ && spread == S_) {                                                    \
+        hipLaunchKernelGGL((k_linear_fused<N_, C_, W_, S_>), grid, block, smem, st, (const uint16_t *)A, lda, g, R, cbw, \
+                           recip);                                                                               \
         return hipGetLastError();                                                                                \
     }
+#define BWTA_FL(N_, C_) \
+    BWTA_FL_S(N_, C_, 4, false) BWTA_FL_S(N_, C_, 4, true) BWTA_FL_S(N_, C_, 8, false) BWTA_FL_S(N_, C_, 8, true)
     BWTA_FL(1, 1) BWTA_FL(1, 2) BWTA_FL(2, 1) BWTA_FL(2, 2) BWTA_FL(3, 1) BWTA_FL(3, 2) BWTA_FL(4, 1) BWTA_FL(4, 2)
 #undef BWTA_FL
+#undef BWTA_FL_S
     return hipErrorInvalidValue;
 }
 

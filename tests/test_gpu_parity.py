@@ -561,6 +561,25 @@ def test_linear_results_share_memory_with_the_activations(M, N, K, pitch, start)
     assert same_half(buf.cpu().numpy(), flat)
 
 
+@pytest.mark.parametrize("M,N", [(2, 4300), (70, 3001), (297, 4990), (513, 4090), (513, 10990), (1000, 9000)])
+@pytest.mark.parametrize("K", [200, 300, 515, 900])
+def test_linear_one_launch_strips_beyond_a_round_of_xcds(M, N, K):
+    """Token strips that do not come in whole rounds of 8 and with many workgroups each: their workgroups are dealt to
+    the XCDs one by one.  One strip alone, a few, and some behind whole rounds; four and eight wavefronts, one and two
+    channel blocks per group, one to four chunks of K; every (strip, split) must be done once."""
+    _say("one-launch linear, partial round of strips", M, N, K)
+    B.set_tile(901)  # K = 900 also beyond 4096 channels
+    try:
+        assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == B.KERNEL_LINEAR_FUSED
+        A, s = _activation_case(980 + M + K, M, K)
+        w = synth.binary_pm1(41, M + N + K, (N, K))
+        s_w = synth.scales(41, 12, N)
+        _, _, want = oracle.linear(A, s, w, s_w)
+        assert same_half(gpu_linear(A, s, gpu_pack_weights(w), s_w, N), want)
+    finally:
+        B.set_tile(0)
+
+
 def test_linear_one_launch_seeded_random_shapes():
     """40 seeded random shapes (M 256..1500, N 128..2500, K 8..1024 in steps of 8) through the
     dispatcher's own choice of launch form, split count and kernel instance."""
