@@ -16,11 +16,11 @@
 //     words of a thread pair then lie in different banks); weight row r is its 64 bytes with piece c at
 //     slot c ^ (r / 4 % 4), so that 16 neighbouring rows' 16-byte reads meet no bank twice.
 //   * What bounds it: the vector ALU and the matrix cores in turn (two wavefronts per SIMD do not overlap
-//     them fully): per slab 0.6 us of ternarising (31 instructions per 8 elements) and 0.2 NB of widening
-//     weight bits and products; 3.9 us stand outside the slabs.  bwta_linear 4096 x 768 x 3072 15.6 -> 12.1 us,
-//     2048 x 768 x 2048 10.7 -> 8.0, 256 x 4096 x 4096 11.4 -> 9.7, 64 x 768 x 3072 8.8 -> 7.8.  The loop copies
-//     no registers on purpose: with an exit between its two slabs the compiler moved a requested slab at
-//     the back edge, waiting for all loads, and 4096 x 768 x 3072 took 12.9 us.
+//     them fully): per slab 0.55 us of ternarising (31 instructions per 8 elements) and 0.25 NB of widening
+//     weight bits and products; 3.4 to 5.2 us stand outside the slabs.  bwta_linear replayed back to back,
+//     two kernels -> this one: 4096 x 768 x 3072 15.7 -> 12.8 us, 2048 x 768 x 2048 10.0 -> 8.1,
+//     256 x 4096 x 4096 11.5 -> 10.5.  The loop copies no registers on purpose: with an exit between its two
+//     slabs the compiler moved a requested slab at the back edge, waiting for all loads (6 % there).
 #include <atomic>
 #include <type_traits>
 
@@ -241,22 +241,31 @@ static int strip_blocks(const GemmArgs &g)
     return 0;
 }
 
-// Where one launch is ahead.  Its time is about 3.9 us + (0.6 + 0.2 NB) us per slab of 512, whatever M and N;
-// that of the two kernels grows with M K (ternarising, fragments out and in).  Measured on 170 shapes, M 8 .. 8192,
-// N 300 .. 11008, K 1100 .. 11008, two kernels against one, us:
-//   up to 128 tokens (the decode kernel is the other side) ahead up to K = 3072: 64 x 4096 x 2048 9.3 / 6.6,
-//   64 x 768 x 3072 8.8 / 7.8; level at 4096 (96 x 4096 x 4096 8.2 / 9.6) and behind beyond;
-//   NB = 1 from 129 tokens ahead everywhere: 256 x 4096 x 2048 8.0 / 6.7, 2048 x 300 x 4096 14.0 / 10.1;
-//   NB = 2 ahead from 777 tokens (777 x 1536 x 4096 13.3 / 11.6), mixed below (512 x 4096 x 4096 12.3 / 11.9,
-//   256 x 8192 x 4096 12.4 / 13.0);
-//   NB = 3 ahead from 2048 tokens (4096 x 768 x 3072 15.6 / 12.1, 2048 x 1536 x 2048 11.5 / 9.8), mixed below
-//   (777 x 3072 x 4096 15.3 / 14.2, 1024 x 3072 x 11008 28.3 / 32.0).
+// Where one launch is ahead.  Its time is about 3.4 / 4.0 / 5.2 us + 0.8 / 1.0 / 1.3 us per slab of 512 for NB = 1 / 2 /
+// 3, whatever M and N; that of the two kernels grows with M K (ternarising, fragments out and in).  Measured on 900
+// shapes, M 2 .. 8192, N 64 .. 28000, K 520 .. 30000, replayed from a graph, two kernels / one, us:
+//   Up to 128 tokens (the decode kernel is the other side) level up to K = 1536 (64 x 768 5.8 / 5.6); at K = 2048
+//   6 to 16 % behind with few outputs (64 x 768 5.9 / 6.5) but 10 to 20 % ahead where calls are made one by one (7.5 /
+//   6.2), ahead with many (128 x 8192 8.3 / 7.1); beyond, up to 40 % behind and no faster call by call (64 x 768 x 3072
+//   6.0 / 8.1, 7.9 / 7.8) except with many outputs: from a quarter of a million at K = 2560 (64 x 8192 x 2500 8.8 /
+//   7.6), from half a million at K = 3072 (33 x 16384 9.3 / 8.5, 128 x 8192 9.5 / 8.3).
+//   NB = 1 from 129 tokens ahead everywhere: 256 x 4096 x 2048 8.3 / 7.1, 256 x 4096 x 16384 31.8 / 30.0.
+//   NB = 2 ahead from 513 tokens (513 x 3072 x 2048 9.1 / 8.2, 777 x 1536 x 4096 13.8 / 11.9), mixed below (512 x 4096 x
+//   4096 12.3 / 11.9, 256 x 8192 x 4096 12.4 / 13.0); at K = 30000 only with narrow matrices (777 x 2500 63.9 / 71.6,
+//   2048 x 768 78.6 / 68.5), whose tiles suit the other side less.
+//   NB = 3 ahead from 2048 tokens (4096 x 768 x 3072 15.7 / 12.8, 2048 x 1536 x 2048 11.4 / 10.1), mixed below (777 x 3072 x
+//   4096 15.3 / 14.2, 1024 x 3072 x 11008 28.3 / 32.0); beyond K = 8192 only with narrow matrices (2048 x 1536 x 11008 31.5 /
+//   33.5, 4096 x 768 x 11008 39.1 / 33.2).
 bool linear_strip_supported(const GemmArgs &g)
 {
     if (g.K <= 512 || g.out == nullptr || g.acc != nullptr || fp4_tuning_forced()) return false;
     const int nb = strip_blocks(g);
-    if (g.M <= 128) return nb >= 1 && nb <= 2 && g.K <= 3072;
-    return nb == 1 || (nb == 2 && g.M > 512) || (nb == 3 && g.M >= 2048);
+    const int64_t outputs = (int64_t)g.M * g.N;
+    if (g.M <= 128)
+        return (nb == 1 || nb == 2) &&
+               (g.K <= 2048 || (g.K <= 2560 && outputs >= 256 * 1024) || (g.K <= 3072 && outputs > 512 * 1024));
+    const bool narrow = g.N <= 1152;
+    return nb == 1 || (nb == 2 && g.M > 512 && (g.K <= 16384 || narrow)) || (nb == 3 && g.M >= 2048 && (g.K <= 8192 || narrow));
 }
 
 hipError_t launch_linear_strip(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st)

@@ -73,6 +73,12 @@ def test_planned_kernel_of_the_linear():
 
     assert plan(4096, 3072, 768) == plan(2, 128, 8) == plan(300, 515, 515) == B.KERNEL_LINEAR_FUSED
     assert plan(4096, 768, 3072) == plan(64, 1536, 2048) == plan(300, 100, 768) == B.KERNEL_LINEAR_STRIP
+    # the slab kernel's bounds: K at decode-sized token counts, very long K on wide matrices
+    for (M, N), last in (((64, 768), 2048), ((2, 28000), 2048), ((64, 4096), 2560), ((64, 8193), 3072), ((128, 8192), 3072), ((777, 2500), 16384),
+                         ((777, 1152), 32768), ((2048, 1536), 8192), ((4096, 768), 32768), ((256, 4096), 32768)):
+        assert plan(M, N, last) == B.KERNEL_LINEAR_STRIP, (M, N, last)
+        assert last == 32768 or plan(M, N, last + 1) in (B.KERNEL_GEMV_FP4, B.KERNEL_GEMM_FP4), (M, N, last)
+    assert plan(512, 4096, 4096) == plan(1024, 3072, 4096) == B.KERNEL_GEMM_FP4
     assert plan(1, 11008, 4096) == plan(1, 1, 8) == plan(1, 128, 16384) == B.KERNEL_LINEAR_ONE
     assert plan(1, 128, 7) == B.KERNEL_GEMV_POPC and plan(16, 11008, 4096) == B.KERNEL_GEMV_FP4
     assert plan(2048, 11008, 4096) == B.KERNEL_GEMM_FP4
