@@ -71,6 +71,9 @@ int bwta_linear_launches(int M, int N, int K);
  * wherever the one-launch kernel can run, 900 + R the same with R channel splits per token
  * strip); 0 restores the built-in choices.  Results do not depend on it. */
 int bwta_set_tile(int tile);
+/* Which of those tiles the tiled FP4 kernel (BWTA_KERNEL_GEMM_FP4) takes for a shape and fp16 results under
+ * the current settings; 0 for a non-positive dimension. */
+int bwta_planned_tile(int M, int N, int K);
 #ifdef __cplusplus
 }
 #endif

@@ -58,6 +58,7 @@ hipError_t launch_gemm_mfma(const GemmArgs &g, hipStream_t st);
 
 size_t gemm_fp4_frag_bytes(int M, int K);
 void set_fp4_tile(int t);
+int fp4_planned_tile(int M, int N, int K);
 // the whole linear in one launch (short K, fp16 in, fp16 out)
 bool linear_fused_supported(const GemmArgs &g);
 hipError_t launch_linear_fused(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);

@@ -754,6 +754,74 @@ bool fp4_tuning_forced()
     return g_fp4_tile.load(std::memory_order_relaxed) != 0 || linear_fused_mode() != 1 || gemv_fp4_tuning_forced();
 }
 
+// The tile of a product on ready fragments, fp16 results (bwta_set_tile's numbers).
+static int fp4_tile_for(const GemmArgs &g)
+{
+    const int64_t tm = (g.M + 127) / 128;
+    const int64_t tiles128 = tm * ((g.N + 127) / 128), tiles96 = tm * ((g.N + 95) / 96);
+    // Large products: both operands through LDS by direct loads.  Measured against the register-fed
+    // kernel below on ready fragments (us, M x N x K): 128 x 256 tiles of 8 wavefronts win once there are
+    // about 160 of them and K is long enough to pay for filling the ring -- 2048 x 4096 x 4096 15.9 against
+    // 18.2, 2048 x 11008 x 4096 40.4 against 48.7, 2048 x 4096 x 11008 37.4 against 43.3, 512 x 11008 x 4096
+    // (172 tiles) 14.6 against 16.7, 8192 x 768 x 3072 (192) 12.1 against 13.8, 4096 x 4096 x 1024 12.6
+    // against 14.8; with fewer, 128 x 128 tiles of 4 wavefronts win where they come to about one per compute
+    // unit -- 1024 x 4096 x 4096 11.0 against 11.6, 512 x 8192 x 8192 17.7 against 19.0, 1024 x 4096 x 1024
+    // 6.2 against 6.7 -- and lose below that (512 x 4096 x 4096: 10.6 against 8.8).
+    if (g.K >= 1024 && gemm_fp4_lds_supported(g)) {
+        const int64_t tiles256 = tm * ((g.N + 255) / 256), tiles64 = ((int64_t)g.M + 63) / 64 * ((g.N + 127) / 128);
+        // Tiles of 64 x 128 at three wavefronts per SIMD where 128 x 128 ones fill one round badly and K is short
+        // enough that their second fetch of the weights is not what counts.  us on ready fragments, the other choice
+        // against this one:
+        //   A little more than one 128 x 128 tile per compute unit, while the 64 x 128 ones come to two at most (a last
+        //   row of tiles that is half empty): 300 x 11008 x 2048 9.7 / 8.4, 1600 x 2500 x 3072 12.8 / 11.3; with more
+        //   than two, 1024 x 4608 x 3072 12.1 / 13.0, except for K just beyond 1024, which the LDS-staged kernel walks as
+        //   1536 (3000 x 1536 x 1100 8.5 / 7.9).
+        //   129 to 223 tiles that 128 x 96 ones spread over one round: where 96 leaves a ragged edge (600 x 4096 x 1100
+        //   7.7 / 7.0, 900 x 2500 x 1536 8.1 / 7.8) or 64 x 128 ones make one round too (300 x 6144 x 1536 6.7 / 6.1), up to
+        //   K = 1536; not where 96 divides N (2048 x 1536 x 1536 6.6 / 7.2), nor beyond (900 x 3001 x 2048 8.7 / 9.0).
+        //   129 to 223 of which 128 x 96 ones make more than a round: up to K = 1536, and with a ragged edge at 128 to
+        //   3072 (1200 x 2500 x 2048 9.7 / 9.2); 384 x 8192 x 2048 8.0 / 8.3.
+        const bool spills = tiles128 > 256 && tiles128 <= 288 && (tiles64 <= 512 || (g.K > 1024 && g.K <= 1280));
+        const bool between = tiles128 > 128 && tiles128 < 224 &&
+                             (tiles96 <= 256 ? g.K <= 1536 && (g.N % 96 != 0 || tiles64 <= 256) : g.K <= 1536 || g.N % 128 != 0);
+        if ((spills || between) && g.K <= 3072 && tiles256 < 160) return 12;
+        if (tiles256 >= (g.K >= 2048 ? 160 : 224)) return 243;
+        if (tiles128 >= 224) return 223;
+    }
+    // A few hundred tokens against a narrow matrix: 128 x 128 tiles would leave half the compute units
+    // or more without a workgroup, 64 x 64 tiles quadruple the workgroups (measured at N = 4096,
+    // 192-512 tokens: 7.5-9.4 us against 11.4-12.0 us at K = 4096, 15.8-19.7 against 24-25 at K = 11008).
+    if (tiles128 <= 128 && g.K >= 1024) return 11;
+    // Between 129 and 255 tiles of 128 x 128 some compute units get no workgroup at all.  If tiles of
+    // 128 x 96 (four wavefronts of 32 x 96) number at most 256, every one of them still runs in the
+    // first round and more compute units take part (measured at M = 4096, N = 768, K = 3072: 192 -> 256
+    // workgroups, 9.7 -> 8.3 us).
+    if (tiles128 < 256 && tiles96 > tiles128 && tiles96 <= 256 && g.K >= 1024) return 13;
+    // measured: long K runs best with 2 wavefronts per SIMD (179 registers), short K with 3
+    return g.K >= 2048 ? 22 : 23;
+}
+
+// the forced tile (tuning sweeps) where the shape can take it, else the rule's
+static int fp4_tile(const GemmArgs &g)
+{
+    const int forced = g_fp4_tile.load(std::memory_order_relaxed);
+    switch (forced) {
+    case 11: case 12: case 13: case 21: case 22: case 23: case 222: return forced;
+    case 223: case 243: case 323:
+        if (gemm_fp4_lds_supported(g)) return forced;
+        break;
+    default: break;
+    }
+    return fp4_tile_for(g);
+}
+
+int fp4_planned_tile(int M, int N, int K)
+{
+    GemmArgs g{};
+    g.M = M, g.N = N, g.K = K, g.rw = (int)(4 * (((int64_t)K + 127) / 128));
+    return fp4_tile(g);
+}
+
 // frag_ready: the fragments were already produced by launch_quantize_to_fp4 (planes unused)
 hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, hipStream_t st)
 {
@@ -772,58 +840,20 @@ hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, h
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const int forced = g_fp4_tile.load(std::memory_order_relaxed);
-    if ((forced == 223 || forced == 243 || forced == 323) && gemm_fp4_lds_supported(g))
-        return launch_gemm_fp4_lds(g, frag, forced, st);
-    // Large products: both operands through LDS by direct loads.  Measured against the register-fed
-    // kernel below on ready fragments (us, M x N x K): 128 x 256 tiles of 8 wavefronts win once there are
-    // about 160 of them and K is long enough to pay for filling the ring -- 2048 x 4096 x 4096 15.9 against
-    // 18.2, 2048 x 11008 x 4096 40.4 against 48.7, 2048 x 4096 x 11008 37.4 against 43.3, 512 x 11008 x 4096
-    // (172 tiles) 14.6 against 16.7, 8192 x 768 x 3072 (192) 12.1 against 13.8, 4096 x 4096 x 1024 12.6
-    // against 14.8; with fewer, 128 x 128 tiles of 4 wavefronts win where they come to about one per compute
-    // unit -- 1024 x 4096 x 4096 11.0 against 11.6, 512 x 8192 x 8192 17.7 against 19.0, 1024 x 4096 x 1024
-    // 6.2 against 6.7 -- and lose below that (512 x 4096 x 4096: 10.6 against 8.8).
-    if (forced == 0 && g.acc == nullptr && g.K >= 1024 && gemm_fp4_lds_supported(g)) {
-        const int64_t tm = (g.M + 127) / 128;
-        const int64_t tiles256 = tm * ((g.N + 255) / 256), tiles128 = tm * ((g.N + 127) / 128);
-        // Tiles of 64 x 128 at three wavefronts per SIMD where 128 x 128 ones fill one round badly and K is short
-        // enough that their second fetch of the weights is not what counts: just above 256 (a second round of
-        // a few: bwta_linear 300 x 11008 x 2048 12.3 -> 10.3 us, 1600 x 2500 x 3072 18.2 -> 15.9), or 129 to 223 of which
-        // 128 x 96 ones make no single round (1200 x 2500 x 2048 13.1 -> 11.5) or K <= 1536 (600 x 4096 x 1100
-        // 10.2 -> 8.8, 160 x 11008 x 1536 9.6 -> 8.4).  Level or behind outside: 600 x 8192 x 2048 (320) 12.8 / 13.1,
-        // 400 x 4096 x 1536 (128) 7.8 / 8.6, 900 x 2500 x 3072 (160) 13.2 / 13.7.
-        const bool spills = tiles128 > 256 && tiles128 <= 288;
-        const bool between = tiles128 > 128 && tiles128 < 224 && (g.K <= 1536 || tm * ((g.N + 95) / 96) > 256);
-        if ((spills || between) && g.K <= 3072 && tiles256 < 160) return launch<1, 2, 2, 2, 3, false>(g, frag, s_pad, st);
-        if (tiles256 >= (g.K >= 2048 ? 160 : 224)) return launch_gemm_fp4_lds(g, frag, 243, st);
-        if (tiles128 >= 224) return launch_gemm_fp4_lds(g, frag, 223, st);
-    }
-    if (g.acc) return launch<2, 2, 2, 2, 2, true>(g, frag, s_pad, st);  // int32 output: test / debug path
-    switch (forced) {  // forced tile (tuning sweeps); 0 = heuristic below
-    case 22: return launch<2, 2, 2, 2, 2, false>(g, frag, s_pad, st);
+    const int tile = fp4_tile(g);
+    const bool lds = tile == 223 || tile == 243 || tile == 323;
+    // int32 output (test / debug path) takes the LDS-staged kernel only where it is forced
+    if (lds && (!g.acc || tile == g_fp4_tile.load(std::memory_order_relaxed))) return launch_gemm_fp4_lds(g, frag, tile, st);
+    if (g.acc) return launch<2, 2, 2, 2, 2, true>(g, frag, s_pad, st);
+    switch (tile) {
     case 23: return launch<2, 2, 2, 2, 3, false>(g, frag, s_pad, st);
     case 21: return launch<2, 1, 2, 2, 3, false>(g, frag, s_pad, st);
     case 12: return launch<1, 2, 2, 2, 3, false>(g, frag, s_pad, st);
     case 11: return launch<1, 1, 2, 2, 4, false>(g, frag, s_pad, st);
     case 13: return launch<1, 3, 4, 1, 2, false>(g, frag, s_pad, st);
     case 222: return launch<2, 2, 2, 2, 2, false, 2>(g, frag, s_pad, st);
-    default: break;
+    default: return launch<2, 2, 2, 2, 2, false>(g, frag, s_pad, st);  // 22
     }
-    // A few hundred tokens against a narrow matrix: 128 x 128 tiles would leave half the compute units
-    // or more without a workgroup, 64 x 64 tiles quadruple the workgroups (measured at N = 4096,
-    // 192-512 tokens: 7.5-9.4 us against 11.4-12.0 us at K = 4096, 15.8-19.7 against 24-25 at K = 11008).
-    const int64_t tiles128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-    if (tiles128 <= 128 && g.K >= 1024) return launch<1, 1, 2, 2, 4, false>(g, frag, s_pad, st);
-    // Between 129 and 255 tiles of 128 x 128 some compute units get no workgroup at all.  If tiles of
-    // 128 x 96 (four wavefronts of 32 x 96) number at most 256, every one of them still runs in the
-    // first round and more compute units take part (measured at M = 4096, N = 768, K = 3072: 192 -> 256
-    // workgroups, 9.7 -> 8.3 us).
-    const int64_t tiles96 = (int64_t)((g.M + 127) / 128) * ((g.N + 95) / 96);
-    if (tiles128 < 256 && tiles96 > tiles128 && tiles96 <= 256 && g.K >= 1024)
-        return launch<1, 3, 4, 1, 2, false>(g, frag, s_pad, st);
-    // measured: long K runs best with 2 wavefronts per SIMD (179 registers), short K with 3
-    if (g.K >= 2048) return launch<2, 2, 2, 2, 2, false>(g, frag, s_pad, st);
-    return launch<2, 2, 2, 2, 3, false>(g, frag, s_pad, st);
 }
 
 }  // namespace bwta

@@ -439,11 +439,13 @@ def test_linear_one_launch_every_kernel_instance(N, K):
     assert same_half(out, want)
 
 
-@pytest.mark.parametrize("M,N,K", [(1590, 2490, 1030), (330, 8200, 1024), (1190, 2500, 3071), (410, 5000, 1530), (300, 11007, 1100)])
+@pytest.mark.parametrize("M,N,K", [(1590, 2490, 1030), (330, 8200, 1024), (1190, 2500, 3071), (410, 5000, 1530), (300, 11007, 1100),
+                                   (1270, 3299, 1300), (2040, 1536, 1530)])
 def test_tiled_product_between_rounds_of_workgroups(M, N, K):
     """Products whose 128 x 128 tiles come to a little more than one per compute unit, or to few enough to leave
-    many without one: tiles of 64 x 128, ragged on all sides, fp16 output."""
+    many without one: tiles of 64 x 128, ragged on all sides, fp16 output; the last two just outside their windows."""
     _say("tiled product between rounds", M, N, K)
+    assert B.planned_tile(M, N, K) == {1270: 223, 2040: 13}.get(M, 12)
     t = synth.ternary(90, M + N, (M, K), 0.5)
     w = synth.binary_pm1(91, M + K, (N, K))
     s_a, s_w = synth.scales(92, 1, M), synth.scales(92, 2, N)
