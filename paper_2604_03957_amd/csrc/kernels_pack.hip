@@ -672,21 +672,24 @@ __global__ __launch_bounds__(NT) void k_act_scale_quantize(const uint16_t *__res
     }
 }
 
-// Scale and fragments in one pass for a prompt's worth of rows (K <= 16384).  Bound: HBM (2 bytes in,
-// half a byte out per element), with the vector ALU close behind (8.5 instructions per element).  A
-// workgroup of NW wavefronts takes 4 rows: a fragment holds 16 bytes per row with consecutive rows side
-// by side, so a workgroup per row wrote 16-byte pieces of lines that eight workgroups on eight XCDs
-// shared.  Sixteen lanes of a wavefront hold 128 consecutive elements of a row, all NG loads of a
-// thread are in flight before the first sum, and the row sums meet in LDS once.  2, 4 and 8 rows per
-// workgroup and 4 to 16 wavefronts are within 10 % of each other (2048 x 11008: 16.3, 16.1, 16.9 us).
-// Measured, back to back on fresh rows, a workgroup per row before: 2048 x 4096 8.7 -> 6.6 us,
-// 2048 x 11008 18.3 -> 16.1 us (3.5 TB/s), 4096 x 2048 11.0 -> 6.6 us.
-template <int NW, int NG>
+// Scale and fragments in one pass (K <= 16384).  Bound: HBM (2 bytes in, half a byte out per element), with the
+// vector ALU close behind (8.5 instructions per element).  A workgroup of NW wavefronts takes RB rows: a
+// fragment holds 16 bytes per row with consecutive rows side by side, so a workgroup per row writes 16-byte
+// pieces of lines that eight workgroups on eight XCDs share.  64 / RB lanes of a wavefront hold that many
+// groups of 8 consecutive elements of a row, all NG loads of a thread are in flight before the first sum, and the
+// row sums meet in LDS once.  Four rows (8 are within 10 %) where they still make 192 workgroups or more, as rows come
+// in padded to 256: up to 512 rows two, up to 256 one, unless K is so short that launches are all there is.
+// Two as well between K = 11265 and 12288, where four would run with a quarter of their lanes idle.
+// us, a workgroup of 256 or 1024 threads per row with conversions to double before / four / two / one rows:
+//    256 x  4096   3.8 / 4.0 / 3.6 / 3.4      512 x  4096   4.4 / 4.0 / 3.7 / 4.2
+//    256 x 12288   5.9 / 8.0 / 4.8 / 4.7      512 x 12288   8.5 / 8.3 / 5.5 / 6.7
+//   1024 x  4096   6.0 / 4.2 / 4.6 / 5.8     2048 x 11008  18.3 / 13.6 / 13.5 / 17.0 (4.1 TB/s)
+template <int RB, int NW, int NG>
 __global__ __launch_bounds__(64 * NW) void k_act_scale_fragments(const uint16_t *__restrict__ A, int64_t lda, int M,
                                                                 int K, uint16_t *__restrict__ s_out,
                                                                 uint32_t *__restrict__ frag, int s_pad)
 {
-    constexpr int RB = 4, LPR = 64 / RB;  // rows; lanes, and groups of 8 elements, per row in one pass of a wavefront
+    constexpr int LPR = 64 / RB;  // lanes, and groups of 8 elements, per row in one pass of a wavefront
     __shared__ long long s_part[NW][RB];
     __shared__ uint16_t s_bits[RB];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -791,13 +794,23 @@ hipError_t launch_act_scale_quantize(const void *A, int64_t lda, int M, int K, u
     const int s_pad = fp4_s_pad(rw);
     const int rows = frag ? 32 * fp4_rb_pad(M) : M;
     const int c8 = frag ? 8 * s_pad : 4 * rw;  // 128-bit groups a row's threads must cover (padding included)
-#define BWTA_SF(NW_, NG_)                                                                                          \
-    if (frag && c8 <= 16 * NW_ * NG_) {                                                                            \
-        hipLaunchKernelGGL((k_act_scale_fragments<NW_, NG_>), dim3(rows / 4), dim3(64 * NW_), 0, st,                \
+#define BWTA_SF(RB_, NW_, NG_)                                                                                     \
+    if (c8 <= 64 / RB_ * NW_ * NG_) {                                                                              \
+        hipLaunchKernelGGL((k_act_scale_fragments<RB_, NW_, NG_>), dim3(rows / RB_), dim3(64 * NW_), 0, st,         \
                            (const uint16_t *)A, lda, M, K, s_out, frag, s_pad);                                    \
         return hipGetLastError();                                                                                  \
     }
-    BWTA_SF(4, 1) BWTA_SF(4, 2) BWTA_SF(4, 4) BWTA_SF(8, 4) BWTA_SF(8, 6) BWTA_SF(8, 8) BWTA_SF(8, 11) BWTA_SF(8, 16)
+    // Rows per workgroup: see k_act_scale_fragments.  rows is a multiple of 256, c8 of 64.
+    if (frag) {
+        if (rows <= 256 && c8 > 128) {
+            BWTA_SF(1, 4, 1) BWTA_SF(1, 8, 1) BWTA_SF(1, 8, 2) BWTA_SF(1, 8, 3) BWTA_SF(1, 8, 4)
+        }
+        if ((rows <= 512 && c8 > 64) || (c8 > 1408 && c8 <= 1536)) {
+            BWTA_SF(2, 4, 1) BWTA_SF(2, 4, 2) BWTA_SF(2, 4, 4) BWTA_SF(2, 8, 4) BWTA_SF(2, 8, 6) BWTA_SF(2, 8, 8)
+        }
+        BWTA_SF(4, 4, 1) BWTA_SF(4, 4, 2) BWTA_SF(4, 4, 4) BWTA_SF(4, 8, 4) BWTA_SF(4, 8, 6) BWTA_SF(4, 8, 8)
+        BWTA_SF(4, 8, 11) BWTA_SF(4, 8, 16)
+    }
 #undef BWTA_SF
     if (frag) {
         if (c8 > 4096) return hipErrorInvalidValue;

@@ -202,12 +202,14 @@ def test_scale_and_ternarise_in_one_pass(M, N, K, lda, path):
 
 
 @pytest.mark.parametrize("K", [1, 7, 129, 512, 513, 1024, 1031, 2048, 2050, 4096, 4100, 6144, 6150, 8192, 8195, 11264, 11270,
-                               16384, 16385])
-def test_one_pass_fragments_at_the_edges_of_their_row_splits(K):
+                               12288, 12289, 16384, 16385])
+@pytest.mark.parametrize("M", [133, 411, 643])
+def test_one_pass_fragments_at_the_edges_of_their_row_splits(M, K):
     """Fragments of bwta_prepare_act_autoscale against bwta_act_scale + bwta_prepare_act (both held to the
     oracle above), bit for bit over the whole padded operand: row lengths around every change of
-    wavefronts and groups per thread, a row count that leaves padding rows, rows on odd addresses."""
-    M, lda = 133, K + 1
+    wavefronts and groups per thread with one, two and four rows per workgroup, row counts that leave padding
+    rows, rows on odd addresses."""
+    lda = K + 1
     _say("one-pass fragments", M, K)
     A = np.ascontiguousarray(synth.gaussian_outlier_activations(400 + K, 1, M, lda))
     A[:, K:] = np.nan
