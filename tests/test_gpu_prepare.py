@@ -123,7 +123,7 @@ SCALE_K = [1, 3, 7, 8, 9, 63, 64, 65, 127, 128, 130, 256, 257, 511, 512, 515, 10
 
 
 @pytest.mark.parametrize("K", SCALE_K)
-@pytest.mark.parametrize("M", [1, 67])
+@pytest.mark.parametrize("M", [1, 67, 515])  # up to 512 rows and beyond: a workgroup or a wavefront per long row
 def test_act_scale_at_the_edges_of_its_row_splits(M, K):
     """Exact at every split: odd leading dimensions (rows start on any 2-byte boundary), a row with
     NaN and Inf beside finite ones, subnormals, the largest values, an all-zero row.  The row past the
