@@ -384,11 +384,15 @@ hipError_t launch_linear_one(const void *A, const GemmArgs &g, hipStream_t st)
         return hipGetLastError();
     };
     // Two passes per wavefront halve the workgroups that ternarise the row; where one pass comes to a
-    // workgroup per compute unit at most, one.  Kernel time with 1 / 2 / 4 passes, us: N x K 11008 x 4096
-    // 4.5 / 3.9 / 3.9, 11008 x 11008 7.1 / 5.6 / 5.7, 4096 x 11008 4.6 / 4.1 / 4.7, 768 x 1024 2.7 / 2.9 / 3.2.
+    // workgroup per compute unit at most, one; where two come to more than six, four.  us with 1 / 2 / 4 passes:
+    // N x K 768 x 1024 2.7 / 2.9 / 3.2, 4096 x 11008 4.6 / 4.1 / 4.7 (kernel), 11008 x 4096 4.5 / 3.6 / 3.5,
+    // 11008 x 11008 7.1 / 5.1 / 5.0; with 2 / 4 passes 32000 x 4096 5.5 / 5.2, 32000 x 16384 14.1 / 12.7 (two kernels
+    // 13.0), 128256 x 4096 14.8 / 12.2 (13.7).
     auto pick = [&](auto lanes, auto chunks) {
-        if ((int64_t)g.N * decltype(lanes)::value <= 256 * 4 * 64) return go(lanes, chunks, std::integral_constant<int, 1>{});
-        return go(lanes, chunks, std::integral_constant<int, 2>{});
+        const int64_t lanes_all = (int64_t)g.N * decltype(lanes)::value;  // of one pass over all rows
+        if (lanes_all <= 256 * 4 * 64) return go(lanes, chunks, std::integral_constant<int, 1>{});
+        if (lanes_all <= 6 * 256 * 4 * 64) return go(lanes, chunks, std::integral_constant<int, 2>{});
+        return go(lanes, chunks, std::integral_constant<int, 4>{});
     };
     constexpr std::integral_constant<int, 8> g8{};
     constexpr std::integral_constant<int, 16> g16{};

@@ -490,6 +490,23 @@ def test_linear_one_token_one_launch(N, K):
             assert same_half(a[:N].cpu().numpy()[None], want)
 
 
+@pytest.mark.parametrize("K", [1024, 1020, 2048, 2047, 4096, 4000, 8192, 8100, 12288, 12001, 16384, 16000])
+@pytest.mark.parametrize("passes", [2, 4])
+def test_linear_one_token_tall_matrices(passes, K):
+    """One token against matrices whose rows take two and four passes per wavefront: every row split (lanes per row,
+    chunks per lane), rows that are whole 128-byte lines and rows that are not, a last workgroup that is partly empty."""
+    lanes = 8 if K <= 1024 else 16 if K <= 2048 else 32
+    N = (65536 if passes == 2 else 6 * 65536) // lanes + 77
+    _say("one-launch linear, one token, tall", passes, N, K)
+    assert B.planned_kernel(B.OPERAND_FP16, 1, N, K) == B.KERNEL_LINEAR_ONE
+    A, s = _activation_case(42 + N + K, 1, K)
+    block = synth.binary_pm1(43, K, (64, K))
+    w = np.ascontiguousarray(block[np.arange(N) % 64] * synth.binary_pm1(44, N, (N, 1))).astype(np.int8)
+    s_w = synth.scales(43, 9, N)
+    _, _, want = oracle.linear(A, s, w, s_w)
+    assert same_half(gpu_linear(A, s, gpu_pack_weights(w), s_w, N), want)
+
+
 @pytest.mark.parametrize("M,N,K", [(2, 1, 1025), (31, 129, 1536), (128, 250, 3072), (97, 8191, 1031), (129, 128, 1537),
                                    (300, 500, 2047), (250, 4096, 1025), (200, 70, 11003), (513, 1900, 1100),
                                    (777, 1500, 2560), (2050, 383, 1800), (2048, 1536, 1030), (2300, 1100, 2049),
