@@ -75,15 +75,15 @@ def test_quantize_pack_fp16_large_aligned_rows(M, K, lda):
 def test_quantize_pack_rows_on_any_address(M, K, lda, shift):
     """Rows that start on any element and end inside a group of 8, in the kernels of one and of four
     groups per thread: ternary and boolean planes of fp16, ternary planes of int8.  What lies past a
-    row's end is NaN (fp16) or non-zero (int8) and must not show."""
+    row's end is large (fp16) or non-zero (int8) and must not show."""
     _say("quantize rows on any address", M, K, lda, shift)
     A, s = _activation_case(500 + K, M, K, lda)
-    A[:, K:] = np.nan
+    inputs.poison_gap(A, K)
     t = oracle.ternarize(np.ascontiguousarray(A[:, :K]), s)
     mask, sign, _ = oracle.pack_act(t)
     rw = B.plane_row_words(K)
     m, g = (torch.full((M, rw), -1, dtype=torch.int32, device="cuda:0") for _ in range(2))
-    flat = torch.full((shift + A.size,), float("nan"), dtype=torch.float16, device="cuda:0")
+    flat = torch.full((shift + A.size,), 65504.0, dtype=torch.float16, device="cuda:0")
     flat[shift:] = dev(A).reshape(-1)
     B.bwta_quantize_pack_act(flat[shift:], dev(s), m, g, None, M=M, K=K, lda=lda)
     torch.cuda.synchronize()
@@ -459,12 +459,12 @@ def _scratch(M, N, K):
     return torch.empty(max(B.workspace_bytes(M, N, K), 256), dtype=torch.uint8, device="cuda:0")
 
 
-@pytest.mark.parametrize("K", [8, 300, 1024, 1025, 2048, 2999, 4096, 8193, 11008, 12289, 16384])
+@pytest.mark.parametrize("K", [8, 300, 1024, 1025, 2048, 2999, 4096, 4097, 5000, 8192, 8193, 11008, 12288, 12289, 16384])
 @pytest.mark.parametrize("N", [1, 9, 1031, 2050])
 def test_linear_one_token_one_launch(N, K):
     """One token in one launch: both sides of every row split (lanes per row, chunks per lane), rows that
-    end inside a word and inside a group of 8, one and two passes per wavefront, the three scale modes, an
-    invalid scale, and results that overwrite the activations."""
+    end inside a word and inside a group of 8, one pass per wavefront and where 32 lanes share a row two, the three
+    scale modes, an invalid scale, and results that overwrite the activations.  (More passes: the tall matrices.)"""
     rng = np.random.default_rng(N + K)
     _say("one-launch linear, one token", N, K)
     assert B.planned_kernel(B.OPERAND_FP16, 1, N, K) == B.KERNEL_LINEAR_ONE
@@ -476,7 +476,7 @@ def test_linear_one_token_one_launch(N, K):
         _, _, want = oracle.linear(A, s_a, w, sw)
         out = torch.full((1, N), float("nan"), dtype=torch.float16, device="cuda:0")
         off = int(rng.integers(0, 8))  # rows of any address
-        buf = torch.zeros(K + 8, dtype=torch.float16, device="cuda:0")
+        buf = torch.full((K + 8,), 65504.0, dtype=torch.float16, device="cuda:0")  # and large values beside it
         a = buf[off:off + K]
         a.copy_(dev(A)[0])
         B.bwta_linear(a, None if s_a is None else dev(s_a), wsign, None if sw is None else dev(sw), out,
@@ -536,7 +536,10 @@ def test_linear_slabs_one_launch(M, N, K, scales):
     pitch = max(lda, ldo)
     buf = torch.zeros(M * pitch + 8, dtype=torch.float16, device="cuda:0")
     a = buf[M % 8:M % 8 + M * pitch].view(M, pitch)
-    a[:, :K] = dev(A)
+    rows = np.zeros((M, pitch), np.float16)
+    rows[:, :K] = A
+    inputs.poison_gap(rows, K)
+    a.copy_(dev(rows))
     out = torch.full((M, ldo), float("nan"), dtype=torch.float16, device="cuda:0")
     args = (None if s_a is None else dev(s_a), wsign, None if sw is None else dev(sw))
     modes = dict(a_scale_mode=B.SCALE_VECTOR, w_scale_mode=B.SCALE_VECTOR) if scales == "vector" else {}
@@ -684,12 +687,12 @@ def test_linear_one_launch_scale_modes_and_strides():
                                         (5, 130, 1500, 0), (300, 131, 1029, 0), (300, 261, 1100, 243), (150, 131, 1100, 223)])
 def test_linear_rows_on_any_address(M, N, K, tile):
     """bwta_linear with input and output rows that start on odd elements, lengths that end inside a group
-    of 8 on both sides: the one-launch kernel, the decode kernel and the tiled kernels.  NaN lies
+    of 8 on both sides: the one-launch kernel, the decode kernel and the tiled kernels.  Large values lie
     between the input rows; what lies between the output rows stays."""
     _say("linear on any address", M, N, K, tile)
     lda, ldo = K + 3, N + 2
     A, s = _activation_case(900 + K, M, K, lda)
-    A[:, K:] = np.nan
+    inputs.poison_gap(A, K)
     w = synth.binary_pm1(901 + K, 2, (N, K))
     s_w = synth.scales(901 + K, 3, N)
     _, _, want = oracle.linear(np.ascontiguousarray(A[:, :K]), s, w, s_w)

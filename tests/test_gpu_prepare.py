@@ -9,6 +9,7 @@ import torch
 import oracle
 from gpu_util import dev, gpu_gemm, host_u32, max_rel_err, same_half
 from paper_2604_03957_amd import binding as B
+import inputs
 import synth
 
 pytestmark = pytest.mark.gpu
@@ -126,12 +127,12 @@ SCALE_K = [1, 3, 7, 8, 9, 63, 64, 65, 127, 128, 130, 256, 257, 511, 512, 515, 10
 @pytest.mark.parametrize("M", [1, 67, 515])  # up to 512 rows and beyond: a workgroup or a wavefront per long row
 def test_act_scale_at_the_edges_of_its_row_splits(M, K):
     """Exact at every split: odd leading dimensions (rows start on any 2-byte boundary), a row with
-    NaN and Inf beside finite ones, subnormals, the largest values, an all-zero row.  The row past the
-    last one's end is poisoned with NaN where the matrix has room for it."""
+    NaN and Inf beside finite ones, subnormals, the largest values, an all-zero row.  What lies between
+    the rows is large and must not show."""
     _say("act scale edges", M, K)
     lda = K + 3
     A = np.ascontiguousarray(synth.gaussian_outlier_activations(300 + K, 1, M, lda))
-    A[:, K:] = np.nan
+    inputs.poison_gap(A, K)
     A[0, K - 1] = np.float16(-65504.0)
     if M > 4:
         A[1, :K] = np.float16(6e-8)
@@ -208,11 +209,11 @@ def test_one_pass_fragments_at_the_edges_of_their_row_splits(M, K):
     """Fragments of bwta_prepare_act_autoscale against bwta_act_scale + bwta_prepare_act (both held to the
     oracle above), bit for bit over the whole padded operand: row lengths around every change of
     wavefronts and groups per thread with one, two and four rows per workgroup, row counts that leave padding
-    rows, rows on odd addresses."""
+    rows, rows on odd addresses with large values between them."""
     lda = K + 1
     _say("one-pass fragments", M, K)
     A = np.ascontiguousarray(synth.gaussian_outlier_activations(400 + K, 1, M, lda))
-    A[:, K:] = np.nan
+    inputs.poison_gap(A, K)
     A[1, K - 1] = np.inf
     A[2, :] = 0
     dA = dev(A)
