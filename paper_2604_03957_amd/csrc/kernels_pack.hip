@@ -452,7 +452,7 @@ struct SignedSum {
 // than 2^24 units of 2^-24 and exact in fp32; the groups' sums are added as integers.  (Weights of a standard
 // deviation up to 0.08 or so pass; any others take the double form.)
 struct SmallSum {
-    int units = 0;  // at most 24 groups: below 2^29
+    int units = 0;  // at most 16 groups of less than 2^24: below 2^28
 
     __device__ __forceinline__ void add(const uint32_t (&w)[4])
     {

@@ -459,7 +459,7 @@ def _scratch(M, N, K):
     return torch.empty(max(B.workspace_bytes(M, N, K), 256), dtype=torch.uint8, device="cuda:0")
 
 
-@pytest.mark.parametrize("K", [8, 300, 1024, 1025, 2048, 2999, 4096, 4097, 5000, 8192, 8193, 11008, 12288, 12289, 16384])
+@pytest.mark.parametrize("K", [8, 300, 1024, 1025, 2048, 2999, 3900, 4096, 4097, 5000, 8192, 8193, 11008, 12288, 12289, 16384])
 @pytest.mark.parametrize("N", [1, 9, 1031, 2050])
 def test_linear_one_token_one_launch(N, K):
     """One token in one launch: both sides of every row split (lanes per row, chunks per lane), rows that
@@ -490,7 +490,7 @@ def test_linear_one_token_one_launch(N, K):
             assert same_half(a[:N].cpu().numpy()[None], want)
 
 
-@pytest.mark.parametrize("K", [1024, 1020, 2048, 2047, 4096, 4000, 8192, 8100, 12288, 12001, 16384, 16000])
+@pytest.mark.parametrize("K", [1024, 890, 2048, 1900, 4096, 3900, 8192, 8000, 12288, 12001, 16384, 16000])
 @pytest.mark.parametrize("passes", [2, 4])
 def test_linear_one_token_tall_matrices(passes, K):
     """One token against matrices whose rows take two and four passes per wavefront: every row split (lanes per row,
