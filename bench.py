@@ -330,7 +330,7 @@ def run_c2(args, torch, B, synth):
                 "algorithmic_bytes": alg_bytes,
                 "frac_of_hbm_peak": round(alg_bytes / (contraction_ms[dom] * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
                 # HBM/fabric bytes per launch of this kernel from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
-                # runs scaled by the copy probe (profiles/traffic_c2_ffn.md)
+                # runs scaled by the copy probe (profiles/traffic__hbm_bytes_per_launch.md)
                 "traffic": _traffic_from_profiles(B, names[dom], "M=%d N=%d K=%d" % (L.M, L.N, L.K)),
                 "other_contraction_kernels": other}
     out = {"metric": "BWTA linear effective TOPS (ternarize+pack+GEMM+epilogue), encoder FFN shapes",

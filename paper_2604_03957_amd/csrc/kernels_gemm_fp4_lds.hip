@@ -28,9 +28,11 @@
 //     and every wavefront issues the same ones, so n = the younger loads still in flight); after it
 //     the slab is visible to all, and what the previous slab was read from is requested again, one
 //     load between two MFMA steps.  The last two slabs request nothing.
-//     Measured with the 64-byte runs and the spread loads, us on ready fragments (M x N x K):
-//     2048 x 11008 x 4096 40.9 -> 40.4, 2048 x 4096 x 11008 38.9 -> 38.3, 2048 x 4096 x 4096
-//     16.7 -> 16.6, 4096 x 3072 x 1024 10.6 -> 9.9.
+//     The 64-byte runs and the spread loads together, us on ready fragments whose bits seldom toggle
+//     (M x N x K): 2048 x 11008 x 4096 36.4 -> 35.4, 4096 x 4096 x 4096 25.5 -> 25.0, 8192 x 4096 x 1024
+//     21.1 -> 20.6; level at 2048 x 4096 x 11008 (34.4 / 34.5), within 1 % at 2048 x 4096 x 4096 and
+//     4096 x 3072 x 1024.  With random operands, which the clock pays for, all are level within the noise
+//     (40.2 / 40.4 and 38.6 / 38.7 on the first and the fourth).
 //   * What bounds it: with all-zero operands the same launch of 2048 x 11008 x 4096 takes 34 us
 //     instead of 40 (the clock drops under the power of toggling operands); without direct loads 36.5,
 //     without LDS reads 35, without both 31.6.
