@@ -584,11 +584,11 @@ def test_linear_results_share_memory_with_the_activations(M, N, K, pitch, start)
     assert same_half(buf.cpu().numpy(), flat)
 
 
-@pytest.mark.parametrize("M,N", [(2, 4300), (70, 3001), (297, 4990), (513, 4090), (513, 10990), (1000, 9000)])
+@pytest.mark.parametrize("M,N", [(2, 4300), (70, 3001), (297, 4990), (513, 4090), (513, 10990), (1000, 9000), (8230, 130)])
 @pytest.mark.parametrize("K", [200, 300, 515, 900])
 def test_linear_one_launch_strips_beyond_a_round_of_xcds(M, N, K):
     """Token strips that do not come in whole rounds of 8 and with many workgroups each: their workgroups are dealt to
-    the XCDs one by one.  One strip alone, a few, and some behind whole rounds; four and eight wavefronts, one and two
+    the XCDs one by one.  One strip alone, a few, some behind whole rounds, and strips that are not split; four and eight wavefronts, one and two
     channel blocks per group, one to four chunks of K; every (strip, split) must be done once."""
     _say("one-launch linear, partial round of strips", M, N, K)
     B.set_tile(901)  # K = 900 also beyond 4096 channels
