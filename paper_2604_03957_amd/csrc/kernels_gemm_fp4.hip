@@ -770,20 +770,22 @@ static int fp4_tile_for(const GemmArgs &g)
     if (g.K >= 1024 && gemm_fp4_lds_supported(g)) {
         const int64_t tiles256 = tm * ((g.N + 255) / 256), tiles64 = ((int64_t)g.M + 63) / 64 * ((g.N + 127) / 128);
         // Tiles of 64 x 128 at three wavefronts per SIMD where 128 x 128 ones fill one round badly and K is short
-        // enough that their second fetch of the weights is not what counts.  us on ready fragments, the other choice
-        // against this one:
+        // enough that their second fetch of the weights is not what counts.  us of bwta_linear, whose product reads
+        // fragments that have just been written (a product that finds them in its L2 gains 0 to 5 % less from these
+        // tiles), the other choice against this one:
         //   A little more than one 128 x 128 tile per compute unit, while the 64 x 128 ones come to two at most (a last
-        //   row of tiles that is half empty): 300 x 11008 x 2048 9.7 / 8.4, 1600 x 2500 x 3072 12.8 / 11.3; with more
-        //   than two, 1024 x 4608 x 3072 12.1 / 13.0, except for K just beyond 1024, which the LDS-staged kernel walks as
-        //   1536 (3000 x 1536 x 1100 8.5 / 7.9).
-        //   129 to 223 tiles that 128 x 96 ones spread over one round: where 96 leaves a ragged edge (600 x 4096 x 1100
-        //   7.7 / 7.0, 900 x 2500 x 1536 8.1 / 7.8) or 64 x 128 ones make one round too (300 x 6144 x 1536 6.7 / 6.1), up to
-        //   K = 1536; not where 96 divides N (2048 x 1536 x 1536 6.6 / 7.2), nor beyond (900 x 3001 x 2048 8.7 / 9.0).
-        //   129 to 223 of which 128 x 96 ones make more than a round: up to K = 1536, and with a ragged edge at 128 to
-        //   3072 (1200 x 2500 x 2048 9.7 / 9.2); 384 x 8192 x 2048 8.0 / 8.3.
+        //   row of tiles that is half empty): 300 x 11008 x 2048 12.7 / 10.7, 1600 x 2500 x 3072 19.1 / 16.1; with more
+        //   than two, 1024 x 4608 x 3072 16.4 / 16.9, except for K just beyond 1024, which the LDS-staged kernel walks
+        //   as 1536 (3000 x 1536 x 1100 13.7 / 13.0).
+        //   129 to 223 tiles that 128 x 96 ones spread over one round: up to K = 1536 where 96 leaves a ragged edge (600 x
+        //   4096 x 1100 10.7 / 9.4, 900 x 2500 x 1536 11.3 / 10.4) or 64 x 128 ones make one round too (300 x 6144 x
+        //   1536 9.5 / 9.2); where 96 divides N up to 1280 (2048 x 1536 x 1100 10.5 / 10.1), level at 1536 and behind on
+        //   fragments in the L2 (4096 x 768 x 1536 11.8 / 12.0).
+        //   129 to 223 of which 128 x 96 ones make more than a round: 1200 x 2500 x 2048 13.4 / 12.1, 300 x 8192 x 2048
+        //   11.2 / 10.7.
         const bool spills = tiles128 > 256 && tiles128 <= 288 && (tiles64 <= 512 || (g.K > 1024 && g.K <= 1280));
         const bool between = tiles128 > 128 && tiles128 < 224 &&
-                             (tiles96 <= 256 ? g.K <= 1536 && (g.N % 96 != 0 || tiles64 <= 256) : g.K <= 1536 || g.N % 128 != 0);
+                             (tiles96 > 256 || g.K <= (g.N % 96 != 0 || tiles64 <= 256 ? 1536 : 1280));
         if ((spills || between) && g.K <= 3072 && tiles256 < 160) return 12;
         if (tiles256 >= (g.K >= 2048 ? 160 : 224)) return 243;
         if (tiles128 >= 224) return 223;

@@ -93,16 +93,16 @@ def test_planned_kernel_of_the_linear():
 
 def test_planned_tile_of_the_tiled_product():
     """Tiles of 64 x 128 only in the windows where they are ahead: few more 128 x 128 tiles than compute units while the
-    64 x 128 ones come to two each; 129 to 223 with a ragged edge at 96 (or 128) channels or one round of 64 x 128."""
+    64 x 128 ones come to two each; 129 to 223, where 128 x 96 ones make one round only for a short K."""
     t = B.planned_tile
     assert t(300, 11008, 2048) == t(1600, 2500, 3072) == t(400, 9216, 1024) == 12        # 430, 500, 504 tiles of 64 x 128
     assert t(1024, 4608, 2048) == t(384, 11008, 1536) == t(1280, 3300, 3072) == 223      # 576, 516, 520 of them
     assert t(300, 11008, 3073) == t(1024, 4608, 1024) == t(1024, 4608, 1281) == 223 and t(1024, 4608, 1025) == 12
     assert t(600, 4096, 1536) == t(900, 2500, 1024) == t(300, 6144, 1536) == 12
-    assert t(2048, 1536, 1536) == t(4096, 768, 1024) == t(1600, 1536, 1100) == 13        # 96 divides N
+    assert t(2048, 1536, 1280) == t(4096, 768, 1024) == 12 and t(2048, 1536, 1281) == t(4096, 768, 1536) == 13  # 96 divides N
     assert t(600, 4096, 1537) == t(900, 3001, 2048) == 13
-    assert t(1200, 2500, 3072) == t(900, 3300, 2048) == t(384, 8192, 1536) == 12          # 128 x 96: more than a round
-    assert t(384, 8192, 1537) == 23 and t(384, 8192, 2048) == t(1200, 2500, 3073) == 22
+    assert t(1200, 2500, 3072) == t(900, 3300, 2048) == t(384, 8192, 2048) == 12          # 128 x 96: more than a round
+    assert t(384, 8192, 3073) == t(1200, 2500, 3073) == 22
     assert t(2048, 11008, 4096) == 243 and t(1024, 4096, 4096) == 223 and t(512, 4096, 4096) == 11
     assert t(4096, 3072, 768) == 23 and t(0, 8, 8) == 0
     huge_n = (1 << 32) // (344 * 4) + 1          # packed weights beyond the LDS-staged kernel's 32-bit offsets
