@@ -63,7 +63,9 @@ int bwta_linear_launches(int M, int N, int K);
  * = blocks of 32 rows x 32 columns per wavefront; 23 = 22 at three wavefronts per SIMD; 222 = 22
  * with K split over two groups of wavefronts; 243, 223, 323 = the kernel that stages both operands
  * through LDS with direct loads, as 128 x 256 tiles of 8 wavefronts, 128 x 128 tiles of 4, or
- * 128 x 256 tiles of 4 wavefronts of 64 tokens x 128 channels), the popcount decode kernel's row split (1000 + 16 *
+ * 128 x 256 tiles of 4 wavefronts of 64 tokens x 128 channels; 422, 521, 611 = the kernel of 16 x 16 blocks,
+ * fp16 results only, as 128 x 256 tiles, 128 x 128 with K split over two groups of wavefronts, 64 x 128 with
+ * K split over four), the popcount decode kernel's row split (1000 + 16 *
  * lanes per row (8, 16, 32) + chunks per lane; ignored where the registers cannot hold it) or the
  * matrix-core decode kernel's work split (2000 + 1024 * ring depth (2..4) + 64 * chunks per
  * wavefront (1..4) + tiles per workgroup (rounded up to a multiple of the ring depth, fewer if LDS
@@ -71,8 +73,10 @@ int bwta_linear_launches(int M, int N, int K);
  * wherever the one-launch kernel can run, 900 + R the same with R channel splits per token
  * strip); 0 restores the built-in choices.  Results do not depend on it. */
 int bwta_set_tile(int tile);
-/* Which of those tiles the tiled FP4 kernel (BWTA_KERNEL_GEMM_FP4) takes for a shape and fp16 results under
- * the current settings; 0 for a non-positive dimension. */
+/* How a product (BWTA_KERNEL_GEMM_FP4) of fp16 results runs under the current settings: bwta_planned_wide says which
+ * tile of the kernel of 16 x 16 blocks (422, 521, 611) takes the shape, 0 if none does; then, and for int32 results,
+ * bwta_planned_tile says which of the other tiles.  0 for a non-positive dimension. */
+int bwta_planned_wide(int M, int N, int K);
 int bwta_planned_tile(int M, int N, int K);
 #ifdef __cplusplus
 }

@@ -599,6 +599,12 @@ int bwta_planned_tile(int M, int N, int K)
     return bwta::fp4_planned_tile(M, N, K);
 }
 
+int bwta_planned_wide(int M, int N, int K)
+{
+    if (M <= 0 || N <= 0 || K <= 0) return 0;
+    return bwta::fp4_planned_wide(M, N, K);
+}
+
 int bwta_version(void) { return 2; }
 
 #ifndef BWTA_BUILD_ID

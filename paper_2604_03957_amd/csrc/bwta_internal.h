@@ -59,6 +59,7 @@ hipError_t launch_gemm_mfma(const GemmArgs &g, hipStream_t st);
 size_t gemm_fp4_frag_bytes(int M, int K);
 void set_fp4_tile(int t);
 int fp4_planned_tile(int M, int N, int K);
+int fp4_planned_wide(int M, int N, int K);
 // the whole linear in one launch (short K, fp16 in, fp16 out)
 bool linear_fused_supported(const GemmArgs &g);
 hipError_t launch_linear_fused(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);
@@ -79,6 +80,7 @@ void set_gemv_tile(int g, int nch);
 hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, hipStream_t st);
 bool gemm_fp4_lds_supported(const GemmArgs &g);
 hipError_t launch_gemm_fp4_lds(const GemmArgs &g, const uint32_t *frag, int variant, hipStream_t st);
+hipError_t launch_gemm_fp4_wide(const GemmArgs &g, const uint32_t *frag, int variant, hipStream_t st);
 hipError_t launch_quantize_to_fp4(const void *A, int64_t lda, ScaleArg s_a, int M, int K, uint32_t *frag,
                                   hipStream_t st);
 hipError_t launch_act_scale_quantize(const void *A, int64_t lda, int M, int K, uint16_t *s_out, uint32_t *frag,

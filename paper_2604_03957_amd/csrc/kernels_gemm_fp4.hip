@@ -803,6 +803,53 @@ static int fp4_tile_for(const GemmArgs &g)
     return g.K >= 2048 ? 22 : 23;
 }
 
+// Where the kernel of 16 x 16 blocks (kernels_gemm_fp4_wide.hip) is ahead of those tiles, and with which of its tiles:
+// 422 = 128 x 256, 521 = 128 x 128 with K split over 2 groups of wavefronts, 611 = 64 x 128 with K split over 4; 0: not.
+// It draws less power per operation and its fixed cost is higher (a larger tile per wavefront to fill, sums to exchange),
+// so K decides: by pairs of slabs (512 k), of which every group should get the same number.  From 1 580 shapes of
+// bwta_linear as two kernels, M 160 .. 8192, N 300 .. 11008, K 1100 .. 11008; the tiles above / this one, us:
+//   Up to 256 tiles of 64 x 128 (the others give fewer workgroups than compute units): K split over 4 from K = 3073, where
+//   it takes two pairs per group: 512 x 2048 x 3500 12.1 / 11.3, 256 x 4096 x 4096 14.2 / 11.9, 300 x 1152 x 11008 27.8 / 21.
+//   Up to K = 3072 it is level (0.95 to 1.03 of the others' time).
+//   257 to 512 of them: over 4 where the pairs come out even (K = 4096: 0.90 to 0.95, 8192: 0.85 to 0.92), else over 2 (K =
+//   5000: 0.95, 6500: 0.96), from six pairs (K = 2816: 0.96 to 1.01, 3072: 0.95 to 1.0); except where tiles of 64 x 128
+//   of the other kernel just fill two rounds (1300 x 3001 x 3072 15.3 / 17.4).
+//   513 to 1536: over 2, from six pairs on (K = 2816: 0.96 to 0.98, 4096: 0.91 to 0.95, 11008: 0.85 to 0.94), not with
+//   seven, where one group idles for an eighth of the time (K = 3500: 0.98 to 1.03).
+//   More: whole tiles of 128 x 256, from eight pairs on (K = 4096: 0.95 to 0.97; 2048 x 11008 x 4096 46.5 / 44.6); with six
+//   level (0.96 to 1.05), below behind.
+static int fp4_wide_for(const GemmArgs &g)
+{
+    if (!gemm_fp4_lds_supported(g)) return 0;
+    const int64_t tn = ((int64_t)g.N + 127) / 128, tiles64 = ((int64_t)g.M + 63) / 64 * tn, tiles128 = ((int64_t)g.M + 127) / 128 * tn;
+    const int pairs = fp4_s_pad(g.rw) / 8;
+    if (tiles64 <= 256) return pairs >= 7 ? 611 : 0;
+    if (tiles64 <= 512 && pairs >= 7 && (pairs % 4 == 0 || pairs % 4 == 3)) return 611;
+    if (tiles64 <= 1536) {
+        const bool spills = tiles128 > 256 && tiles64 <= 512 && pairs <= 6;  // 12 below
+        return pairs >= 6 && pairs != 7 && !spills ? 521 : 0;
+    }
+    return pairs >= 8 ? 422 : 0;
+}
+
+// the kernel of 16 x 16 blocks: forced (tuning sweeps), or by the rule unless one of the other tiles is forced
+static int fp4_wide(const GemmArgs &g)
+{
+    const int forced = g_fp4_tile.load(std::memory_order_relaxed);
+    switch (forced) {
+    case 422: case 521: case 611: return gemm_fp4_lds_supported(g) ? forced : 0;
+    case 11: case 12: case 13: case 21: case 22: case 23: case 222: case 223: case 243: case 323: return 0;
+    default: return fp4_wide_for(g);
+    }
+}
+
+int fp4_planned_wide(int M, int N, int K)
+{
+    GemmArgs g{};
+    g.M = M, g.N = N, g.K = K, g.rw = (int)(4 * (((int64_t)K + 127) / 128));
+    return fp4_wide(g);
+}
+
 // the forced tile (tuning sweeps) where the shape can take it, else the rule's
 static int fp4_tile(const GemmArgs &g)
 {
@@ -842,6 +889,8 @@ hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, h
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
+    const int wide = g.acc ? 0 : fp4_wide(g);  // int32 output: test / debug path
+    if (wide) return launch_gemm_fp4_wide(g, frag, wide, st);
     const int tile = fp4_tile(g);
     const bool lds = tile == 223 || tile == 243 || tile == 323;
     // int32 output (test / debug path) takes the LDS-staged kernel only where it is forced

@@ -256,6 +256,23 @@ static int strip_blocks(const GemmArgs &g)
 //   NB = 3 ahead from 2048 tokens (4096 x 768 x 3072 15.7 / 12.8, 2048 x 1536 x 2048 11.4 / 10.1), mixed below (777 x 3072 x
 //   4096 15.3 / 14.2, 1024 x 3072 x 11008 28.3 / 32.0); beyond K = 8192 only with narrow matrices (2048 x 1536 x 11008 31.5 /
 //   33.5, 4096 x 768 x 11008 39.1 / 33.2).
+// From K = 3073 to 12288 the two kernels end in the product of 16 x 16 blocks with K split inside the workgroup, which
+// leaves this kernel what is cheap to ternarise often or too narrow for it (strip_keeps_long_k; two kernels / one, us):
+//   NB = 1 up to K = 5120 (256 x 768 x 5000 11.4 / 11.4, 1024 x 512 x 4096 10.9 / 9.7; many outputs 256 x 4096 x 5000 12.0 /
+//   13.0), to 7168 from 641 tokens (777 x 768 x 6500 15.1 / 13.6; 512 x 2048 x 6000 12.0 / 14.2), beyond only tall and narrow
+//   (2048 x 512 x 11008 24.9 / 24.2; 777 x 2048.. and wider behind, 256 x 4096 x 11008 16.4 / 21.9).
+//   NB = 2 up to K = 4608 for N <= 1536 (1300 x 1152 x 4096 14.4 / 13.9; 1024 x 2048 x 4096 13.2 / 14.3), to 7168 for N <= 768
+//   (2048 x 768 x 5000 17.8 / 16.5; 777 x 1536 x 6000 14.2 / 16.3), beyond for N <= 512 (4096 x 512 x 11008 33.1 / 28.6).
+//   NB = 3 beyond 8192 for N <= 768 (4096 x 768 x 11008 37.8 / 32.6; 2048 x 1152 x 11008 29.3 / 31.8).
+// Longer K and N below 256 were not swept again.
+static bool strip_keeps_long_k(const GemmArgs &g, int nb)
+{
+    if (g.K <= 3072 || g.K > 12288 || g.N < 256) return true;
+    if (nb == 1) return g.K <= 5120 || (g.M > 640 && g.K <= 7168) || (g.M >= 1280 && g.N <= 512);
+    if (nb == 2) return g.N <= (g.K <= 4608 ? 1536 : g.K <= 7168 ? 768 : 512);
+    return g.K <= 8192 || g.N <= 768;
+}
+
 bool linear_strip_supported(const GemmArgs &g)
 {
     if (g.K <= 512 || g.out == nullptr || g.acc != nullptr || fp4_tuning_forced()) return false;
@@ -264,6 +281,7 @@ bool linear_strip_supported(const GemmArgs &g)
     if (g.M <= 128)
         return (nb == 1 || nb == 2) &&
                (g.K <= 2048 || (g.K <= 2560 && outputs >= 256 * 1024) || (g.K <= 3072 && outputs > 512 * 1024));
+    if (!strip_keeps_long_k(g, nb)) return false;
     const bool narrow = g.N <= 1152;
     return nb == 1 || (nb == 2 && g.M > 512 && (g.K <= 16384 || narrow)) || (nb == 3 && g.M >= 2048 && (g.K <= 8192 || narrow));
 }

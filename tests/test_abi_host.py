@@ -117,6 +117,29 @@ def test_planned_tile_of_the_tiled_product():
         B.set_tile(0)
 
 
+def test_planned_kernel_of_long_products():
+    """Where the kernel of 16 x 16 blocks takes a product, by pairs of slabs (512 k) and tiles of 64 x 128: the edges."""
+    w = B.planned_wide
+    assert [w(512, 4096, K) for K in (3072, 3073, 11008)] == [0, 611, 611]                 # 256 tiles
+    assert [w(513, 4096, K) for K in (2560, 2561, 3073, 4096, 4097, 8192)] == [0, 521, 611, 611, 521, 611]
+    assert w(1300, 3001, 3000) == 0 and w(777, 3001, 2999) == 521                           # 64 x 128 tiles just fill two rounds
+    assert [w(2048, 4096, K) for K in (2560, 3072, 3500, 4096, 11008)] == [0, 521, 0, 521, 521]
+    assert w(3072, 4096, 4096) == 521 and [w(2048, 11008, K) for K in (3584, 3585, 4096)] == [0, 422, 422]
+    assert w(2048, (1 << 32) // (344 * 4) + 1, 11008) == 0 and w(0, 8, 8) == 0              # beyond 32-bit offsets
+    one = [B.planned_kernel(B.OPERAND_FP16, *s) == B.KERNEL_LINEAR_STRIP for s in
+           ((256, 4096, 5120), (256, 4096, 5121), (641, 768, 7168), (640, 768, 7168), (641, 768, 7169), (1280, 512, 12288), (1280, 513, 12288),
+            (1300, 1536, 4096), (1024, 2048, 4096), (2048, 768, 7168), (2048, 768, 7169), (4096, 512, 11008), (4096, 768, 11008),
+            (2048, 1152, 11008), (2048, 1152, 8192))]
+    assert one == [True, False, True, False, False, True, False, True, False, True, False, True, True, False, True]
+    try:
+        B.set_tile(243)
+        assert w(2048, 11008, 4096) == 0 and B.planned_tile(2048, 11008, 4096) == 243
+        B.set_tile(611)
+        assert w(2048, 11008, 4096) == 611
+    finally:
+        B.set_tile(0)
+
+
 def _code(fn, *a, **k):
     with pytest.raises(B.BwtaError) as e:
         fn(*a, **k)

@@ -902,3 +902,36 @@ def test_lds_staged_seeded_random_shapes():
                 assert same_half(gpu_linear(A, s, wsign, s_w, N, path=B.PATH_FP4), want), (case, M, N, K, variant)
         finally:
             B.set_tile(0)
+
+
+@pytest.mark.parametrize("variant", [422, 521, 611])
+@pytest.mark.parametrize("M,N,K", [(129, 1, 100), (300, 200, 1000), (257, 513, 2100), (64 * 5 + 1, 700, 4096), (130, 90, 11008), (192, 256, 3500),
+                                   (1000, 704, 600), (129, 129, 513)])
+def test_tiled_product_of_16x16_blocks(M, N, K, variant):
+    """The kernel of 16 x 16 blocks, every tile forced: one pair of slabs, pairs that do not divide by the groups that
+    share K (some groups get none), ragged tokens and channels, whole and odd rows of results, the three scale
+    modes; what lies between the rows stays."""
+    _say("16 x 16 blocks", M, N, K, variant)
+    t, w, s_a, s_w = _gemm_case(6000 + M + variant, M, N, K, p0=0.5)
+    acc = oracle.gemm_unpacked(t, w)
+    prep = torch.empty(B.prepared_bytes(M, K), dtype=torch.uint8, device="cuda:0")
+    dw = dev(oracle.pack_weights(w))
+    B.set_path(B.PATH_FP4)
+    B.set_tile(variant)
+    try:
+        assert B.planned_wide(M, N, K) == variant
+        assert B.prepared_format(M, K) == B.PREPARED_FP4
+        fmt = B.bwta_prepare_act(dev(t.astype(np.float16)), None, prep, M=M, K=K)  # +-1 / 0 under scale 1: themselves
+        for ldo, off, sa, sw in ((N, 0, s_a, s_w), (N + 3, 1, s_a[:1], s_w), ((N + 15) // 8 * 8, 0, None, None)):
+            out = torch.full((off + M * ldo,), 7.0, dtype=torch.float16, device="cuda:0")
+            B.bwta_gemm_prepared(prep, dw, None if sa is None else dev(sa), None if sw is None else dev(sw), None, out[off:],
+                                 fmt=fmt, M=M, N=N, K=K, ldo=ldo)
+            torch.cuda.synchronize()
+            rows = out.cpu().numpy()[off:].reshape(M, ldo)
+            ones_a, ones_w = np.ones(M, np.float16), np.ones(N, np.float16)
+            want = oracle.epilogue(acc, ones_a if sa is None else np.resize(sa, M), ones_w if sw is None else sw)
+            assert same_half(np.ascontiguousarray(rows[:, :N]), want), (ldo, off)
+            assert (rows[:, N:] == 7).all() and (off == 0 or out[0].item() == 7)
+    finally:
+        B.set_path(B.PATH_AUTO)
+        B.set_tile(0)
