@@ -2,9 +2,14 @@
 
 Argument marshalling only: every step of the path runs in the HIP kernels.  Tensors are
 torch CUDA tensors used as device buffers; the current torch stream is passed through.
+The calls a program makes per layer are marshalled by ``csrc/binding_native.cpp`` where they come in
+their ordinary form (device tensors, Python integers, the current stream); the functions below say
+what every other form does.
 Importing this module without the compiled library raises -- there is no fallback.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 import struct
 
@@ -15,6 +20,7 @@ import torch  # noqa: F401
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # BWTA_LIB: load this build of the same sources instead (the sanitizer test's host-instrumented one)
 LIB_PATH = os.environ.get("BWTA_LIB") or os.path.join(_HERE, "csrc", "libbwta.so")
+NATIVE_PATH = os.path.join(_HERE, "csrc", "_bwta_native.so")
 
 OK = 0
 ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_UNSUPPORTED, ERR_WORKSPACE, ERR_HIP, ERR_TOO_LARGE = -1, -2, -3, -4, -5, -6, -7
@@ -35,10 +41,11 @@ EXPORTS = ["bwta_plane_row_words", "bwta_workspace_bytes", "bwta_quantize_pack_a
            "bwta_quantize_pack_bool", "bwta_matmul_tt", "bwta_prepare_weights", "bwta_act_scale",
            "bwta_prepare_act_autoscale", "bwta_matmul_bool_prepared"]
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError(
-        "%s is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
-        "or python paper_2604_03957_amd/build.py); there is no CPU fallback" % LIB_PATH)
+for _path in (LIB_PATH, NATIVE_PATH):
+    if not os.path.exists(_path):
+        raise ImportError(
+            "%s is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
+            "or python paper_2604_03957_amd/build.py); there is no CPU fallback" % _path)
 
 _lib = ctypes.CDLL(LIB_PATH)
 _c = ctypes
@@ -58,7 +65,8 @@ _lib.bwta_gemm.argtypes = [_P, _P, _P, _c.c_int, _c.c_int, _c.c_int, _P, _c.c_in
 _lib.bwta_linear.restype = _c.c_int
 _lib.bwta_linear.argtypes = [_P, _c.c_int64, _P, _c.c_int, _P, _P, _c.c_int, _c.c_int, _c.c_int,
                              _c.c_int, _P, _c.c_int64, _P, _c.c_size_t, _P]
-# the same call with its arguments packed into one block: 15 ctypes conversions cost more than packing them
+# the same call with its arguments packed into one block (15 ctypes conversions cost more): addresses given as integers,
+# which the native marshalling leaves to this form
 _linear_call = _lib.bwta_linear_call
 _linear_call.restype = _c.c_int
 _linear_call.argtypes = [_c.c_char_p]
@@ -379,3 +387,17 @@ def bwta_gemm_grouped(problem_array, workspace, *, M, N, K, a_scale_mode=SCALE_V
     ldo = N if ldo is None else ldo
     _check(_lib.bwta_gemm_grouped(problem_array, len(problem_array), M, N, K, a_scale_mode, w_scale_mode, ldo,
                                   _ptr(workspace), _nbytes(workspace, workspace_bytes), _stream(stream)))
+
+
+def _load_native():
+    loader = importlib.machinery.ExtensionFileLoader("_bwta_native", NATIVE_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_bwta_native", NATIVE_PATH, loader=loader))
+    loader.exec_module(module)
+    module.setup(_check, _raw_stream, _cur_device)
+    return module
+
+
+# From here on each of these names is the native function, with the Python form above as what it falls back to.
+_native = _load_native()
+for _name in _native.parameters():
+    globals()[_name] = _native.bind(_name, _c.cast(getattr(_lib, _name), _P).value, globals()[_name])

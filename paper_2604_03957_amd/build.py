@@ -1,7 +1,8 @@
 """Compile csrc/*.hip into csrc/libbwta.so for gfx950 with hipcc (cross-compiles without a GPU).
 
 Each source is its own translation unit: the files are compiled side by side (up to 8 at a time)
-into objects under csrc/_build/ and then linked.  Every call compiles everything again unless
+into objects under csrc/_build/ and then linked; the Python binding's host part (csrc/_bwta_native.so)
+is compiled beside them with g++.  Every call compiles everything again unless
 `incremental=True` (a developer convenience: objects newer than their source and every header are
 kept)."""
 import concurrent.futures
@@ -22,6 +23,27 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes",
 ]
+
+
+BINDING_SRC = os.path.join(CSRC, "binding_native.cpp")
+BINDING = os.path.join(CSRC, "_bwta_native.so")
+
+
+def build_binding(verbose=True):
+    """The host-only extension that marshals the per-layer calls (binding_native.cpp), against this torch and Python."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           BINDING_SRC, "-o", tmp, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, BINDING)
+    return BINDING
 
 
 def sources():
@@ -64,8 +86,12 @@ def build_library(verbose=True, extra_flags=(), incremental=False, jobs=8):
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
 
-    with concurrent.futures.ThreadPoolExecutor(max_workers=max(1, min(jobs, len(todo) or 1))) as pool:
+    stale = not (incremental and os.path.exists(BINDING) and os.path.getmtime(BINDING) > max(os.path.getmtime(BINDING_SRC), newest_header))
+    with concurrent.futures.ThreadPoolExecutor(max_workers=max(1, min(jobs, len(todo) + 1))) as pool:
+        binding = pool.submit(build_binding, verbose) if stale else None
         list(pool.map(compile_one, todo))
+        if binding:
+            binding.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs
     if verbose:

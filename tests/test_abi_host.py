@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2604_03957_amd import binding as B
 
@@ -217,6 +218,30 @@ def test_the_block_of_linear_arguments_states_its_size():
     assert len(good) == B._LINEAR_ARGS_SIZE == 104
     assert call(good) == B.OK                                                        # M = N = 0
     assert call(B._linear_pack(*[0] * 16)) == B.ERR_UNSUPPORTED and call(None) == B.ERR_NULL
+
+
+def test_native_marshalling_knows_the_python_forms():
+    """Every natively marshalled call has the Python form's parameters, in its order, and hands it whatever is not the
+    ordinary form (here: host tensors, integers, wrong argument lists) as it came."""
+    import inspect
+    table = B._native.parameters()
+    assert len(table) == 11
+    for name, (positional, params) in table.items():
+        sig = inspect.signature(getattr(B, name))
+        assert [p.name for p in sig.parameters.values()] == params, name
+        assert sum(p.kind is p.POSITIONAL_OR_KEYWORD for p in sig.parameters.values()) == positional, name
+        seen = []
+        f = B._native.bind(name, 0, lambda *a, **k: seen.append((a, k)))    # no address: it must not be called
+        host = torch.zeros(4)
+        required = {p.name: 1 for p in sig.parameters.values() if p.kind is p.KEYWORD_ONLY and p.default is p.empty}
+        for args, kw in (((host,) * positional, required), ((FAKE,) * positional, required), ((), {}), ((None,) * (positional + 1), required),
+                         ((None,) * positional, dict(required, M=1.5, K=1.5)), ((None,) * positional, dict(required, K=2 ** 70)),
+                         ((None,) * positional, dict(required, stream=0)), ((None,) * positional, dict(required, nothing=1))):
+            f(*args, **kw)
+            assert len(seen) == 1 and len(seen[0][0]) == len(args) and all(x is y for x, y in zip(seen[0][0], args)) and seen[0][1] == kw
+            seen.clear()
+    with pytest.raises(KeyError):
+        B._native.bind("bwta_nothing", 0, print)
 
 
 def test_prepare_and_gemm_prepared_reject_bad_arguments():
