@@ -54,6 +54,9 @@ enum {
 };
 enum { BWTA_OPERAND_FP16 = 3 };
 int bwta_planned_kernel(int operand, int M, int N, int K);
+/* 1 where bwta_linear's one launch is the kernel for few tokens and narrow matrices (strips of 16 tokens, all of K at
+ * once), which bwta_planned_kernel counts under BWTA_KERNEL_LINEAR_FUSED (short K) or _STRIP (beyond); else 0. */
+int bwta_planned_rows(int M, int N, int K);
 /* How many kernels bwta_linear launches for a shape under the current settings, given results that do
  * not overlap the activations (a call that works in place always takes two): 1 where ternarisation,
  * product and epilogue run as one kernel (bwta_planned_kernel says which), else 2.  Informational

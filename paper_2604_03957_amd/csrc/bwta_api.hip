@@ -91,7 +91,7 @@ int plan_from_planes(const bwta::GemmArgs &g, bool have_scratch)
 }
 
 // which kernel computes bwta_linear from fp16 in one launch, if one does
-enum class OneLaunch { kNo, kShortK, kStrip, kOneToken };
+enum class OneLaunch { kNo, kShortK, kStrip, kOneToken, kRows };
 
 // Activations and results that share memory (a caller working in place): with two kernels the activations
 // have been read before the first result is written, with one they have not.  Rows of one pitch that lie side by
@@ -110,6 +110,7 @@ bool rows_overlap(const void *A, int64_t lda, int K, const void *out, int64_t ld
 OneLaunch one_launch_linear(const bwta::GemmArgs &g)
 {
     const int path = resolve_path(g.M, g.N, g.K);
+    if (path == BWTA_PATH_FP4 && bwta::linear_rows_supported(g)) return OneLaunch::kRows;
     if (path == BWTA_PATH_FP4 && bwta::linear_fused_supported(g)) return OneLaunch::kShortK;
     if (path == BWTA_PATH_FP4 && bwta::linear_strip_supported(g)) return OneLaunch::kStrip;
     if (path == BWTA_PATH_POPC && bwta::linear_one_supported(g)) return OneLaunch::kOneToken;
@@ -236,6 +237,7 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
     switch (rows_overlap(A, lda, K, out, ldo, N, M) ? OneLaunch::kNo : one_launch_linear(g)) {
     case OneLaunch::kShortK: return hip_result(bwta::launch_linear_fused(A, lda, g, (hipStream_t)stream));
     case OneLaunch::kStrip: return hip_result(bwta::launch_linear_strip(A, lda, g, (hipStream_t)stream));
+    case OneLaunch::kRows: return hip_result(bwta::launch_linear_rows(A, lda, g, (hipStream_t)stream));
     case OneLaunch::kOneToken: return hip_result(bwta::launch_linear_one(A, g, (hipStream_t)stream));
     case OneLaunch::kNo: break;
     }
@@ -560,13 +562,16 @@ int bwta_auto_path(int M, int N, int K)
     return M > 1 ? BWTA_PATH_FP4 : BWTA_PATH_POPC;
 }
 
-static OneLaunch planned_linear(int M, int N, int K)
+static uint16_t plan_sink;  // stands for the results of a call that is only planned
+
+static bwta::GemmArgs planned_args(int M, int N, int K)
 {
-    uint16_t sink = 0;
-    bwta::GemmArgs g{nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
-                     {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &sink, N};
-    return one_launch_linear(g);
+    return {nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
+            {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &plan_sink, N};
 }
+
+static OneLaunch planned_linear(int M, int N, int K) { return one_launch_linear(planned_args(M, N, K)); }
+static bool fused_takes(int M, int N, int K) { return bwta::linear_fused_supported(planned_args(M, N, K)); }
 
 int bwta_linear_launches(int M, int N, int K)
 {
@@ -579,6 +584,7 @@ int bwta_planned_kernel(int operand, int M, int N, int K)
     if (M <= 0 || N <= 0 || K <= 0) return 0;
     if (operand == BWTA_OPERAND_FP16) {
         switch (planned_linear(M, N, K)) {
+        case OneLaunch::kRows: return fused_takes(M, N, K) ? BWTA_KERNEL_LINEAR_FUSED : BWTA_KERNEL_LINEAR_STRIP;
         case OneLaunch::kShortK: return BWTA_KERNEL_LINEAR_FUSED;
         case OneLaunch::kStrip: return BWTA_KERNEL_LINEAR_STRIP;
         case OneLaunch::kOneToken: return BWTA_KERNEL_LINEAR_ONE;
@@ -591,6 +597,12 @@ int bwta_planned_kernel(int operand, int M, int N, int K)
     g.M = M, g.N = N, g.K = K;
     g.rw = (int)bwta_plane_row_words(K);
     return plan_from_planes(g, operand == 0);
+}
+
+int bwta_planned_rows(int M, int N, int K)
+{
+    if (M <= 0 || N <= 0 || K <= 0) return 0;
+    return planned_linear(M, N, K) == OneLaunch::kRows;
 }
 
 int bwta_planned_tile(int M, int N, int K)

@@ -67,6 +67,9 @@ void set_linear_fused(int mode, int r);
 // ... walking K in slabs (any K, few enough outputs for one round of workgroups)
 bool linear_strip_supported(const GemmArgs &g);
 hipError_t launch_linear_strip(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);
+// ... of a decode-sized number of tokens
+bool linear_rows_supported(const GemmArgs &g);
+hipError_t launch_linear_rows(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);
 // a tuning hook is set (bwta_set_tile) that picks kernels of the two-launch form
 bool fp4_tuning_forced();
 bool gemv_fp4_tuning_forced();

@@ -118,6 +118,24 @@ def test_planned_tile_of_the_tiled_product():
         B.set_tile(0)
 
 
+def test_planned_kernel_of_small_linears():
+    """Where bwta_linear's one launch is the kernel of 16-token strips, by workgroups of 128 channels and K: the edges."""
+    r = B.planned_rows
+    assert [r(1, 768, 768), r(2, 768, 768), r(2, 1, 8), r(2, 1, 7)] == [0, 1, 1, 0]
+    assert [r(128, 4096, 2048), r(128, 4097, 2048), r(64, 768, 2048), r(64, 768, 2049)] == [1, 0, 1, 0]          # 256, 264 workgroups
+    assert [r(128, 6144, 1280), r(128, 6145, 1280), r(128, 6144, 1281)] == [1, 0, 0]                              # 384, 392
+    assert [r(512, 2048, 1024), r(513, 2048, 1024), r(512, 2048, 1281)] == [1, 0, 0]                              # 512, 528
+    assert [r(256, 2048, K) for K in (6144, 6145)] == [1, 0] and [r(128, 2048, K) for K in (3072, 6144)] == [0, 0]
+    assert [r(129, 896, 8192), r(129, 897, 8192), r(129, 384, 12288), r(129, 385, 12288), r(129, 384, 12289)] == [1, 0, 1, 0, 0]
+    for M, N, K, kernel in ((64, 768, 768, B.KERNEL_LINEAR_FUSED), (64, 100, 768, B.KERNEL_LINEAR_STRIP), (64, 768, 1025, B.KERNEL_LINEAR_STRIP)):
+        assert r(M, N, K) == 1 and B.planned_kernel(B.OPERAND_FP16, M, N, K) == kernel and B.linear_launches(M, N, K) == 1
+    try:
+        B.set_tile(901)                                                                                             # tuning: the other kernel
+        assert r(64, 768, 768) == 0
+    finally:
+        B.set_tile(0)
+
+
 def test_planned_kernel_of_long_products():
     """Where the kernel of 16 x 16 blocks takes a product, by pairs of slabs (512 k) and tiles of 64 x 128: the edges."""
     w = B.planned_wide

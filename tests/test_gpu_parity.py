@@ -935,3 +935,40 @@ def test_tiled_product_of_16x16_blocks(M, N, K, variant):
     finally:
         B.set_path(B.PATH_AUTO)
         B.set_tile(0)
+
+
+@pytest.mark.parametrize("M,N,K", [(2, 1, 8), (16, 128, 512), (17, 129, 513), (100, 5000, 1024), (40, 77, 1025), (100, 4000, 1536), (5, 70, 1537),
+                                   (60, 2500, 2000), (130, 2200, 2048), (150, 130, 3000), (200, 1000, 2999), (300, 1500, 3072), (129, 65, 4000),
+                                   (260, 900, 4096), (400, 1200, 3500), (140, 200, 6100), (330, 700, 5000), (390, 1250, 4500), (131, 500, 8192),
+                                   (150, 300, 11003), (250, 4000, 700)])
+def test_linear_strips_of_16_tokens(M, N, K):
+    """The one-launch linear of 16-token strips: every number of chunks of 512 k and of groups that share them, one row
+    of workgroups and two, ragged tokens and channels, K that ends inside a group of 8, a word and a chunk, rows of any
+    address and pitch, ties, infinities and NaN, the three scale modes, results that overwrite the activations."""
+    _say("one-launch linear, strips of 16 tokens", M, N, K)
+    assert B.planned_rows(M, N, K) == 1
+    lda, ldo = K + 3, N + 2
+    A, s = _activation_case(1200 + K, M, K, lda)
+    inputs.poison_gap(A, K)
+    w = synth.binary_pm1(1201 + K, 2, (N, K))
+    s_w = synth.scales(1201 + K, 3, N)
+    rows = np.ascontiguousarray(A[:, :K])
+    wsign = gpu_pack_weights(w)
+    a = torch.zeros(1 + A.size, dtype=torch.float16, device="cuda:0")
+    a[1:] = dev(A).reshape(-1)
+    for sa, sw in ((s, s_w), (s[:1], s_w[:1]), (None, None)):
+        full = np.ones(M, np.float16) if sa is None else np.resize(sa, M)
+        _, _, want = oracle.linear(rows, full, w, np.ones(N, np.float16) if sw is None else np.resize(sw, N))
+        out = torch.full((1 + M * ldo,), 7.0, dtype=torch.float16, device="cuda:0")
+        B.bwta_linear(a[1:], None if sa is None else dev(sa), wsign, None if sw is None else dev(sw), out[1:], _scratch(M, N, K), M=M, N=N, K=K,
+                      lda=lda, ldo=ldo)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert same_half(np.ascontiguousarray(got[1:].reshape(M, ldo)[:, :N]), want)
+        assert got[0] == 7 and (got[1:].reshape(M, ldo)[:, N:] == 7).all()
+    _, _, want = oracle.linear(rows, s, w, s_w)
+    pitch = max(K, N)
+    both = torch.zeros((M, pitch), dtype=torch.float16, device="cuda:0")
+    both[:, :K] = dev(rows)
+    B.bwta_linear(both, dev(s), wsign, dev(s_w), both, _scratch(M, N, K), M=M, N=N, K=K, lda=pitch, ldo=pitch)
+    assert same_half(np.ascontiguousarray(both.cpu().numpy()[:, :N]), want)
