@@ -624,6 +624,164 @@ __global__ __launch_bounds__(NT) void k_prepare_weights(const uint16_t *__restri
     }
 }
 
+// The same with RB rows to a workgroup of NW wavefronts: 64 / RB lanes of a wavefront hold that many groups of 8 consecutive
+// elements of a row.  What a row costs whatever its length (two 64-bit reductions, two divisions in double, a search on
+// the binary16 grid: some 200 instructions) is then spent on RB rows at a time and its divisions by one lane per row, where
+// before every wavefront of every row went through all of it.  us replayed, before / after: 4096 x 768 5.1 / 4.4, 11008 x
+// 1000 9.5 / 8.0, 11008 x 3000 18.8 / 15.3, 64 x 3000 4.3 / 3.8, 4096 x 5000 15.3 / 12.7, 5504 x 6000 19.2 / 15.5 (4.8 TB/s).  Four
+// wavefronts: with eight 3 to 15 % slower, with one row per workgroup 20 % and more.
+template <int RB, int NW, int NG>
+__global__ __launch_bounds__(64 * NW) void k_prepare_weights_rows(const uint16_t *__restrict__ W, int64_t ldw, int N, int K, int rw,
+                                                                 uint32_t *__restrict__ wsign, uint16_t *__restrict__ s_w)
+{
+    constexpr int LPR = 64 / RB;
+    __shared__ long long s_sum[NW][RB], s_low[NW][RB], s_row[RB];
+    __shared__ int s_bad[NW][RB], s_below[NW][RB], s_finite[RB];
+    __shared__ uint32_t s_bound[RB];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane / LPR, cl = lane % LPR;
+    const int64_t n = (int64_t)RB * blockIdx.x + r;
+    const uint16_t *row = W + (n < N ? n : N - 1) * ldw;  // rows past the last: that one again, not stored
+    const int first = LPR * wave + cl;
+    constexpr int STEP = LPR * NW;
+    uint4 x[NG];
+    load_row<NG>(row, first, STEP, K, x);
+
+    uint32_t squares = 0;  // the largest sum of a group's squares, as its bits
+    SmallSum small_sum;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
+        small_sum.add(w);
+        float sq = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sq = add_squares(w[i], sq);
+        squares = max(squares, __float_as_uint(sq));
+    }
+    const bool small = __all(SmallSum::exact_below(squares));
+    const bool finite = __all(squares < 0x7f800000u);
+    long long S = small_sum.units;
+    int bad = 0;  // non-finite elements
+    if (!small) {
+        if (finite) {
+            SignedSum sum;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) sum.add(x[g].x), sum.add(x[g].y), sum.add(x[g].z), sum.add(x[g].w);
+            S = sum.units();
+        } else {  // one by one, from memory again
+            double part = 0.0;
+#pragma unroll 1
+            for (int c = first; 8 * c < K; c += STEP)
+#pragma unroll 1
+                for (int k = 8 * c; k < 8 * c + 8 && k < K; ++k) {
+                    const uint16_t h = row[k];
+                    const bool fin = (h & 0x7c00) != 0x7c00;
+                    part += (double)(fin ? half_bits_to_float(h) : 0.0f);
+                    bad += fin ? 0 : 1;
+                }
+            S = double_units(part);
+            bad = lane_group_sum<LPR>(bad);
+        }
+    }
+    S = lane_group_sum<LPR>(S);
+    if (cl == 0) s_sum[wave][r] = S, s_bad[wave][r] = bad;
+    __syncthreads();
+    if (threadIdx.x < RB) {  // one lane per row
+        long long T = 0;
+        int b = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) T += s_sum[i][threadIdx.x], b += s_bad[i][threadIdx.x];
+        // ceil(T / K): the quotient in double is off by less than one, its remainder says which way
+        long long q = (long long)floor((double)T / (double)K);
+        long long rem = T - q * K;
+        if (rem < 0) --q, rem += K;
+        if (rem >= K) ++q, rem -= K;
+        const _Float16 bound16 = (_Float16)half_grid_ceil(q + (rem > 0 ? 1 : 0));  // exact
+        uint16_t bbits;
+        __builtin_memcpy(&bbits, &bound16, 2);
+        s_bound[threadIdx.x] = bbits * 0x10001u, s_row[threadIdx.x] = T, s_finite[threadIdx.x] = K - b;
+    }
+    __syncthreads();
+    const uint32_t bound2 = s_bound[r], one2 = 0x00010001u;
+    // The second pass works on the registers again: kept opaque here, or the compiler carries what the
+    // first one derived from them across the reduction.
+#pragma unroll
+    for (int g = 0; g < NG; ++g) asm volatile("" : "+v"(x[g].x), "+v"(x[g].y), "+v"(x[g].z), "+v"(x[g].w));
+
+    int NN = 0;
+    long long SN;
+    uint32_t *dst = wsign + (n < N ? n : 0) * rw;
+    const int words = n < N ? rw : 0;
+    auto finish = [&](int c, uint32_t bits) {
+        const int left = K - 8 * c;  // elements from here to the row's end
+        if (8 * STEP * NG > K) bits &= (1u << (left >= 8 ? 8 : (left > 0 ? left : 0))) - 1u;  // +0 was loaded beyond it
+        NN += __popc(bits);
+        const uint32_t word = quad_word(bits, lane);  // whole quads stay together: rw is a multiple of 4
+        if ((lane & 3) == 0 && (c >> 2) < words) dst[c >> 2] = word;
+    };
+    // the signs of the registers' groups; low(w) gets each group's elements below the bound, the others zero
+    auto signs = [&](auto low) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            uint32_t w[4] = {x[g].x, x[g].y, x[g].z, x[g].w};
+            uint32_t V = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t d, flag, keep;
+                asm("v_pk_add_f16 %0, %1, %2 neg_lo:[0,1] neg_hi:[0,1] clamp" : "=v"(d) : "v"(bound2), "v"(w[i]));
+                asm("v_pk_min_u16 %0, %1, %2" : "=v"(flag) : "v"(d), "v"(one2));  // 1 where x < bound
+                asm("v_pk_sub_i16 %0, 0, %1" : "=v"(keep) : "v"(flag));           // 0xffff there
+                V = flag << (2 * i) | V;
+                w[i] &= keep;
+            }
+            low(w);
+            int c = first + STEP * g;
+            asm volatile("" : "+v"(c));  // its conditions are evaluated here, not carried through the kernel
+            finish(c, (V & 0x55u) | (V >> 15 & 0xaau));
+        }
+    };
+    if (small) {
+        SmallSum low;
+        signs([&](const uint32_t (&w)[4]) { low.add(w); });
+        SN = low.units;
+    } else if (finite) {
+        SignedSum low;
+        signs([&](const uint32_t (&w)[4]) { low.add(w[0]), low.add(w[1]), low.add(w[2]), low.add(w[3]); });
+        SN = low.units();
+    } else {
+        const float bound = half_bits_to_float((uint16_t)bound2);
+        double low = 0.0;
+#pragma unroll 1
+        for (int c = first; c < STEP * NG; c += STEP) {
+            uint32_t bits = 0;
+#pragma unroll 1
+            for (int i = 0; i < 8 && 8 * c + i < K; ++i) {
+                const uint16_t h = row[8 * c + i];
+                const float f = half_bits_to_float(h);
+                const bool neg = !(f >= bound);  // NaN and -Inf -> -1, +Inf -> +1
+                const bool fin_neg = neg && (h & 0x7c00) != 0x7c00;
+                bits |= (uint32_t)neg << i;
+                low += (double)(fin_neg ? f : 0.0f);
+                NN -= neg && !fin_neg ? 1 : 0;  // counted with the others
+            }
+            finish(c, bits);
+        }
+        SN = double_units(low);
+    }
+    SN = lane_group_sum<LPR>(SN);
+    NN = lane_group_sum<LPR>(NN);
+    if (cl == 0) s_low[wave][r] = SN, s_below[wave][r] = NN;
+    __syncthreads();
+    if (threadIdx.x < RB && (int64_t)RB * blockIdx.x + threadIdx.x < N) {
+        SN = 0, NN = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) SN += s_low[i][threadIdx.x], NN += s_below[i][threadIdx.x];
+        const long long T = s_row[threadIdx.x];
+        const double sum = (double)K * (double)(T - 2 * SN) - (double)T * (double)(s_finite[threadIdx.x] - 2 * NN);
+        s_w[(int64_t)RB * blockIdx.x + threadIdx.x] = double_to_half_bits(sum / ((double)K * (double)K * 16777216.0));
+    }
+}
+
 // The same scale and, from the same registers, the ternarised row: one pass over A where
 // bwta_act_scale followed by bwta_prepare_act makes two.  One workgroup of NT threads per row, for
 // the two bit planes and for fragments of rows that k_act_scale_fragments cannot hold.  FRAG: E2M1
@@ -755,6 +913,28 @@ hipError_t launch_prepare_weights(const void *W, int64_t ldw, int N, int K, uint
                            wsign, s_w);                                                                       \
         return hipGetLastError();                                                                             \
     }
+    // Rows side by side in a workgroup where the fixed part of a row counts (k_prepare_weights_rows): up to K = 2048 where
+    // they are many, to 3072, and from 4097 to 6144; in between and beyond the registers of long rows decide, and the two
+    // are level (4096 x 11008 20.8 / 20.7).
+#define BWTA_PREPR(RB_, NG_)                                                                                             \
+    if (c8 <= 64 / RB_ * 4 * NG_) {                                                                                      \
+        hipLaunchKernelGGL((k_prepare_weights_rows<RB_, 4, NG_>), dim3((N + RB_ - 1) / RB_), dim3(256), 0, st,           \
+                           (const uint16_t *)W, ldw, N, K, rw, wsign, s_w);                                              \
+        return hipGetLastError();                                                                                        \
+    }
+    if (c8 <= 256 && N >= 2560) {
+        BWTA_PREPR(4, 1) BWTA_PREPR(4, 2) BWTA_PREPR(4, 3) BWTA_PREPR(4, 4)
+    }
+    if (c8 > 256 && c8 <= 384) {
+        if (N < 2048) {
+            BWTA_PREPR(2, 3)
+        }
+        BWTA_PREPR(4, 6)
+    }
+    if (c8 > 512 && c8 <= 768 && N >= 896) {
+        BWTA_PREPR(2, 6)
+    }
+#undef BWTA_PREPR
     BWTA_PREP(1, 64) BWTA_PREP(2, 64) BWTA_PREP(4, 64) BWTA_PREP(8, 64)
     BWTA_PREP(4, 256) BWTA_PREP(6, 256) BWTA_PREP(8, 256) BWTA_PREP(16, 256)
 #undef BWTA_PREP

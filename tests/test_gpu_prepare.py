@@ -226,3 +226,23 @@ def test_one_pass_fragments_at_the_edges_of_their_row_splits(M, K):
     torch.cuda.synchronize()
     assert f1 == f2 == B.PREPARED_FP4
     assert same_half(s1.cpu().numpy(), s2.cpu().numpy()) and torch.equal(one, two)
+
+
+@pytest.mark.parametrize("N,K", [(2561, 40), (2562, 1000), (2563, 1500), (2567, 2047), (2050, 3000), (5, 2500), (1001, 3071), (901, 6001), (897, 4097)])
+def test_prepare_weights_rows_side_by_side(N, K):
+    """Weight rows that share a workgroup: row counts that do not divide by theirs, rows of odd pitch that end inside a
+    group of 8, rows of small values, of large ones, of ties around the mean, and with NaN and infinities beside finite
+    neighbours; signs and scales bit for bit."""
+    _say("prepare weights, rows side by side", N, K)
+    ldw = K + 1
+    W = (synth.gaussian(70 + K, 1, N * ldw) * 0.03 + 0.002).astype(np.float16).reshape(N, ldw)
+    W[1] *= np.float16(1000.0)
+    W[2, :K] = np.float16(0.25)
+    W[3, :4] = np.array([np.nan, np.inf, -np.inf, 65504.0], np.float16)
+    W[N - 1, K - 1] = np.nan
+    W[N - 2, :K] = 0
+    inputs.poison_gap(W, K)
+    w, s = oracle.prepare_weights(np.ascontiguousarray(W[:, :K]))
+    planes, sw = gpu_prepare(W, K)
+    assert np.array_equal(planes, oracle.pack_weights(w))
+    assert np.array_equal(sw.view(np.uint16), s.view(np.uint16))
