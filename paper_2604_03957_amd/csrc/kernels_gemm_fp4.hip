@@ -799,6 +799,12 @@ static int fp4_tile_for(const GemmArgs &g)
     // first round and more compute units take part (measured at M = 4096, N = 768, K = 3072: 192 -> 256
     // workgroups, 9.7 -> 8.3 us).
     if (tiles128 < 256 && tiles96 > tiles128 && tiles96 <= 256 && g.K >= 1024) return 13;
+    // The same for short K (products on prepared fragments and from planes; bwta_linear takes one launch there): the
+    // smaller tiles' second fetch of the operands costs nothing, so they are ahead to more tiles.  us of one ternarisation
+    // and three products, 128 x 128 / this choice: 129 x 768 x 768 19.9 / 13.8, 256 x 768 x 768 19.8 / 14.0, 1024 x 1152 x 700
+    // 20.7 / 15.9, 1500 x 2048 x 512 (192 tiles) 20.3 / 18.1, 2048 x 2048 x 256 18.8 / 17.1, 777 x 4096 x 768 22.0 / 19.7,
+    // 1500 x 4096 x 768 (384 tiles) 25.5 / 25.0; from there on 128 x 128: 2048 x 4096 x 768 27.3 / 28.6 with 64 x 128.
+    if (g.K < 1024) return tiles128 <= 192 ? 11 : tiles128 <= 384 ? 12 : 23;
     // measured: long K runs best with 2 wavefronts per SIMD (179 registers), short K with 3
     return g.K >= 2048 ? 22 : 23;
 }

@@ -118,6 +118,13 @@ def test_planned_tile_of_the_tiled_product():
         B.set_tile(0)
 
 
+def test_planned_tile_of_short_products():
+    """Below K = 1024 the tile follows the number of 128 x 128 tiles alone: 64 x 64 to 192, 64 x 128 to 384."""
+    t = B.planned_tile
+    assert [t(2048, 1536, 1023), t(2048, 1537, 768), t(2048, 3072, 100), t(2048, 3073, 768)] == [11, 12, 12, 23]
+    assert t(129, 768, 768) == 11 and t(2048, 1536, 1024) == 12
+
+
 def test_planned_kernel_of_small_linears():
     """Where bwta_linear's one launch is the kernel of 16-token strips, by workgroups of 128 channels and K: the edges."""
     r = B.planned_rows

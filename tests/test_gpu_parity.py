@@ -972,3 +972,19 @@ def test_linear_strips_of_16_tokens(M, N, K):
     both[:, :K] = dev(rows)
     B.bwta_linear(both, dev(s), wsign, dev(s_w), both, _scratch(M, N, K), M=M, N=N, K=K, lda=pitch, ldo=pitch)
     assert same_half(np.ascontiguousarray(both.cpu().numpy()[:, :N]), want)
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(129, 70, 1000, 11), (1500, 1990, 511, 11), (1500, 2055, 700, 12), (2050, 2690, 130, 12), (2050, 2900, 250, 23)])
+def test_short_products_by_tile(M, N, K, tile):
+    """Products of short K on prepared fragments, on both sides of where the tile changes, ragged on all sides."""
+    _say("short product", M, N, K, tile)
+    assert B.planned_tile(M, N, K) == tile and B.planned_wide(M, N, K) == 0
+    t, w, s_a, s_w = _gemm_case(7000 + M, M, N, K, p0=0.5)
+    want = oracle.epilogue(oracle.gemm_unpacked(t, w), s_a, s_w)
+    prep = torch.empty(B.prepared_bytes(M, K), dtype=torch.uint8, device="cuda:0")
+    fmt = B.bwta_prepare_act(dev(t.astype(np.float16)), None, prep, M=M, K=K)
+    assert fmt == B.PREPARED_FP4
+    out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda:0")
+    B.bwta_gemm_prepared(prep, gpu_pack_weights(w), dev(s_a), dev(s_w), None, out, fmt=fmt, M=M, N=N, K=K)
+    torch.cuda.synchronize()
+    assert same_half(out.cpu().numpy(), want)
