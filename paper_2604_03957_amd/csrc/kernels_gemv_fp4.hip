@@ -23,6 +23,7 @@
 //            no address clamps.  No workgroup barrier in the main loop.
 //   tokens:  the wavefront's k-range of the mask/sign planes -> E2M1 nibbles in registers, once
 //            per workgroup, reused for every tile
+//            (a workgroup may own several such runs of T tiles, reduced one after the other: see blocks_per_workgroup)
 //   reduce:  a wavefront's 16 x 16 partial of a tile is an integer of magnitude <= 512 RPW <= 2048,
 //            exactly representable in fp16: it is parked in LDS as four halfs per lane right after
 //            the tile (no accumulator registers held across tiles); after one barrier the
@@ -35,6 +36,7 @@
 // the E2M1 codes 0.5, 1, 2 and a sign; tokens carrying -4 t, -2 t, -t, +t; a per-token correction
 // starting the accumulators) cuts the expansion from 7 to 4 operations per word and is exact, but
 // the kernel is not bound by the vector ALU: no faster, and the extra registers cost occupancy.
+#include <algorithm>
 #include <atomic>
 
 #include "bwta_internal.h"
@@ -59,9 +61,10 @@ struct DecodeBatch {
 struct DecodeShape {
     int M, N, rw, a_mode, w_mode;  // M tokens in all, worked on in groups of 16
     int P;  // 16-byte pieces per packed row (rw / 4)
-    int T;  // channel tiles per workgroup (a multiple of the ring depth)
+    int T;  // channel tiles per block (a multiple of the ring depth)
     int G;  // token groups of 16 (ceil(M / 16)); NB = workgroups along the channels per group
     int64_t ldo;
+    int U;  // blocks per workgroup, reduced one by one (more than one: MULTI instances only)
 };
 
 union PartialBits {
@@ -69,7 +72,7 @@ union PartialBits {
     uint32_t u;
 };
 
-template <int RPW, int PF, int MAXW, bool NT>
+template <int RPW, int PF, int MAXW, bool NT, bool MULTI>
 __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_gemv_fp4(DecodeBatch b, DecodeShape sh)
 {
     constexpr int PW = 4 * RPW;          // pieces (16 bytes) per row in one wavefront's k-range
@@ -86,16 +89,17 @@ __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_ge
     const int tok0 = 16 * tgroup;                                     // first token of this group
     const int Mg = sh.M - tok0 < 16 ? sh.M - tok0 : 16;               // tokens in it
     const int rw = sh.rw, P = sh.P, T = sh.T;
-    const int64_t tile0 = (int64_t)tblock * T;
+    const int TT = MULTI ? T * sh.U : T;  // tiles of this workgroup
+    const int64_t tile0 = (int64_t)tblock * TT;
     if (16 * tile0 >= sh.N) return;  // the grid is padded to whole rounds of 8 tile blocks
     extern __shared__ __attribute__((aligned(16))) v4u s_lds[];
     v4u *patch = s_lds + w * (16 * PITCH);              // this wavefront's transposition patch
-    uint2 *s_part = (uint2 *)(s_lds + KW * (16 * PITCH));  // [T][KW][64 lanes] x four halfs
-    float *s_scale = (float *)(s_part + T * KW * 64);       // [16 T] channel scales, then [16] token scales
+    uint2 *s_part = (uint2 *)(s_lds + KW * (16 * PITCH));  // [T][KW][64 lanes] x four halfs; MULTI: two of them, in turn
+    float *s_scale = (float *)(s_part + (MULTI ? 2 : 1) * T * KW * 64);  // [16 TT] channel scales, then [16] token scales
 
     // The scales the epilogue needs are requested before anything else and parked in LDS, so the
-    // end of the workgroup waits on no global load.  Entry e < 16 T: channel 16 tile0 + e; then
-    // 16 tokens.  The host keeps 16 T + 16 <= 2 blockDim.
+    // end of the workgroup waits on no global load.  Entry e < 16 TT: channel 16 tile0 + e; then
+    // 16 tokens.  The host keeps 16 TT + 16 <= 2 blockDim.
     const ScaleArg sa{b.s_a[p] && sh.a_mode == 2 ? b.s_a[p] + tok0 : b.s_a[p], b.s_a[p] ? sh.a_mode : 0};
     const ScaleArg sw{b.s_w[p], b.s_w[p] ? sh.w_mode : 0};
     uint16_t my_scale[2];  // fp16 bits
@@ -104,14 +108,14 @@ __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_ge
     for (int k = 0; k < 2; ++k) {
         const int e = threadIdx.x + k * blockDim.x;
         const int64_t n = 16 * tile0 + e;
-        const bool chan = e < 16 * T;
+        const bool chan = e < 16 * TT;
         const bool use_w = chan && n < sh.N && sw.mode != 0;
-        const bool use_a = !chan && e - 16 * T < Mg && sa.mode != 0;
+        const bool use_a = !chan && e - 16 * TT < Mg && sa.mode != 0;
         // every lane loads (an entry with no scale reads the matrix's first bytes and drops them),
         // so the request is issued here and first waited for where the value is parked
         const uint16_t *src = (const uint16_t *)b.wsign[p];
         if (use_w) src = sw.ptr + (sw.mode == 1 ? 0 : n);
-        if (use_a) src = sa.ptr + (sa.mode == 1 ? 0 : e - 16 * T);
+        if (use_a) src = sa.ptr + (sa.mode == 1 ? 0 : e - 16 * TT);
         have_scale[k] = use_w || use_a;
         my_scale[k] = *src;
     }
@@ -125,7 +129,7 @@ __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_ge
     // 32 bits (checked by the host) and advance by a constant 16 rows per tile; the descriptor's
     // size is the end of this workgroup's rows, clipped to the matrix.
     const int row_first = 16 * (int)tile0;
-    const int row_end = row_first + 16 * T < sh.N ? row_first + 16 * T : sh.N;
+    const int row_end = row_first + 16 * TT < sh.N ? row_first + 16 * TT : sh.N;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)b.wsign[p], 0, (int)((uint32_t)row_end * (uint32_t)rw * 4u), 0x00020000);
     uint32_t voff[RPW], toff[RPW];
@@ -220,122 +224,198 @@ __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_ge
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int e = threadIdx.x + k * blockDim.x;
-        if (e < 16 * T + 16) s_scale[e] = have_scale[k] ? half_bits_to_float(my_scale[k]) : 1.0f;
+        if (e < 16 * TT + 16) s_scale[e] = have_scale[k] ? half_bits_to_float(my_scale[k]) : 1.0f;
     }
 
-    for (int t0 = 0; t0 < T; t0 += PF) {
+    // (a loop around a single block costs small launches 5 to 10 %: it draws the epilogue's scalar loads into the tile loop)
+    auto block = [&](const int tb) __attribute__((always_inline)) {
+        for (int t0 = 0; t0 < T; t0 += PF) {
 #pragma unroll
-        for (int f = 0; f < PF; ++f) {
+            for (int f = 0; f < PF; ++f) {
 #pragma unroll
-            for (int j = 0; j < RPW; ++j) patch[sdst[j]] = ring[f][j];
-            load_next_tile(ring[f]);  // tile t0 + f + PF; past the workgroup's last row it costs nothing
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            v4u x4[RPW];
+                for (int j = 0; j < RPW; ++j) patch[sdst[j]] = ring[f][j];
+                load_next_tile(ring[f]);  // tile t0 + f + PF; past the workgroup's last row it costs nothing
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                v4u x4[RPW];
 #pragma unroll
-            for (int r = 0; r < RPW; ++r) x4[r] = patch[i * PITCH + 4 * r + g];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            v4f a4 = v4f{0.f, 0.f, 0.f, 0.f};
+                for (int r = 0; r < RPW; ++r) x4[r] = patch[i * PITCH + 4 * r + g];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                v4f a4 = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int r = 0; r < RPW; ++r)
+                for (int r = 0; r < RPW; ++r)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t x = x4[r][e];
-                    v8i a;
-                    a[0] = (int)(((x << 3) & m88) | c22);
-                    a[1] = (int)(((x << 2) & m88) | c22);
-                    a[2] = (int)(((x << 1) & m88) | c22);
-                    a[3] = (int)((x & m88) | c22);
-                    a[4] = a[5] = a[6] = a[7] = 0;
-                    a4 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, tok[r][e], a4, 4, 4, 0, 0, 0, 0);
-                }
-            PartialBits lo, hi;
-            lo.h = __builtin_amdgcn_cvt_pkrtz(a4[0], a4[1]);  // exact: integers of magnitude <= 2048
-            hi.h = __builtin_amdgcn_cvt_pkrtz(a4[2], a4[3]);
-            s_part[((t0 + f) * KW + w) * 64 + lane] = make_uint2(lo.u, hi.u);
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t x = x4[r][e];
+                        v8i a;
+                        a[0] = (int)(((x << 3) & m88) | c22);
+                        a[1] = (int)(((x << 2) & m88) | c22);
+                        a[2] = (int)(((x << 1) & m88) | c22);
+                        a[3] = (int)((x & m88) | c22);
+                        a[4] = a[5] = a[6] = a[7] = 0;
+                        a4 = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, tok[r][e], a4, 4, 4, 0, 0, 0, 0);
+                    }
+                PartialBits lo, hi;
+                lo.h = __builtin_amdgcn_cvt_pkrtz(a4[0], a4[1]);  // exact: integers of magnitude <= 2048
+                hi.h = __builtin_amdgcn_cvt_pkrtz(a4[2], a4[3]);
+                s_part[((t0 + f) * KW + w) * 64 + lane] = make_uint2(lo.u, hi.u);
+            }
         }
-    }
 
-    // reduction over the wavefronts and epilogue.  Item x of a tile sums the KW partials of token
-    // x / 4, channels 4 (x % 4) .. + 3  (accumulator layout: lane l, register v -> channel
-    // 4 (l / 16) + v, token l % 16).
-    int32_t *accp = b.acc[p] ? b.acc[p] + (int64_t)tok0 * sh.N : nullptr;
-    uint16_t *out = b.out[p] ? b.out[p] + (int64_t)tok0 * sh.ldo : nullptr;
-    const bool vec_ok = ((sh.ldo & 3) == 0) && (((uintptr_t)out & 7) == 0);
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < T * 64; idx += blockDim.x) {
-        const int tt = idx >> 6, token = (idx & 63) >> 2, cg = idx & 3;
-        const int64_t n = 16 * (tile0 + tt) + 4 * cg;
-        if (token >= Mg || n >= sh.N) continue;
-        v4f s = v4f{0.f, 0.f, 0.f, 0.f};
-        for (int ww = 0; ww < KW; ++ww) {
-            const uint2 q = s_part[(tt * KW + ww) * 64 + cg * 16 + token];
-            PartialBits lo, hi;
-            lo.u = q.x;
-            hi.u = q.y;
-            s[0] += (float)lo.h[0];
-            s[1] += (float)lo.h[1];
-            s[2] += (float)hi.h[0];
-            s[3] += (float)hi.h[1];
-        }
-        const float fa = s_scale[16 * T + token];
-        const float *fwp = s_scale + 16 * tt + 4 * cg;
-        uint16_t *dstp = out + (int64_t)token * sh.ldo + n;
-        int32_t *accq = accp + (int64_t)token * sh.N + n;
-        if (n + 4 <= sh.N) {  // whole item inside the matrix: no per-element checks
-            if (accp) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) accq[v] = (int)s[v];
+        // reduction over the wavefronts and epilogue.  Item x of a tile sums the KW partials of token
+        // x / 4, channels 4 (x % 4) .. + 3  (accumulator layout: lane l, register v -> channel
+        // 4 (l / 16) + v, token l % 16).
+        int32_t *accp = b.acc[p] ? b.acc[p] + (int64_t)tok0 * sh.N : nullptr;
+        uint16_t *out = b.out[p] ? b.out[p] + (int64_t)tok0 * sh.ldo : nullptr;
+        const bool vec_ok = ((sh.ldo & 3) == 0) && (((uintptr_t)out & 7) == 0);
+        __syncthreads();
+        for (int idx = threadIdx.x; idx < T * 64; idx += blockDim.x) {
+            const int tt = idx >> 6, token = (idx & 63) >> 2, cg = idx & 3;
+            const int64_t n = 16 * (tile0 + tb + tt) + 4 * cg;
+            if (token >= Mg || n >= sh.N) continue;
+            v4f s = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int ww = 0; ww < KW; ++ww) {
+                const uint2 q = s_part[(tt * KW + ww) * 64 + cg * 16 + token];
+                PartialBits lo, hi;
+                lo.u = q.x;
+                hi.u = q.y;
+                s[0] += (float)lo.h[0];
+                s[1] += (float)lo.h[1];
+                s[2] += (float)hi.h[0];
+                s[3] += (float)hi.h[1];
             }
-            if (out) {
-                float fw[4];
+            const float fa = s_scale[16 * TT + token];
+            const float *fwp = s_scale + 16 * (tb + tt) + 4 * cg;
+            uint16_t *dstp = out + (int64_t)token * sh.ldo + n;
+            int32_t *accq = accp + (int64_t)token * sh.N + n;
+            if (n + 4 <= sh.N) {  // whole item inside the matrix: no per-element checks
+                if (accp) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) fw[v] = fa * fwp[v];
-                uint2 o;
-                o.x = scaled_to_half2(s[0], fw[0], s[1], fw[1]);
-                o.y = scaled_to_half2(s[2], fw[2], s[3], fw[3]);
-                if (vec_ok) {
-                    *(uint2 *)dstp = o;
-                } else {
-                    dstp[0] = (uint16_t)o.x, dstp[1] = (uint16_t)(o.x >> 16);
-                    dstp[2] = (uint16_t)o.y, dstp[3] = (uint16_t)(o.y >> 16);
+                    for (int v = 0; v < 4; ++v) accq[v] = (int)s[v];
+                }
+                if (out) {
+                    float fw[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) fw[v] = fa * fwp[v];
+                    uint2 o;
+                    o.x = scaled_to_half2(s[0], fw[0], s[1], fw[1]);
+                    o.y = scaled_to_half2(s[2], fw[2], s[3], fw[3]);
+                    if (vec_ok) {
+                        *(uint2 *)dstp = o;
+                    } else {
+                        dstp[0] = (uint16_t)o.x, dstp[1] = (uint16_t)(o.x >> 16);
+                        dstp[2] = (uint16_t)o.y, dstp[3] = (uint16_t)(o.y >> 16);
+                    }
+                }
+            } else {
+                for (int v = 0; v < 4 && n + v < sh.N; ++v) {
+                    if (accp) accq[v] = (int)s[v];
+                    if (out) dstp[v] = scaled_to_half(s[v], fa * fwp[v]);
                 }
             }
-        } else {
-            for (int v = 0; v < 4 && n + v < sh.N; ++v) {
-                if (accp) accq[v] = (int)s[v];
-                if (out) dstp[v] = scaled_to_half(s[v], fa * fwp[v]);
-            }
         }
+    };
+    if constexpr (MULTI) {
+        for (int tb = 0; tb < TT && 16 * (tile0 + tb) < sh.N; tb += T) {
+            block(tb);
+            // The next block's partials go to the other buffer.  A wavefront comes back to this one behind the next
+            // block's barrier, which no wavefront reaches before it has read its sums here.
+            s_part += tb / T & 1 ? -(T * KW * 64) : T * KW * 64;
+        }
+    } else {
+        block(0);
     }
 }
 
 std::atomic<int> g_force_rpw{0}, g_force_t{0}, g_force_pf{0};  // tuning override (relaxed: a launch sees old or new)
 
-size_t decode_lds_bytes(int RPW, int KW, int T)
+size_t decode_lds_bytes(int RPW, int KW, int T, int U)
 {
-    return (size_t)KW * 16 * (4 * RPW + 1) * 16 + (size_t)T * KW * 512 + (size_t)(16 * T + 16) * 4;
+    return (size_t)KW * 16 * (4 * RPW + 1) * 16 + (size_t)(U > 1 ? 2 : 1) * T * KW * 512 + (size_t)(16 * T * U + 16) * 4;
+}
+
+// Several blocks of tiles per workgroup, one after the other: the number of them, and *T2 = the tiles per block (T if one).
+// With K cut over 5 or more wavefronts a compute unit holds one to three workgroups, each of which starts with a round
+// trip for its token planes and ends with a reduction.  A workgroup that goes on to the next block has its tokens already
+// and its ring running through the reduction.  So a launch of more than one round of workgroups becomes one of the
+// fewest blocks that make it a single round, or (several token groups, whose planes cost more) of up to 8 blocks in more
+// than one, unless
+//  - rounding a matrix's workgroups up to the 8 XCDs grows with it (5000 channels: up to +36 %),
+//  - fewer than half of the workgroups that fit at once would be left (11 % behind at 4 x 5000 x 8192),
+//  - the compute units would not get the same number of workgroups.  A quarter may be missing where a workgroup had 2 or
+//    4 tiles (100 x 10240 x 14546: 280 workgroups 26 / 31), a tenth where it had 8 or fewer blocks do as well
+//    (2 x 4096 x 10984, count 48: 384 workgroups +13 %; 40 x 8192 x 8192, count 8: 32 tiles +11 %, 16 tiles -6 %),
+//  - one token group, blocks of 8 tiles as it is and 7 or 8 wavefronts of two or four chunks: level (0.99 to 1.03 of the
+//    time; with three, K = 9217 .. 12288, 0 to 4 % ahead),
+//  - blocks of 4 tiles do not fit the LDS: blocks of 2 from 9 wavefronts on, or for several token groups (one group,
+//    K = 16384: 3 to 17 % behind).
+// Up to 4 wavefronts (K <= 4096) the five or four workgroups of a compute unit hide each other's ends: level.
+// us, one block / this: 16 x 2048 x 11008, count 16, -28 %; 40 x 4096 x 11008, count 16, 37.8 / 32.7; 16 x 4096 x 8192, count
+// 16, 16.1 / 14.4; 40 x 4096 x 8192, count 64, 109 / 88; 16 x 4096 x 11008, count 64, 74.7 / 73.3 (4.9 TB/s); 128 x 4096 x
+// 11008 -28 %; 4 x 4096 x 20480, count 8, -24 %.  Over 417 shapes that it takes, K from 4500 to 20480: 0.83 of the time, none
+// behind by 2 %.
+int blocks_per_workgroup(const DecodeShape &sh, int count, int RPW, int KW, int T, int *T2)
+{
+    const int G = (sh.M + 15) / 16, tiles = (sh.N + 15) / 16;
+    auto workgroups = [&](int tt) { return (int64_t)(((tiles + tt - 1) / tt + 7) / 8 * 8) * count * G; };
+    auto at_once = [&](size_t lds) { return 256 * (int64_t)std::min<size_t>(16 / KW, 160 * 1024 / lds); };
+    if (KW < 5 || T < 2 || workgroups(T) <= at_once(decode_lds_bytes(RPW, KW, T, 1))) return 1;
+    if (G == 1 && T == 8 && KW >= 7 && KW <= 8 && RPW != 3) return 1;
+    const int t = decode_lds_bytes(RPW, KW, 4, 2) <= 64 * 1024 ? 4 : 2;
+    if (t == 2 && KW <= 8 && G == 1) return 1;
+    int best = 1;
+    for (int u = 2; u <= 8; u *= 2) {
+        if (t * u <= T) continue;
+        const size_t lds = decode_lds_bytes(RPW, KW, t, u);
+        if (lds > 64 * 1024 || 16 * t * u + 16 > 128 * KW) break;
+        const int64_t n = workgroups(t * u), fit = at_once(lds);
+        if (n * t * u > workgroups(T) * T || 2 * n < fit) break;
+        // percent of the compute units' workgroups that are there in the fullest round of the chip
+        const int64_t q = n <= fit ? 256 : fit, full = n < 256 ? (2 * n == fit ? 100 : 100 * n / 256) : 100 * n / ((n + q - 1) / q * q);
+        if (n <= fit) {
+            if (full >= ((T == 8 && KW >= 7) || best > 1 ? 90 : 74)) best = u;
+            break;
+        }
+        if (G > 1 && full >= 74) best = u;
+    }
+    if (best == 1) return 1;
+    *T2 = t;
+    return best;
 }
 
 template <int RPW, int PF>
 hipError_t launch_cfg(const DecodeBatch &b, int count, DecodeShape sh, hipStream_t st)
 {
     const int KW = (sh.P + 4 * RPW - 1) / (4 * RPW);
-    if (KW < 1 || KW > 16 || sh.T < PF || sh.T % PF != 0 || 16 * sh.T + 16 > 128 * KW) return hipErrorInvalidValue;
+    if (KW < 1 || KW > 16 || sh.T < PF || sh.T % PF != 0 || 16 * sh.T * sh.U + 16 > 128 * KW) return hipErrorInvalidValue;
     const int tiles = (sh.N + 15) / 16;
     sh.G = (sh.M + 15) / 16;
-    const int nb8 = ((tiles + sh.T - 1) / sh.T + 7) / 8 * 8;
+    const int nb8 = ((tiles + sh.T * sh.U - 1) / (sh.T * sh.U) + 7) / 8 * 8;
     const dim3 grid((unsigned)(nb8 * sh.G), count, 1), block(64 * KW);
-    const size_t lds = decode_lds_bytes(RPW, KW, sh.T);
+    const size_t lds = decode_lds_bytes(RPW, KW, sh.T, sh.U);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     const bool nt = (sh.rw & 31) == 0 && sh.G == 1;  // later token groups are meant to hit the L2
+    if (sh.U > 1) {
+        if constexpr (RPW >= 2 && (PF == 2 || PF == 4)) {  // what blocks_per_workgroup chooses it for
+#define BWTA_DEC_GO(MAXW_)                                                                             \
+    do {                                                                                               \
+        if (nt) hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, true, true>), grid, block, lds, st, b, sh);  \
+        else hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, false, true>), grid, block, lds, st, b, sh);    \
+    } while (0)
+            if (KW <= 8) BWTA_DEC_GO(8);
+            else BWTA_DEC_GO(16);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+#undef BWTA_DEC_GO
 #define BWTA_DEC_GO(MAXW_)                                                                      \
     do {                                                                                        \
-        if (nt) hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, true>), grid, block, lds, st, b, sh);  \
-        else hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, false>), grid, block, lds, st, b, sh);    \
+        if (nt) hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, true, false>), grid, block, lds, st, b, sh);  \
+        else hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, false, false>), grid, block, lds, st, b, sh);    \
     } while (0)
     if (KW <= 4) BWTA_DEC_GO(4);
     else if (KW <= 8) BWTA_DEC_GO(8);
@@ -367,13 +447,14 @@ hipError_t launch_shape(const DecodeBatch &b, int count, DecodeShape sh, hipStre
     const int KW = (chunks + RPW - 1) / RPW;
     T = (T + PF - 1) / PF * PF;
     // partials must fit beside the patches, and two threads' worth of scale entries cover the tiles
-    while (decode_lds_bytes(RPW, KW, T) > 64 * 1024 || 16 * T + 16 > 128 * KW) {
+    while (decode_lds_bytes(RPW, KW, T, 1) > 64 * 1024 || 16 * T + 16 > 128 * KW) {
         if (T > PF) T -= PF;
         else if (PF > 2) PF = T = 2;
         else if (PF == 2) PF = T = 1;
         else break;
     }
     sh.T = T;
+    sh.U = f_rpw ? 1 : blocks_per_workgroup(sh, count, RPW, KW, T, &sh.T);
 #define BWTA_DEC(R_, P_) if (RPW == R_ && PF == P_) return launch_cfg<R_, P_>(b, count, sh, st);
     BWTA_DEC(1, 1) BWTA_DEC(1, 2) BWTA_DEC(1, 3) BWTA_DEC(1, 4)
     BWTA_DEC(2, 1) BWTA_DEC(2, 2) BWTA_DEC(2, 3) BWTA_DEC(2, 4)
@@ -418,7 +499,7 @@ hipError_t launch_gemv_fp4_grouped(const GemmArgs *gs, int count, hipStream_t st
             if (gs[base + i].s_a.mode) a_mode = gs[base + i].s_a.mode;
             if (gs[base + i].s_w.mode) w_mode = gs[base + i].s_w.mode;
         }
-        DecodeShape sh{g0.M, g0.N, g0.rw, a_mode, w_mode, P, 0, 1, g0.ldo};
+        DecodeShape sh{g0.M, g0.N, g0.rw, a_mode, w_mode, P, 0, 1, g0.ldo, 1};
         hipError_t e = launch_shape(b, n, sh, st);
         if (e != hipSuccess) return e;
     }

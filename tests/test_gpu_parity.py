@@ -988,3 +988,36 @@ def test_short_products_by_tile(M, N, K, tile):
     B.bwta_gemm_prepared(prep, gpu_pack_weights(w), dev(s_a), dev(s_w), None, out, fmt=fmt, M=M, N=N, K=K)
     torch.cuda.synchronize()
     assert same_half(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("M,N,K,count", [
+    (16, 2041, 4500, 24),   # one round of two blocks of 4 tiles, a ragged last tile
+    (2, 4090, 5000, 32),    # four blocks of 4 tiles in place of 8 tiles
+    (3, 4096, 4500, 64),    # eight blocks
+    (40, 1000, 11000, 16),  # three groups of tokens, the last one of 8
+    (128, 4090, 11008, 1),  # one matrix, eight groups of tokens
+    (4, 2048, 20480, 8),    # ten wavefronts: two blocks of 2 tiles
+    (4, 2040, 20480, 16),   # the same, four blocks
+])
+def test_decode_of_several_blocks_per_workgroup(M, N, K, count):
+    """Launches whose workgroups go on from one block of channel tiles to the next, with and without int32 results."""
+    _say("decode blocks", M, N, K, count)
+    sides = []
+    for i in range(min(count, 2)):
+        t, w, s_a, s_w = _gemm_case(7100 + 10 * i + M, M, N, K, p0=0.5)
+        mask, sign, _ = oracle.pack_act(t)
+        acc = oracle.gemm_unpacked(t, w)
+        sides.append((dev(mask), dev(sign), gpu_pack_weights(w), dev(s_a), dev(s_w), acc, oracle.epilogue(acc, s_a, s_w)))
+    probs, got = [], []
+    for i in range(count):
+        dm, dsg, dw, dsa, dsw, _, _ = sides[i % len(sides)]
+        acc = torch.full((M, N), -9, dtype=torch.int32, device="cuda:0") if i % 3 == 0 else None
+        out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda:0")
+        got.append((acc, out))
+        probs.append((dm, dsg, dw, dsa, dsw, acc, out))
+    ws = torch.empty(max(B.workspace_bytes(M, N, K), 256) * count, dtype=torch.uint8, device="cuda:0")
+    B.bwta_gemm_grouped(B.make_problems(probs), ws, M=M, N=N, K=K)
+    torch.cuda.synchronize()
+    for i, (acc, out) in enumerate(got):
+        assert acc is None or np.array_equal(acc.cpu().numpy(), sides[i % len(sides)][5])
+        assert same_half(out.cpu().numpy(), sides[i % len(sides)][6])
