@@ -132,7 +132,14 @@ __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_ge
     const int row_end = row_first + 16 * TT < sh.N ? row_first + 16 * TT : sh.N;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)b.wsign[p], 0, (int)((uint32_t)row_end * (uint32_t)rw * 4u), 0x00020000);
-    uint32_t voff[RPW], toff[RPW];
+    // Four chunks per wavefront and several blocks: 128 registers hold that without scratch only if one offset per lane
+    // says where all its pieces are, which lie 4 rows apart.  With an offset each, two registers went to scratch, and
+    // a reload waits for the whole ring of requests (us, scratch / none: 28 x 8058 x 15744, 41 problems, 200.6 / 181.6;
+    // 33 x 5671 x 14990, 33, 159.7 / 145.4; over 53 shapes of K 12289 .. 20480 0.966 of the time).
+    constexpr bool ONE_OFFSET = MULTI && RPW == 4;
+    static_assert(!ONE_OFFSET || 64 % PW == 0, "a lane's pieces lie whole rows apart");
+    const uint32_t piece_step = (uint32_t)(64 / PW) * (uint32_t)rw * 4u;
+    uint32_t voff[ONE_OFFSET ? 1 : RPW], toff[RPW];
     int sdst[RPW];
 #pragma unroll
     for (int j = 0; j < RPW; ++j) {
@@ -141,7 +148,7 @@ __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_ge
         const int cc = c < P ? c : 0;
         sdst[j] = srow * PITCH + pc;
         toff[j] = ((uint32_t)srow * (uint32_t)rw + 4u * cc) * 4u;
-        voff[j] = toff[j] + (uint32_t)row_first * (uint32_t)rw * 4u;
+        if (!ONE_OFFSET || j == 0) voff[ONE_OFFSET ? 0 : j] = toff[j] + (uint32_t)row_first * (uint32_t)rw * 4u;
     }
 
     // The token planes of this group are fetched like one more tile (rows = tokens, so a request
@@ -168,9 +175,11 @@ __global__ __launch_bounds__(64 * MAXW, MAXW == 4 && RPW <= 2 ? 5 : 4) void k_ge
     auto load_next_tile = [&](v4u(&dst)[RPW]) {  // tiles are requested in order
 #pragma unroll
         for (int j = 0; j < RPW; ++j) {
-            dst[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)voff[j], 0, NT ? 2 : 0);
-            voff[j] += tile_bytes;
+            const uint32_t off = ONE_OFFSET ? voff[0] + (uint32_t)j * piece_step : voff[j];
+            dst[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, NT ? 2 : 0);
+            if constexpr (!ONE_OFFSET) voff[j] += tile_bytes;
         }
+        if constexpr (ONE_OFFSET) voff[0] += tile_bytes;
     };
     v4u ring[PF][RPW];
 #pragma unroll

@@ -23,3 +23,22 @@ def test_the_popcount_decode_kernels_use_no_scratch():
     assert len(names) == len(scratch) > 100
     assert any("k_gemv_popc" in n for n in names) and any("k_linear_one" in n for n in names)
     assert [(n, b) for n, b in zip(names, scratch) if b] == []
+
+
+def _scratch_of(source):
+    """{mangled kernel name: bytes of scratch per lane} as the compiler reports them."""
+    cmd = [HIPCC] + build.HIPCC_FLAGS + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+                                         os.path.join(build.CSRC, source), "-o", os.devnull]
+    report = subprocess.run(cmd, stderr=subprocess.PIPE, text=True, check=True).stderr
+    names = re.findall(r"Function Name: (\S+)", report)
+    scratch = [int(b) for b in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", report)]
+    assert names and len(names) == len(scratch)
+    return dict(zip(names, scratch))
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_the_matrix_core_decode_kernels_use_no_scratch():
+    """The ring of weight requests runs on behind everything a workgroup does; an access to scratch would wait for it."""
+    scratch = _scratch_of("kernels_gemv_fp4.hip")
+    assert any("k_gemv_fp4" in n for n in scratch)
+    assert {n: b for n, b in scratch.items() if b} == {}
