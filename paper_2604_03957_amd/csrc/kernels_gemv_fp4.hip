@@ -414,9 +414,14 @@ hipError_t launch_cfg(const DecodeBatch &b, int count, DecodeShape sh, hipStream
         if (nt) hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, true, true>), grid, block, lds, st, b, sh);  \
         else hipLaunchKernelGGL((k_gemv_fp4<RPW, PF, MAXW_, false, true>), grid, block, lds, st, b, sh);    \
     } while (0)
-            if (KW <= 8) BWTA_DEC_GO(8);
-            else BWTA_DEC_GO(16);
-            return hipGetLastError();
+            if (KW <= 8) {
+                BWTA_DEC_GO(8);
+                return hipGetLastError();
+            }
+            if constexpr (RPW == 4) {  // launch_shape keeps fewer chunks to 8 wavefronts
+                BWTA_DEC_GO(16);
+                return hipGetLastError();
+            }
         }
         return hipErrorInvalidValue;
     }
@@ -437,10 +442,9 @@ hipError_t launch_shape(const DecodeBatch &b, int count, DecodeShape sh, hipStre
 {
     const int chunks = (sh.P + 3) / 4;
     const int tiles = (sh.N + 15) / 16;
-    // chunks per wavefront: the smallest of 2..4 that needs at most 8 wavefronts, else at most 16
+    // chunks per wavefront: the smallest of 2..4 that needs at most 8 wavefronts, else 4 (9 to 12 wavefronts)
     int RPW = 2;
     while (RPW < 4 && (chunks + RPW - 1) / RPW > 8) ++RPW;
-    if ((chunks + RPW - 1) / RPW > 8 && (chunks + 1) / 2 <= 16) RPW = 2;
     // tiles per workgroup: as many as still leave about 1024 workgroups in the launch
     const int64_t work = (int64_t)tiles * count * ((sh.M + 15) / 16);
     // (a single small matrix: one tile per workgroup, so that every compute unit gets one)

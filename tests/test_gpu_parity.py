@@ -998,6 +998,11 @@ def test_short_products_by_tile(M, N, K, tile):
     (128, 4090, 11008, 1),  # one matrix, eight groups of tokens
     (4, 2048, 20480, 8),    # ten wavefronts: two blocks of 2 tiles
     (4, 2040, 20480, 16),   # the same, four blocks
+    (2, 828, 6044, 32),     # two chunks per wavefront, rows of whole 128-byte lines
+    (2, 775, 9160, 32),     # three
+    (2, 771, 12381, 32), (2, 794, 13247, 32),  # four, eight wavefronts, rows that are not and that are whole lines
+    (17, 773, 14644, 49),   # the same, two groups of tokens, four blocks of 2 tiles
+    (2, 507, 16699, 32),    # four, nine wavefronts, rows that are not whole lines
 ])
 def test_decode_of_several_blocks_per_workgroup(M, N, K, count):
     """Launches whose workgroups go on from one block of channel tiles to the next, with and without int32 results."""

@@ -42,3 +42,6 @@ def test_the_matrix_core_decode_kernels_use_no_scratch():
     scratch = _scratch_of("kernels_gemv_fp4.hip")
     assert any("k_gemv_fp4" in n for n in scratch)
     assert {n: b for n, b in scratch.items() if b} == {}
+    # several blocks per workgroup: the instances the launcher can choose (more than 8 wavefronts only with four chunks each)
+    several = {tuple(map(int, m.groups())) for m in (re.search(r"k_gemv_fp4ILi(\d+)ELi(\d+)ELi(\d+)ELb[01]ELb1EE", n) for n in scratch) if m}
+    assert several == {(2, 2, 8), (2, 4, 8), (3, 2, 8), (4, 2, 8), (4, 2, 16)}
