@@ -18,7 +18,7 @@
 //     waits, through which the values pass: a read that the compiler sees makes it wait for every direct load.
 //   * A block of 16 channels is widened (7 vector-ALU operations) between the four MFMAs on the block before it.
 //     In one wavefront an MFMA and what follows it still take 23 clocks instead of 16; two wavefronts per SIMD fill
-//     each other's gaps (0.95 of the matrix rate).  They fit by registers (234 to 240 of 256).
+//     each other's gaps (0.95 of the matrix rate).  They fit by registers (236, KS = 2 246, of 256).
 //   * KS groups of wavefronts in a workgroup take every KS-th pair of slabs, so that a compute unit has eight
 //     wavefronts also where it gets one tile of 64 x KS.. outputs and not two; in the end every group keeps 64 / KS
 //     tokens and hands the others' sums over through LDS, in fp32 (whole numbers, exact in any order).  Which
@@ -214,7 +214,9 @@ void k_gemm_fp4_wide(GemmArgs g, const uint32_t *__restrict__ frag, int s_pad, i
                 read_w(wv[(c + 1) & 1], it, c + 1);
             } else if (!LAST) {
                 // this pair's words have all been read (waited for in the step before); the next pair's own requests
-                // are older than the 12 fragment loads of this pair's steps
+                // are older than the 12 fragment loads of this pair's steps.  The count holds while nothing else of this
+                // wavefront reaches memory here: a spilled register's store or reload would be counted too and the
+                // words read too early, so the kernel must not use scratch (the tests look at the compiler's report)
                 asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 read_w(wv[0], it + 1, 0);

@@ -45,3 +45,12 @@ def test_the_matrix_core_decode_kernels_use_no_scratch():
     # several blocks per workgroup: the instances the launcher can choose (more than 8 wavefronts only with four chunks each)
     several = {tuple(map(int, m.groups())) for m in (re.search(r"k_gemv_fp4ILi(\d+)ELi(\d+)ELi(\d+)ELb[01]ELb1EE", n) for n in scratch) if m}
     assert several == {(2, 2, 8), (2, 4, 8), (3, 2, 8), (4, 2, 8), (4, 2, 16)}
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+@pytest.mark.parametrize("source,kernel,instances", [("kernels_gemm_fp4_wide.hip", "k_gemm_fp4_wide", 3), ("kernels_gemm_fp4_lds.hip", "k_gemm_fp4_lds", 6)])
+def test_kernels_that_count_their_loads_use_no_scratch(source, kernel, instances):
+    """These wait for a direct load into LDS by the number of younger memory operations of the wavefront; an access to
+    scratch among them would be counted, and the wait end before the data is there."""
+    scratch = {n: b for n, b in _scratch_of(source).items() if kernel in n}
+    assert len(scratch) == instances and set(scratch.values()) == {0}
