@@ -291,8 +291,9 @@ def run_c2(args, torch, B, synth):
         finally:
             B.set_tile(0)
         k["two_kernel_form_us"] = round(t2 * 1e3, 2)
-        name = {B.KERNEL_LINEAR_FUSED: "k_linear_fused", B.KERNEL_LINEAR_STRIP: "k_linear_strip"}.get(
-            B.planned_kernel(B.OPERAND_FP16, L.M, L.N, L.K), "k_gemm_fp4")
+        name = {B.KERNEL_LINEAR_FUSED: "k_linear_fused", B.KERNEL_LINEAR_STRIP: "k_linear_strip",
+                B.KERNEL_LINEAR_ROWS: "k_linear_rows", B.KERNEL_LINEAR_ONE: "k_linear_one"}.get(
+                    B.planned_kernel(B.OPERAND_FP16, L.M, L.N, L.K), "k_gemm_fp4")
         names.append(name)
         if launches == 1:
             k["kernel"] = name + (" (ternarise + FP4 MFMA product + scale epilogue); ternarize_us and gemm_us are the "

@@ -50,12 +50,12 @@ enum {
     BWTA_KERNEL_GEMM_POPC = 5,    /* tiled, wave64 popcount (planes)    */
     BWTA_KERNEL_LINEAR_FUSED = 6, /* whole linear, all of a short K     */
     BWTA_KERNEL_LINEAR_STRIP = 7, /* whole linear, K in slabs           */
-    BWTA_KERNEL_LINEAR_ONE = 8    /* whole linear, one token            */
+    BWTA_KERNEL_LINEAR_ONE = 8,   /* whole linear, one token            */
+    BWTA_KERNEL_LINEAR_ROWS = 9   /* whole linear, strips of 16 tokens, all of K at once: few tokens, narrow matrices */
 };
 enum { BWTA_OPERAND_FP16 = 3 };
 int bwta_planned_kernel(int operand, int M, int N, int K);
-/* 1 where bwta_linear's one launch is the kernel for few tokens and narrow matrices (strips of 16 tokens, all of K at
- * once), which bwta_planned_kernel counts under BWTA_KERNEL_LINEAR_FUSED (short K) or _STRIP (beyond); else 0. */
+/* 1 where bwta_planned_kernel answers BWTA_KERNEL_LINEAR_ROWS for BWTA_OPERAND_FP16, else 0. */
 int bwta_planned_rows(int M, int N, int K);
 /* How many kernels bwta_linear launches for a shape under the current settings, given results that do
  * not overlap the activations (a call that works in place always takes two): 1 where ternarisation,

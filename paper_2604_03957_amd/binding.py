@@ -29,7 +29,7 @@ SCALE_NONE, SCALE_SCALAR, SCALE_VECTOR = 0, 1, 2
 PATH_AUTO, PATH_POPC, PATH_MFMA, PATH_FP4 = 0, 1, 2, 3
 PREPARED_PLANES, PREPARED_FP4 = 1, 2
 KERNEL_GEMV_POPC, KERNEL_GEMV_FP4, KERNEL_GEMM_FP4, KERNEL_GEMM_MFMA_I8, KERNEL_GEMM_POPC = 1, 2, 3, 4, 5
-KERNEL_LINEAR_FUSED, KERNEL_LINEAR_STRIP, KERNEL_LINEAR_ONE = 6, 7, 8
+KERNEL_LINEAR_FUSED, KERNEL_LINEAR_STRIP, KERNEL_LINEAR_ONE, KERNEL_LINEAR_ROWS = 6, 7, 8, 9
 OPERAND_FP16 = 3
 
 EXPORTS = ["bwta_plane_row_words", "bwta_workspace_bytes", "bwta_quantize_pack_act",

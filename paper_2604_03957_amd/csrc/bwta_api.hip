@@ -562,16 +562,13 @@ int bwta_auto_path(int M, int N, int K)
     return M > 1 ? BWTA_PATH_FP4 : BWTA_PATH_POPC;
 }
 
-static uint16_t plan_sink;  // stands for the results of a call that is only planned
-
-static bwta::GemmArgs planned_args(int M, int N, int K)
+static OneLaunch planned_linear(int M, int N, int K)
 {
-    return {nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
-            {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &plan_sink, N};
+    uint16_t sink = 0;
+    bwta::GemmArgs g{nullptr, nullptr, nullptr, M, N, K, (int)bwta_plane_row_words(K),
+                     {nullptr, BWTA_SCALE_NONE}, {nullptr, BWTA_SCALE_NONE}, nullptr, &sink, N};
+    return one_launch_linear(g);
 }
-
-static OneLaunch planned_linear(int M, int N, int K) { return one_launch_linear(planned_args(M, N, K)); }
-static bool fused_takes(int M, int N, int K) { return bwta::linear_fused_supported(planned_args(M, N, K)); }
 
 int bwta_linear_launches(int M, int N, int K)
 {
@@ -584,7 +581,7 @@ int bwta_planned_kernel(int operand, int M, int N, int K)
     if (M <= 0 || N <= 0 || K <= 0) return 0;
     if (operand == BWTA_OPERAND_FP16) {
         switch (planned_linear(M, N, K)) {
-        case OneLaunch::kRows: return fused_takes(M, N, K) ? BWTA_KERNEL_LINEAR_FUSED : BWTA_KERNEL_LINEAR_STRIP;
+        case OneLaunch::kRows: return BWTA_KERNEL_LINEAR_ROWS;
         case OneLaunch::kShortK: return BWTA_KERNEL_LINEAR_FUSED;
         case OneLaunch::kStrip: return BWTA_KERNEL_LINEAR_STRIP;
         case OneLaunch::kOneToken: return BWTA_KERNEL_LINEAR_ONE;

@@ -64,20 +64,24 @@ def test_path_selection():
 
 
 def test_planned_kernel_of_the_linear():
-    """Which kernel bwta_linear takes on fp16 rows: the three one-launch kernels each where its rule says, the product
+    """Which kernel bwta_linear takes on fp16 rows: the four one-launch kernels each where its rule says, the product
     kernel behind a ternarise launch elsewhere; the launch count follows."""
     def plan(M, N, K):
         k = B.planned_kernel(B.OPERAND_FP16, M, N, K)
-        one = k in (B.KERNEL_LINEAR_FUSED, B.KERNEL_LINEAR_STRIP, B.KERNEL_LINEAR_ONE)
+        one = k in (B.KERNEL_LINEAR_FUSED, B.KERNEL_LINEAR_STRIP, B.KERNEL_LINEAR_ONE, B.KERNEL_LINEAR_ROWS)
+        assert B.planned_rows(M, N, K) == (k == B.KERNEL_LINEAR_ROWS), (M, N, K)
         assert B.linear_launches(M, N, K) == (1 if one else 2), (M, N, K)
         return k
 
-    assert plan(4096, 3072, 768) == plan(2, 128, 8) == plan(300, 515, 515) == B.KERNEL_LINEAR_FUSED
-    assert plan(4096, 768, 3072) == plan(64, 1536, 2048) == plan(300, 100, 768) == B.KERNEL_LINEAR_STRIP
-    # the slab kernel's bounds: K at decode-sized token counts, very long K on wide matrices
-    for (M, N), last in (((64, 768), 2048), ((2, 28000), 2048), ((64, 4096), 2560), ((64, 8193), 3072), ((128, 8192), 3072), ((777, 2500), 16384),
-                         ((777, 1152), 32768), ((2048, 1536), 8192), ((4096, 768), 32768), ((256, 4096), 32768)):
-        assert plan(M, N, last) == B.KERNEL_LINEAR_STRIP, (M, N, last)
+    assert plan(4096, 3072, 768) == plan(2, 49153, 8) == plan(520, 2049, 515) == B.KERNEL_LINEAR_FUSED
+    assert plan(4096, 768, 3072) == plan(65, 8193, 2048) == plan(4200, 100, 1300) == B.KERNEL_LINEAR_STRIP
+    for shape in ((2, 128, 8), (300, 515, 515), (64, 1536, 2048), (300, 100, 768)):
+        assert plan(*shape) == B.KERNEL_LINEAR_ROWS, shape
+    # bounds in K: of the strips of 16 tokens and of the slab kernel at decode-sized token counts, of the latter on wide matrices
+    for (M, N), last in (((64, 768), 2048), ((2, 28000), 2048), ((2, 40000), 2048), ((64, 4096), 2560), ((64, 8193), 3072), ((128, 8192), 3072),
+                         ((777, 2500), 16384), ((777, 1152), 32768), ((2048, 1536), 8192), ((4096, 768), 32768), ((256, 4096), 32768)):
+        few = (M, N) in ((64, 768), (2, 28000))
+        assert plan(M, N, last) == (B.KERNEL_LINEAR_ROWS if few else B.KERNEL_LINEAR_STRIP), (M, N, last)
         assert last == 32768 or plan(M, N, last + 1) in (B.KERNEL_GEMV_FP4, B.KERNEL_GEMM_FP4), (M, N, last)
     assert plan(512, 4096, 4096) == plan(1024, 3072, 4096) == B.KERNEL_GEMM_FP4
     assert plan(1, 11008, 4096) == plan(1, 1, 8) == plan(1, 128, 16384) == B.KERNEL_LINEAR_ONE
@@ -134,11 +138,11 @@ def test_planned_kernel_of_small_linears():
     assert [r(512, 2048, 1024), r(513, 2048, 1024), r(512, 2048, 1281)] == [1, 0, 0]                              # 512, 528
     assert [r(256, 2048, K) for K in (6144, 6145)] == [1, 0] and [r(128, 2048, K) for K in (3072, 6144)] == [0, 0]
     assert [r(129, 896, 8192), r(129, 897, 8192), r(129, 384, 12288), r(129, 385, 12288), r(129, 384, 12289)] == [1, 0, 1, 0, 0]
-    for M, N, K, kernel in ((64, 768, 768, B.KERNEL_LINEAR_FUSED), (64, 100, 768, B.KERNEL_LINEAR_STRIP), (64, 768, 1025, B.KERNEL_LINEAR_STRIP)):
-        assert r(M, N, K) == 1 and B.planned_kernel(B.OPERAND_FP16, M, N, K) == kernel and B.linear_launches(M, N, K) == 1
+    for M, N, K in ((64, 768, 768), (64, 100, 768), (64, 768, 1025)):
+        assert r(M, N, K) == 1 and B.planned_kernel(B.OPERAND_FP16, M, N, K) == B.KERNEL_LINEAR_ROWS and B.linear_launches(M, N, K) == 1
     try:
         B.set_tile(901)                                                                                             # tuning: the other kernel
-        assert r(64, 768, 768) == 0
+        assert r(64, 768, 768) == 0 and B.planned_kernel(B.OPERAND_FP16, 64, 768, 768) == B.KERNEL_LINEAR_FUSED
     finally:
         B.set_tile(0)
 

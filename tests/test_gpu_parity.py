@@ -510,16 +510,21 @@ def test_linear_one_token_tall_matrices(passes, K):
 @pytest.mark.parametrize("M,N,K", [(2, 1, 1025), (31, 129, 1536), (128, 250, 3072), (97, 8191, 1031), (129, 128, 1537),
                                    (300, 500, 2047), (250, 4096, 1025), (200, 70, 11003), (513, 1900, 1100),
                                    (777, 1500, 2560), (2050, 383, 1800), (2048, 1536, 1030), (2300, 1100, 2049),
-                                   (33, 5000, 900), (128, 5200, 3072), (65, 10100, 2999), (70, 4000, 2500), (520, 1100, 16390)])
+                                   (33, 5000, 900), (128, 5200, 3072), (65, 10100, 2999), (70, 4000, 2500), (520, 1100, 16390),
+                                   (2, 33001, 1537), (31, 17000, 1536), (4111, 100, 1537), (300, 1900, 2047), (250, 4096, 1290),
+                                   (200, 70, 13003), (513, 1900, 1301), (33, 17000, 900)])
 @pytest.mark.parametrize("scales", ["vector", "scalar", "none"])
 def test_linear_slabs_one_launch(M, N, K, scales):
     """The one-launch linear that walks K in slabs of 512: one, two and three channel blocks per wavefront, tokens
     and channels around the tile edges, two slabs and more, odd and even counts, K that ends on a slab, inside a
     word and inside a group of 8, rows of any address and pitch, ties, infinities and NaN, an invalid scale, scales
-    below 2^-13 with an odd last bit and above 8192, and results that overwrite the activations."""
+    below 2^-13 with an odd last bit and above 8192, and results that overwrite the activations.  The same of its
+    neighbours: strips of 16 tokens where tokens or channels are few, the decode kernel where outputs are few for that K."""
     _say("one-launch linear, slabs", M, N, K, scales)
-    if (M, N, K) != (128, 250, 3072):  # few outputs at that K: the decode kernel's
-        assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == B.KERNEL_LINEAR_STRIP
+    strips16 = ((2, 1, 1025), (31, 129, 1536), (129, 128, 1537), (300, 500, 2047), (250, 4096, 1025), (200, 70, 11003), (513, 1900, 1100),
+                (33, 5000, 900))
+    kernel = B.KERNEL_LINEAR_ROWS if (M, N, K) in strips16 else B.KERNEL_GEMV_FP4 if (M, N, K) == (128, 250, 3072) else B.KERNEL_LINEAR_STRIP
+    assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == kernel
     lda = K + M % 3
     A, s = _activation_case(60 + M + K, M, K, lda)
     A, s = A[:, :K].copy(), s.copy()
@@ -559,13 +564,17 @@ def test_linear_slabs_one_launch(M, N, K, scales):
     (200, 400, 768, 768, 300),                            # results start inside the activations' rows ..
     (200, 700, 700, 704, -704 * 3),                       # .. three rows above them
     (500, 300, 515, 900, 520), (500, 256, 512, 768, 512),  # side by side in rows of one pitch: no element shared
-    (500, 300, 515, 815, -300)])
+    (500, 300, 515, 815, -300),
+    # the same with outputs enough for strips of 32 tokens
+    (1100, 1000, 515, 1000, 0), (1100, 1024, 768, 1024, 0), (33, 17100, 9, 17101, 0), (2100, 400, 768, 768, 300),
+    (1500, 700, 700, 704, -704 * 3), (3000, 300, 515, 900, 520), (4200, 256, 512, 768, 512), (3000, 300, 515, 815, -300)])
 def test_linear_results_share_memory_with_the_activations(M, N, K, pitch, start):
     """Short K, where every workgroup of a strip of tokens reads the strip's whole rows: results written over the
     activations, over part of them, and between their rows.  The elements are the oracle's on the original
     activations, and what belongs to neither stays."""
     _say("linear, results in the activations' rows", M, N, K, pitch, start)
-    assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == B.KERNEL_LINEAR_FUSED
+    few = (M + 15) // 16 * ((N + 127) // 128) <= 256  # without the overlap: strips of 16 tokens, or of 32
+    assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == (B.KERNEL_LINEAR_ROWS if few else B.KERNEL_LINEAR_FUSED)
     A, s = _activation_case(970 + M + K, M, K)
     w = synth.binary_pm1(40, M + N + K, (N, K))
     s_w = synth.scales(40, 11, N)
@@ -617,6 +626,21 @@ def test_linear_one_launch_seeded_random_shapes():
         assert B.linear_launches(M, N, K) == 1
         out = gpu_linear(A, s, gpu_pack_weights(w), s_w, N)
         assert same_half(out, want), (case, M, N, K)
+
+
+def test_linear_one_launch_of_32_token_strips_seeded_random_shapes():
+    """20 seeded random shapes (M 1500..4000, N 1000..3000, K 8..1023) with outputs enough for the one-launch linear of
+    32-token strips."""
+    rng = np.random.default_rng(20260406)
+    for case in range(20):
+        M, N, K = int(rng.integers(1500, 4001)), int(rng.integers(1000, 3001)), int(rng.integers(8, 1024))
+        _say("one-launch linear, 32-token strips, random shape", case, M, N, K)
+        A, s = _activation_case(2100 + case, M, K)
+        w = synth.binary_pm1(38, case, (N, K))
+        s_w = synth.scales(38, 100 + case, N)
+        _, _, want = oracle.linear(A, s, w, s_w)
+        assert B.planned_kernel(B.OPERAND_FP16, M, N, K) == B.KERNEL_LINEAR_FUSED
+        assert same_half(gpu_linear(A, s, gpu_pack_weights(w), s_w, N), want), (case, M, N, K)
 
 
 def test_every_entry_and_family_seeded_random_shapes():
