@@ -820,9 +820,11 @@ static int fp4_tile_for(const GemmArgs &g)
 //   257 to 512 of them: over 4 where the pairs come out even (K = 4096: 0.90 to 0.95, 8192: 0.85 to 0.92), else over 2 (K =
 //   5000: 0.95, 6500: 0.96), from six pairs (K = 2816: 0.96 to 1.01, 3072: 0.95 to 1.0); except where tiles of 64 x 128
 //   of the other kernel just fill two rounds (1300 x 3001 x 3072 15.3 / 17.4).
-//   513 to 1536: over 2, from six pairs on (K = 2816: 0.96 to 0.98, 4096: 0.91 to 0.95, 11008: 0.85 to 0.94), not with
-//   seven, where one group idles for an eighth of the time (K = 3500: 0.98 to 1.03).
-//   More: whole tiles of 128 x 256, from eight pairs on (K = 4096: 0.95 to 0.97; 2048 x 11008 x 4096 46.5 / 44.6); with six
+//   Beyond, up to 768 tiles of 128 x 128 (three per compute unit): over 2, from six pairs on (K = 2816: 0.96 to 0.98, 4096:
+//   0.91 to 0.95, 11008: 0.85 to 0.94), not with seven, where one group idles for an eighth of the time (K = 3500: 0.98 to
+//   1.03).
+//   More (counted in tiles of 128 x 128: a last row of tiles that is half empty costs as much as a full one; 652 x 16768 x
+//   5504, 786 of them, 38.6 / over 2 41.4 / 37.1): whole tiles of 128 x 256, from eight pairs on (K = 4096: 0.95 to 0.97; 2048 x 11008 x 4096 46.5 / 44.6); with six
 //   level (0.96 to 1.05), below behind.
 static int fp4_wide_for(const GemmArgs &g)
 {
@@ -831,7 +833,7 @@ static int fp4_wide_for(const GemmArgs &g)
     const int pairs = fp4_s_pad(g.rw) / 8;
     if (tiles64 <= 256) return pairs >= 7 ? 611 : 0;
     if (tiles64 <= 512 && pairs >= 7 && (pairs % 4 == 0 || pairs % 4 == 3)) return 611;
-    if (tiles64 <= 1536) {
+    if (tiles128 <= 768) {
         const bool spills = tiles128 > 256 && tiles64 <= 512 && pairs <= 6;  // 12 below
         return pairs >= 6 && pairs != 7 && !spills ? 521 : 0;
     }

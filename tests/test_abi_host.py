@@ -155,6 +155,7 @@ def test_planned_kernel_of_long_products():
     assert w(1300, 3001, 3000) == 0 and w(777, 3001, 2999) == 521                           # 64 x 128 tiles just fill two rounds
     assert [w(2048, 4096, K) for K in (2560, 3072, 3500, 4096, 11008)] == [0, 521, 0, 521, 521]
     assert w(3072, 4096, 4096) == 521 and [w(2048, 11008, K) for K in (3584, 3585, 4096)] == [0, 422, 422]
+    assert [w(652, 16384, 5504), w(652, 16385, 5504), w(652, 16385, 3000)] == [521, 422, 0]  # 768, 774 tiles of 128 x 128, half a row of them empty
     assert w(2048, (1 << 32) // (344 * 4) + 1, 11008) == 0 and w(0, 8, 8) == 0              # beyond 32-bit offsets
     one = [B.planned_kernel(B.OPERAND_FP16, *s) == B.KERNEL_LINEAR_STRIP for s in
            ((256, 4096, 5120), (256, 4096, 5121), (641, 768, 7168), (640, 768, 7168), (641, 768, 7169), (1280, 512, 12288), (1280, 513, 12288),
