@@ -77,10 +77,11 @@ int bwta_linear_launches(int M, int N, int K);
  * strip); 0 restores the built-in choices.  Results do not depend on it. */
 int bwta_set_tile(int tile);
 /* How a product (BWTA_KERNEL_GEMM_FP4) of fp16 results alone runs under the current settings: bwta_planned_wide says
- * which tile of the kernel of 16 x 16 blocks (422, 521, 611) takes the shape, 0 if none does; then bwta_planned_tile says
- * which of the other tiles.  0 for a non-positive dimension.  A product with int32 results runs on 128 x 128 tiles (22)
+ * which tile of the kernel of 16 x 16 blocks (422, 521, 611) takes the shape in bwta_gemm and bwta_linear, and
+ * bwta_planned_wide_prepared in bwta_gemm_prepared; 0 if none does; then bwta_planned_tile says which of the other tiles.  0 for a non-positive dimension.  A product with int32 results runs on 128 x 128 tiles (22)
  * whatever these answer, except that a tile of the LDS kernel (223, 243, 323) forced by bwta_set_tile takes it too. */
 int bwta_planned_wide(int M, int N, int K);
+int bwta_planned_wide_prepared(int M, int N, int K);
 int bwta_planned_tile(int M, int N, int K);
 #ifdef __cplusplus
 }

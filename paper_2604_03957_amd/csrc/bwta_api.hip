@@ -124,7 +124,7 @@ int run_gemm(const bwta::GemmArgs &g, void *workspace, hipStream_t st)
     case BWTA_KERNEL_GEMV_FP4: return hip_result(bwta::launch_gemv_fp4(g, st));
     case BWTA_KERNEL_GEMM_FP4: {
         uint32_t *frag = (uint32_t *)((char *)workspace + 2 * plane_bytes(g.M, g.K));
-        return hip_result(bwta::launch_gemm_fp4(g, frag, false, st));
+        return hip_result(bwta::launch_gemm_fp4(g, frag, bwta::Frag::kFromPlanes, st));
     }
     case BWTA_KERNEL_GEMM_MFMA_I8: return hip_result(bwta::launch_gemm_mfma(g, st));
     case BWTA_KERNEL_GEMV_POPC: return hip_result(bwta::launch_gemv_popc(g, st));
@@ -218,6 +218,35 @@ int bwta_gemm(const uint32_t *mask, const uint32_t *sign, const uint32_t *wsign,
     return run_gemm(g, workspace, (hipStream_t)stream);
 }
 
+static int gemm_prepared(const void *prepared, size_t prepared_bytes, int prepared_format, bwta::Frag from, const uint32_t *wsign,
+                         int M, int N, int K, const void *s_a, int a_scale_mode, const void *s_w, int w_scale_mode,
+                         int32_t *acc, void *out, int64_t ldo, bwta_stream_t stream)
+{
+    int rc = check_gemm_common(M, N, K, s_a, a_scale_mode, s_w, w_scale_mode, out, ldo);
+    if (rc != BWTA_OK) return rc;
+    if (prepared_format != BWTA_PREPARED_PLANES && prepared_format != BWTA_PREPARED_FP4) return BWTA_ERR_UNSUPPORTED;
+    if (M == 0 || N == 0) return BWTA_OK;
+    if (!wsign) return BWTA_ERR_NULL;
+    if (!acc && !out) return BWTA_ERR_NULL;
+    if (!aligned(wsign, 16) || (acc && !aligned(acc, 4))) return BWTA_ERR_ALIGN;
+    if (!prepared || prepared_bytes < bwta_prepared_bytes(M, K)) return BWTA_ERR_WORKSPACE;
+    if (!aligned(prepared, 256)) return BWTA_ERR_ALIGN;
+    hipStream_t st = (hipStream_t)stream;
+    const uint32_t *mask = (const uint32_t *)prepared;
+    const uint32_t *sign = (const uint32_t *)((const char *)prepared + plane_bytes(M, K));
+    bwta::GemmArgs g{mask, sign, wsign, M, N, K, (int)bwta_plane_row_words(K),
+                     {(const uint16_t *)s_a, s_a ? a_scale_mode : BWTA_SCALE_NONE},
+                     {(const uint16_t *)s_w, s_w ? w_scale_mode : BWTA_SCALE_NONE},
+                     acc, (uint16_t *)out, ldo};
+    // The operand's format, not the current path setting, says which kernels can read it: fragments go
+    // to the tiled FP4 kernel; planes go to a kernel that reads planes and needs no scratch.
+    if (prepared_format == BWTA_PREPARED_FP4) {
+        uint32_t *frag = (uint32_t *)((char *)prepared + 2 * plane_bytes(M, K));
+        return hip_result(bwta::launch_gemm_fp4(g, frag, from, st));
+    }
+    return run_gemm(g, nullptr, st);
+}
+
 int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, const uint32_t *wsign,
                 const void *s_w, int w_scale_mode, int M, int N, int K, void *out, int64_t ldo,
                 void *workspace, size_t workspace_bytes, bwta_stream_t stream)
@@ -244,8 +273,8 @@ int bwta_linear(const void *A, int64_t lda, const void *s_a, int a_scale_mode, c
     int format = 0;
     rc = bwta_prepare_act(A, lda, s_a, a_scale_mode, M, K, workspace, workspace_bytes, &format, stream);
     if (rc != BWTA_OK) return rc;
-    return bwta_gemm_prepared(workspace, workspace_bytes, format, wsign, M, N, K, s_a, a_scale_mode, s_w,
-                              w_scale_mode, nullptr, out, ldo, stream);
+    return gemm_prepared(workspace, workspace_bytes, format, bwta::Frag::kJustWritten, wsign, M, N, K, s_a, a_scale_mode, s_w,
+                         w_scale_mode, nullptr, out, ldo, stream);
 }
 
 int bwta_linear_call(const void *call)
@@ -354,29 +383,8 @@ int bwta_gemm_prepared(const void *prepared, size_t prepared_bytes, int prepared
                        int M, int N, int K, const void *s_a, int a_scale_mode, const void *s_w, int w_scale_mode,
                        int32_t *acc, void *out, int64_t ldo, bwta_stream_t stream)
 {
-    int rc = check_gemm_common(M, N, K, s_a, a_scale_mode, s_w, w_scale_mode, out, ldo);
-    if (rc != BWTA_OK) return rc;
-    if (prepared_format != BWTA_PREPARED_PLANES && prepared_format != BWTA_PREPARED_FP4) return BWTA_ERR_UNSUPPORTED;
-    if (M == 0 || N == 0) return BWTA_OK;
-    if (!wsign) return BWTA_ERR_NULL;
-    if (!acc && !out) return BWTA_ERR_NULL;
-    if (!aligned(wsign, 16) || (acc && !aligned(acc, 4))) return BWTA_ERR_ALIGN;
-    if (!prepared || prepared_bytes < bwta_prepared_bytes(M, K)) return BWTA_ERR_WORKSPACE;
-    if (!aligned(prepared, 256)) return BWTA_ERR_ALIGN;
-    hipStream_t st = (hipStream_t)stream;
-    const uint32_t *mask = (const uint32_t *)prepared;
-    const uint32_t *sign = (const uint32_t *)((const char *)prepared + plane_bytes(M, K));
-    bwta::GemmArgs g{mask, sign, wsign, M, N, K, (int)bwta_plane_row_words(K),
-                     {(const uint16_t *)s_a, s_a ? a_scale_mode : BWTA_SCALE_NONE},
-                     {(const uint16_t *)s_w, s_w ? w_scale_mode : BWTA_SCALE_NONE},
-                     acc, (uint16_t *)out, ldo};
-    // The operand's format, not the current path setting, says which kernels can read it: fragments go
-    // to the tiled FP4 kernel; planes go to a kernel that reads planes and needs no scratch.
-    if (prepared_format == BWTA_PREPARED_FP4) {
-        uint32_t *frag = (uint32_t *)((char *)prepared + 2 * plane_bytes(M, K));
-        return hip_result(bwta::launch_gemm_fp4(g, frag, true, st));
-    }
-    return run_gemm(g, nullptr, st);
+    return gemm_prepared(prepared, prepared_bytes, prepared_format, bwta::Frag::kPrepared, wsign, M, N, K, s_a, a_scale_mode, s_w,
+                         w_scale_mode, acc, out, ldo, stream);
 }
 
 int bwta_gemm_grouped(const bwta_gemm_problem *problems, int count, int M, int N, int K, int a_scale_mode,
@@ -611,7 +619,13 @@ int bwta_planned_tile(int M, int N, int K)
 int bwta_planned_wide(int M, int N, int K)
 {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    return bwta::fp4_planned_wide(M, N, K);
+    return bwta::fp4_planned_wide(M, N, K, false);
+}
+
+int bwta_planned_wide_prepared(int M, int N, int K)
+{
+    if (M <= 0 || N <= 0 || K <= 0) return 0;
+    return bwta::fp4_planned_wide(M, N, K, true);
 }
 
 int bwta_version(void) { return 2; }

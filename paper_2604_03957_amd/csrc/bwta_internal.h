@@ -59,7 +59,7 @@ hipError_t launch_gemm_mfma(const GemmArgs &g, hipStream_t st);
 size_t gemm_fp4_frag_bytes(int M, int K);
 void set_fp4_tile(int t);
 int fp4_planned_tile(int M, int N, int K);
-int fp4_planned_wide(int M, int N, int K);
+int fp4_planned_wide(int M, int N, int K, bool prepared);
 // the whole linear in one launch (short K, fp16 in, fp16 out)
 bool linear_fused_supported(const GemmArgs &g);
 hipError_t launch_linear_fused(const void *A, int64_t lda, const GemmArgs &g, hipStream_t st);
@@ -80,7 +80,10 @@ hipError_t launch_linear_one(const void *A, const GemmArgs &g, hipStream_t st);
 hipError_t launch_att_v_fp4(const GemmArgs &g, const uint32_t *frag, int batch, int64_t w_stride_words,
                             int64_t out_stride, float alpha, hipStream_t st);
 void set_gemv_tile(int g, int nch);
-hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, hipStream_t st);
+// where a product's fragments come from: made from planes by this launch, written just before it and for it alone
+// (bwta_linear), or an operand the caller prepared, which several products read as a rule
+enum class Frag { kFromPlanes, kJustWritten, kPrepared };
+hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, Frag from, hipStream_t st);
 bool gemm_fp4_lds_supported(const GemmArgs &g);
 hipError_t launch_gemm_fp4_lds(const GemmArgs &g, const uint32_t *frag, int variant, hipStream_t st);
 hipError_t launch_gemm_fp4_wide(const GemmArgs &g, const uint32_t *frag, int variant, hipStream_t st);

@@ -826,11 +826,25 @@ static int fp4_tile_for(const GemmArgs &g)
 //   More (counted in tiles of 128 x 128: a last row of tiles that is half empty costs as much as a full one; 652 x 16768 x
 //   5504, 786 of them, 38.6 / over 2 41.4 / 37.1): whole tiles of 128 x 256, from eight pairs on (K = 4096: 0.95 to 0.97; 2048 x 11008 x 4096 46.5 / 44.6); with six
 //   level (0.96 to 1.05), below behind.
-static int fp4_wide_for(const GemmArgs &g)
+// Those are times of products on fragments just written.  On an operand that several products read (prepared) the others
+// gain more from finding it in the L2, and a pair of slabs that not every group gets counts for more:
+//   Up to 128 tiles of 64 x 128, seven or nine pairs of which the last is at most half full: left to the others (one
+//   ternarisation and three products, the others / this one: 305 x 65 x 3075 23.3 / 24.9, 492 x 1447 x 3326 25.0 / 26.3,
+//   309 x 89 x 4287 27.8 / 28.9; with one product this one is 0.3 to 0.9 ahead).
+//   257 to 512, while tiles of 128 x 96 make one round: seven pairs are left to them (312 x 6988 x 3105 34.7 / 38.1, 568 x
+//   4009 x 3325 35.9 / 37.0), eight over 2 (1397 x 1536 x 3631, those / over 4 / over 2 37.0 / 39.7 / 37.0; of 50 shapes over 4 0.98
+//   and over 2 0.96 of their time).
+static int fp4_wide_for(const GemmArgs &g, bool prepared)
 {
     if (!gemm_fp4_lds_supported(g)) return 0;
     const int64_t tn = ((int64_t)g.N + 127) / 128, tiles64 = ((int64_t)g.M + 63) / 64 * tn, tiles128 = ((int64_t)g.M + 127) / 128 * tn;
     const int pairs = fp4_s_pad(g.rw) / 8;
+    if (prepared) {
+        const bool half_pair = (8 * pairs - g.rw / 2) >= 4;
+        if (tiles64 <= 128 && (pairs == 7 || pairs == 9) && half_pair) return 0;
+        const int64_t tiles96 = ((int64_t)g.M + 127) / 128 * (((int64_t)g.N + 95) / 96);
+        if (tiles64 > 256 && tiles64 <= 512 && tiles128 > 128 && tiles96 <= 256 && (pairs == 7 || pairs == 8)) return pairs == 7 ? 0 : 521;
+    }
     if (tiles64 <= 256) return pairs >= 7 ? 611 : 0;
     if (tiles64 <= 512 && pairs >= 7 && (pairs % 4 == 0 || pairs % 4 == 3)) return 611;
     if (tiles128 <= 768) {
@@ -841,21 +855,21 @@ static int fp4_wide_for(const GemmArgs &g)
 }
 
 // the kernel of 16 x 16 blocks: forced (tuning sweeps), or by the rule unless one of the other tiles is forced
-static int fp4_wide(const GemmArgs &g)
+static int fp4_wide(const GemmArgs &g, bool prepared)
 {
     const int forced = g_fp4_tile.load(std::memory_order_relaxed);
     switch (forced) {
     case 422: case 521: case 611: return gemm_fp4_lds_supported(g) ? forced : 0;
     case 11: case 12: case 13: case 21: case 22: case 23: case 222: case 223: case 243: case 323: return 0;
-    default: return fp4_wide_for(g);
+    default: return fp4_wide_for(g, prepared);
     }
 }
 
-int fp4_planned_wide(int M, int N, int K)
+int fp4_planned_wide(int M, int N, int K, bool prepared)
 {
     GemmArgs g{};
     g.M = M, g.N = N, g.K = K, g.rw = (int)(4 * (((int64_t)K + 127) / 128));
-    return fp4_wide(g);
+    return fp4_wide(g, prepared);
 }
 
 // the forced tile (tuning sweeps) where the shape can take it, else the rule's
@@ -879,11 +893,10 @@ int fp4_planned_tile(int M, int N, int K)
     return fp4_tile(g);
 }
 
-// frag_ready: the fragments were already produced by launch_quantize_to_fp4 (planes unused)
-hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, hipStream_t st)
+hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, Frag from, hipStream_t st)
 {
     const int rb_pad = fp4_rb_pad(g.M), s_pad = fp4_s_pad(g.rw);
-    if (!frag_ready) {
+    if (from == Frag::kFromPlanes) {  // else the planes are unused
         const int64_t wgs32 = (int64_t)((s_pad + 15) / 16) * rb_pad;  // workgroups at 32 words each
         if (wgs32 >= 1024)
             hipLaunchKernelGGL(k_planes_to_fp4<32>, dim3((s_pad + 15) / 16, rb_pad), dim3(256), 0, st, g.mask, g.sign, g.M,
@@ -897,7 +910,7 @@ hipError_t launch_gemm_fp4(const GemmArgs &g, uint32_t *frag, bool frag_ready, h
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const int wide = g.acc ? 0 : fp4_wide(g);  // int32 output: test / debug path
+    const int wide = g.acc ? 0 : fp4_wide(g, from == Frag::kPrepared);  // int32 output: test / debug path
     if (wide) return launch_gemm_fp4_wide(g, frag, wide, st);
     const int tile = fp4_tile(g);
     const bool lds = tile == 223 || tile == 243 || tile == 323;

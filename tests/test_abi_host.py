@@ -157,6 +157,16 @@ def test_planned_kernel_of_long_products():
     assert w(3072, 4096, 4096) == 521 and [w(2048, 11008, K) for K in (3584, 3585, 4096)] == [0, 422, 422]
     assert [w(652, 16384, 5504), w(652, 16385, 5504), w(652, 16385, 3000)] == [521, 422, 0]  # 768, 774 tiles of 128 x 128, half a row of them empty
     assert w(2048, (1 << 32) // (344 * 4) + 1, 11008) == 0 and w(0, 8, 8) == 0              # beyond 32-bit offsets
+    # on an operand that was prepared by its own call: seven and nine pairs, the last one half full, are left to the
+    # other tiles where these are few, and seven or eight where 128 x 96 tiles make one round
+    p = lambda *s: w(*s, prepared=True)
+    assert [(w(512, 2048, K), p(512, 2048, K)) for K in (3072, 3073, 3328, 3329, 4096, 4097, 4352, 4353, 5121)] == \
+        [(0, 0), (611, 0), (611, 0), (611, 611), (611, 611), (611, 0), (611, 0), (611, 611), (611, 611)]
+    assert p(512, 2049, 3073) == p(512, 2049, 4097) == 611                                   # 136 tiles
+    assert [(w(513, 4096, K), p(513, 4096, K)) for K in (3073, 3584, 3585, 4096, 4097, 5633)] == \
+        [(611, 0), (611, 0), (611, 521), (611, 521), (521, 521), (611, 611)]
+    assert p(513, 4896, 3073) == 0 and p(513, 4897, 3073) == 611                             # 255, 260 tiles of 128 x 96
+    assert all(w(M, N, K) == p(M, N, K) for M, N, K in ((512, 4096, 3073), (300, 11007, 3073), (2048, 4096, 4096), (2048, 11008, 4096)))
     one = [B.planned_kernel(B.OPERAND_FP16, *s) == B.KERNEL_LINEAR_STRIP for s in
            ((256, 4096, 5120), (256, 4096, 5121), (641, 768, 7168), (640, 768, 7168), (641, 768, 7169), (1280, 512, 12288), (1280, 513, 12288),
             (1300, 1536, 4096), (1024, 2048, 4096), (2048, 768, 7168), (2048, 768, 7169), (4096, 512, 11008), (4096, 768, 11008),

@@ -1014,6 +1014,28 @@ def test_short_products_by_tile(M, N, K, tile):
     assert same_half(out.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("M,N,K,fresh,kept", [(300, 515, 3100, 611, 0), (140, 700, 4200, 611, 0), (513, 1990, 3329, 611, 611), (1030, 2050, 3300, 611, 0),
+                                             (1397, 1536, 3631, 611, 521)])
+def test_products_of_an_operand_that_is_kept(M, N, K, fresh, kept):
+    """Where a product on an operand prepared by its own call takes another tile than bwta_gemm on the same planes: both
+    against the oracle."""
+    _say("kept operand", M, N, K, fresh, kept)
+    assert (B.planned_wide(M, N, K), B.planned_wide(M, N, K, prepared=True)) == (fresh, kept)
+    t, w, s_a, s_w = _gemm_case(7050 + M, M, N, K, p0=0.5)
+    want = oracle.epilogue(oracle.gemm_unpacked(t, w), s_a, s_w)
+    prep = torch.empty(B.prepared_bytes(M, K), dtype=torch.uint8, device="cuda:0")
+    wsign = gpu_pack_weights(w)
+    fmt = B.bwta_prepare_act(dev(t.astype(np.float16)), None, prep, M=M, K=K)
+    for _ in range(2):
+        out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda:0")
+        B.bwta_gemm_prepared(prep, wsign, dev(s_a), dev(s_w), None, out, fmt=fmt, M=M, N=N, K=K)
+        torch.cuda.synchronize()
+        assert same_half(out.cpu().numpy(), want)
+    mask, sign, _ = oracle.pack_act(t)
+    _, out = gpu_gemm(mask, sign, wsign, s_a, s_w, M, N, K, want_acc=False, want_out=True)
+    assert same_half(out, want)
+
+
 @pytest.mark.parametrize("M,N,K,count", [
     (16, 2041, 4500, 24),   # one round of two blocks of 4 tiles, a ragged last tile
     (2, 4090, 5000, 32),    # four blocks of 4 tiles in place of 8 tiles
