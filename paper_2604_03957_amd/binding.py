@@ -12,6 +12,8 @@ import importlib.machinery
 import importlib.util
 import os
 import struct
+import sys
+import warnings
 
 # torch ships its own HIP runtime; load it first so that libbwta.so binds to the same runtime
 # (same SONAME) instead of bringing a second one into the process.
@@ -397,6 +399,10 @@ def bwta_gemm_grouped(problem_array, workspace, *, M, N, K, a_scale_mode=SCALE_V
                                   _ptr(workspace), _nbytes(workspace, workspace_bytes), _stream(stream)))
 
 
+def _native_identity():
+    return "%s %s %d.%d" % ((build_id(), torch.__version__) + sys.version_info[:2])
+
+
 def _load_native():
     loader = importlib.machinery.ExtensionFileLoader("_bwta_native", NATIVE_PATH)
     module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_bwta_native", NATIVE_PATH, loader=loader))
@@ -405,7 +411,13 @@ def _load_native():
     return module
 
 
-# From here on each of these names is the native function, with the Python form above as what it falls back to.
+# From here on each of these names is the native function, with the Python form above as what it falls back to.  An
+# extension of other sources than the library's (its arguments may be others), or for another torch, is not called.
 _native = _load_native()
-for _name in _native.parameters():
-    globals()[_name] = _native.bind(_name, _c.cast(getattr(_lib, _name), _P).value, globals()[_name])
+_built = _native.identity() if hasattr(_native, "identity") else "unknown"
+if _built == _native_identity():
+    for _name in _native.parameters():
+        globals()[_name] = _native.bind(_name, _c.cast(getattr(_lib, _name), _P).value, globals()[_name])
+else:
+    warnings.warn("%s is of build %r, the library and this interpreter are %r: the calls are marshalled in Python; build again"
+                  % (NATIVE_PATH, _built, _native_identity()), RuntimeWarning)

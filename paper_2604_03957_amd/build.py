@@ -27,22 +27,33 @@ HIPCC_FLAGS = [
 
 BINDING_SRC = os.path.join(CSRC, "binding_native.cpp")
 BINDING = os.path.join(CSRC, "_bwta_native.so")
+BINDING_ID = os.path.join(OBJ, "binding_identity.txt")  # of the extension that is there, for the incremental build
 
 
-def build_binding(verbose=True):
-    """The host-only extension that marshals the per-layer calls (binding_native.cpp), against this torch and Python."""
+def _binding_identity(bid):
+    """What the extension must have been built for: these sources, this torch, this Python."""
+    import torch
+    return "%s %s %d.%d" % ((bid, torch.__version__) + sys.version_info[:2])
+
+
+def build_binding(bid, verbose=True):
+    """The host-only extension that marshals the per-layer calls (binding_native.cpp), against this torch and Python.  It
+    holds the C signatures of include/bwta.h and says what it was built from and for, which the binding compares with the
+    library before it uses it."""
     import sysconfig
     import torch
     root = os.path.dirname(torch.__file__)
     tmp = BINDING + ".tmp%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I" + sysconfig.get_paths()["include"],
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DBWTA_IDENTITY="%s"' % _binding_identity(bid), "-I" + sysconfig.get_paths()["include"],
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            BINDING_SRC, "-o", tmp, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, BINDING)
+    with open(BINDING_ID, "w") as f:
+        f.write(_binding_identity(bid))
     return BINDING
 
 
@@ -55,9 +66,9 @@ def _headers():
 
 
 def build_id():
-    """Digest of every source and header the library is built from (and of the compiler flags)."""
+    """Digest of every source and header the library and its binding are built from (and of the compiler flags)."""
     h = hashlib.sha1(" ".join(HIPCC_FLAGS).encode())
-    for f in sorted(sources() + _headers(), key=os.path.basename):
+    for f in sorted(sources() + _headers() + [BINDING_SRC], key=os.path.basename):
         h.update(os.path.basename(f).encode())
         h.update(open(f, "rb").read())
     return h.hexdigest()[:12]
@@ -86,9 +97,9 @@ def build_library(verbose=True, extra_flags=(), incremental=False, jobs=8):
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)
 
-    stale = not (incremental and os.path.exists(BINDING) and os.path.getmtime(BINDING) > max(os.path.getmtime(BINDING_SRC), newest_header))
+    stale = not (incremental and os.path.exists(BINDING) and os.path.exists(BINDING_ID) and open(BINDING_ID).read() == _binding_identity(bid))
     with concurrent.futures.ThreadPoolExecutor(max_workers=max(1, min(jobs, len(todo) + 1))) as pool:
-        binding = pool.submit(build_binding, verbose) if stale else None
+        binding = pool.submit(build_binding, bid, verbose) if stale else None
         list(pool.map(compile_one, todo))
         if binding:
             binding.result()

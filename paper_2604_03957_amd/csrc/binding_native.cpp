@@ -430,7 +430,13 @@ PyObject *parameters(PyObject *, PyObject *)  // {name: (positional parameters, 
     return out;
 }
 
-PyMethodDef kMethods[] = {{"bind", bind, METH_VARARGS, "bind(name, address, fallback) -> function"},
+#ifndef BWTA_IDENTITY
+#define BWTA_IDENTITY "unknown"
+#endif
+PyObject *identity(PyObject *, PyObject *) { return PyUnicode_FromString(BWTA_IDENTITY); }
+
+PyMethodDef kMethods[] = {{"identity", identity, METH_NOARGS, "identity() -> \"<digest of the sources> <torch version> <Python version>\""},
+                          {"bind", bind, METH_VARARGS, "bind(name, address, fallback) -> function"},
                           {"setup", setup, METH_VARARGS, "setup(check, raw_stream, device)"},
                           {"parameters", parameters, METH_NOARGS, "{name: (positional parameters, all parameters)}"},
                           {nullptr, nullptr, 0, nullptr}};
@@ -440,6 +446,13 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_bwta_native", "Marshalling of th
 
 PyMODINIT_FUNC PyInit__bwta_native(void)
 {
+#define BWTA_STR2(x) #x
+#define BWTA_STR(x) BWTA_STR2(x)
+    constexpr char built_for[] = BWTA_STR(PY_MAJOR_VERSION) "." BWTA_STR(PY_MINOR_VERSION) ".";
+    if (strncmp(Py_GetVersion(), built_for, sizeof built_for - 1) != 0) {
+        PyErr_SetString(PyExc_ImportError, "built for another version of Python");
+        return nullptr;
+    }
     BoundType.tp_name = "_bwta_native.function";
     BoundType.tp_basicsize = sizeof(Bound);
     BoundType.tp_dealloc = bound_dealloc;

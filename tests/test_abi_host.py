@@ -284,6 +284,64 @@ def test_native_marshalling_knows_the_python_forms():
         B._native.bind("bwta_nothing", 0, print)
 
 
+def _package_copy(tmp_path):
+    """The package's Python files and built libraries in a folder of their own: what a child interpreter imports."""
+    import shutil
+    src = os.path.dirname(os.path.abspath(B.__file__))
+    dst = tmp_path / os.path.basename(src)
+    (dst / "csrc").mkdir(parents=True)
+    for f in ("__init__.py", "binding.py"):
+        shutil.copy(os.path.join(src, f), str(dst / f))
+    for f in (B.LIB_PATH, B.NATIVE_PATH):
+        shutil.copy(f, str(dst / "csrc" / os.path.basename(f)))
+    return dst
+
+
+_CHILD = """
+import types, warnings
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from paper_2604_03957_amd import binding as B
+says = [str(w.message) for w in seen if issubclass(w.category, RuntimeWarning) and "marshalled in Python" in str(w.message)]
+python = [type(getattr(B, n)) is types.FunctionType for n in ("bwta_linear", "bwta_gemm", "bwta_matmul_bool_prepared")]
+try:
+    B.bwta_linear(None, None, 0x1000, None, 0x1000, None, M=1, N=1, K=128, stream=0)
+    code = 0
+except B.BwtaError as e:
+    code = e.code
+print("RESULT", len(says), all(python), any(python), code)
+"""
+
+
+def _child_import(folder):
+    import subprocess
+    import sys
+    env = {k: v for k, v in os.environ.items() if k != "BWTA_LIB"}
+    r = subprocess.run([sys.executable, "-c", _CHILD], cwd=str(folder), env=dict(env, PYTHONPATH=str(folder)), stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True, timeout=300)
+    lines = [l for l in r.stdout.splitlines() if l.startswith("RESULT")]
+    assert r.returncode == 0 and len(lines) == 1, r.stdout[-2000:]
+    return lines[0]
+
+
+def test_native_marshalling_of_another_build_is_not_called(tmp_path):
+    """The extension holds the C signatures it was compiled with.  One of other sources than the library's, or for another
+    torch, is left alone, with a warning: the Python forms make the calls."""
+    if os.environ.get("BWTA_LIB"):
+        pytest.skip("a library built some other way is loaded")
+    pkg = _package_copy(tmp_path)
+    native = pkg / "csrc" / os.path.basename(B.NATIVE_PATH)
+    assert _child_import(tmp_path) == "RESULT 0 False False %d" % B.ERR_NULL
+    good, mine = native.read_bytes(), B._native.identity().encode()
+    assert good.count(mine) == 1 and B._native.identity() == B._native_identity()
+    for other in (b"0" * 12 + mine[12:], mine[:13] + b"1" * (len(mine) - 13)):
+        native.write_bytes(good.replace(mine, other))
+        assert _child_import(tmp_path) == "RESULT 1 True True %d" % B.ERR_NULL
+    assert good.count(b"\0identity\0") == 1  # one that does not say what it was built from
+    native.write_bytes(good.replace(b"\0identity\0", b"\0identitx\0"))
+    assert _child_import(tmp_path) == "RESULT 1 True True %d" % B.ERR_NULL
+
+
 def test_prepare_and_gemm_prepared_reject_bad_arguments():
     pb = B.prepared_bytes(8, 128)
     assert pb % 256 == 0 and pb > 0 and B.prepared_bytes(0, 128) == 0
