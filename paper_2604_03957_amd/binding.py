@@ -5,7 +5,8 @@ torch CUDA tensors used as device buffers; the current torch stream is passed th
 The calls a program makes per layer are marshalled by ``csrc/binding_native.cpp`` where they come in
 their ordinary form (device tensors, Python integers, the current stream); the functions below say
 what every other form does.
-Importing this module without the compiled library raises -- there is no fallback.
+Importing this module without the compiled library raises -- there is no fallback.  Without the native marshalling it
+warns and makes every call in its Python form.
 """
 import ctypes
 import importlib.machinery
@@ -43,11 +44,10 @@ EXPORTS = ["bwta_plane_row_words", "bwta_workspace_bytes", "bwta_quantize_pack_a
            "bwta_quantize_pack_bool", "bwta_matmul_tt", "bwta_prepare_weights", "bwta_act_scale",
            "bwta_prepare_act_autoscale", "bwta_matmul_bool_prepared"]
 
-for _path in (LIB_PATH, NATIVE_PATH):
-    if not os.path.exists(_path):
-        raise ImportError(
-            "%s is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
-            "or python paper_2604_03957_amd/build.py); there is no CPU fallback" % _path)
+if not os.path.exists(LIB_PATH):
+    raise ImportError(
+        "%s is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
+        "or python paper_2604_03957_amd/build.py); there is no CPU fallback" % LIB_PATH)
 
 _lib = ctypes.CDLL(LIB_PATH)
 _c = ctypes
@@ -404,17 +404,20 @@ def _native_identity():
 
 
 def _load_native():
-    loader = importlib.machinery.ExtensionFileLoader("_bwta_native", NATIVE_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_bwta_native", NATIVE_PATH, loader=loader))
-    loader.exec_module(module)
+    """(the extension or None, what it was built from and for)"""
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_bwta_native", NATIVE_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_bwta_native", NATIVE_PATH, loader=loader))
+        loader.exec_module(module)
+    except ImportError as e:  # no such file, or one for another Python or torch
+        return None, str(e)
     module.setup(_check, _raw_stream, _cur_device)
-    return module
+    return module, module.identity() if hasattr(module, "identity") else "unknown"
 
 
 # From here on each of these names is the native function, with the Python form above as what it falls back to.  An
 # extension of other sources than the library's (its arguments may be others), or for another torch, is not called.
-_native = _load_native()
-_built = _native.identity() if hasattr(_native, "identity") else "unknown"
+_native, _built = _load_native()
 if _built == _native_identity():
     for _name in _native.parameters():
         globals()[_name] = _native.bind(_name, _c.cast(getattr(_lib, _name), _P).value, globals()[_name])

@@ -9,8 +9,10 @@ import concurrent.futures
 import glob
 import hashlib
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -36,17 +38,40 @@ def _binding_identity(bid):
     return "%s %s %d.%d" % ((bid, torch.__version__) + sys.version_info[:2])
 
 
+def _binding_compiler():
+    """The host compiler for the extension: $CXX, else g++, else the clang++ that comes with hipcc; None if there is none."""
+    if os.environ.get("CXX"):
+        return os.environ["CXX"]
+    return shutil.which("g++") or shutil.which("clang++", path="/opt/rocm/llvm/bin")
+
+
+def _binding_headers():
+    """The header folders of this Python and this torch, or None where their headers are not installed."""
+    import torch
+    py, tc = sysconfig.get_paths()["include"], os.path.join(os.path.dirname(torch.__file__), "include")
+    there = os.path.exists(os.path.join(py, "Python.h")) and os.path.exists(os.path.join(tc, "torch", "csrc", "autograd", "python_variable.h"))
+    return (py, tc) if there else None
+
+
 def build_binding(bid, verbose=True):
     """The host-only extension that marshals the per-layer calls (binding_native.cpp), against this torch and Python.  It
     holds the C signatures of include/bwta.h and says what it was built from and for, which the binding compares with the
-    library before it uses it."""
-    import sysconfig
+    library before it uses it.  Returns None where there is nothing to build it with: the binding's Python forms make the
+    calls then, some 1 us slower each."""
+    compiler, headers = _binding_compiler(), _binding_headers()
+    if compiler is None or headers is None:
+        print("_bwta_native.so is not built: %s; the calls are marshalled in Python"
+              % ("no C++ compiler" if compiler is None else "no headers of Python or torch"), flush=True)
+        for left in (BINDING, BINDING_ID):
+            if os.path.exists(left):
+                os.remove(left)
+        return None
     import torch
     root = os.path.dirname(torch.__file__)
     tmp = BINDING + ".tmp%d" % os.getpid()
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DBWTA_IDENTITY="%s"' % _binding_identity(bid), "-I" + sysconfig.get_paths()["include"],
-           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+    cmd = [compiler, "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DBWTA_IDENTITY="%s"' % _binding_identity(bid), "-I" + headers[0],
+           "-isystem", headers[1], "-isystem", os.path.join(headers[1], "torch", "csrc", "api", "include"),
            BINDING_SRC, "-o", tmp, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -342,6 +342,35 @@ def test_native_marshalling_of_another_build_is_not_called(tmp_path):
     assert _child_import(tmp_path) == "RESULT 1 True True %d" % B.ERR_NULL
 
 
+def test_import_without_the_native_marshalling(tmp_path):
+    """No extension, or one that does not load: the package imports, warns and makes every call in its Python form.  (The
+    library itself has no such substitute.)"""
+    if os.environ.get("BWTA_LIB"):
+        pytest.skip("a library built some other way is loaded")
+    pkg = _package_copy(tmp_path)
+    native = pkg / "csrc" / os.path.basename(B.NATIVE_PATH)
+    native.write_bytes(b"no shared object")
+    assert _child_import(tmp_path) == "RESULT 1 True True %d" % B.ERR_NULL
+    native.unlink()
+    assert _child_import(tmp_path) == "RESULT 1 True True %d" % B.ERR_NULL
+
+
+def test_build_without_what_the_native_marshalling_needs(tmp_path, monkeypatch, capsys):
+    """No C++ compiler, or no headers of Python or torch: said, an older extension is taken away, and the build goes on."""
+    from paper_2604_03957_amd import build
+    for what in ("_binding_compiler", "_binding_headers"):
+        files = [tmp_path / "_bwta_native.so", tmp_path / "binding_identity.txt"]
+        for f in files:
+            f.write_text("left from before")
+        with monkeypatch.context() as m:
+            m.setattr(build, "BINDING", str(files[0]))
+            m.setattr(build, "BINDING_ID", str(files[1]))
+            m.setattr(build, what, lambda: None)
+            assert build.build_binding("0" * 12, verbose=False) is None
+        assert "not built" in capsys.readouterr().out and not any(f.exists() for f in files)
+    assert build._binding_compiler() and build._binding_headers()
+
+
 def test_prepare_and_gemm_prepared_reject_bad_arguments():
     pb = B.prepared_bytes(8, 128)
     assert pb % 256 == 0 and pb > 0 and B.prepared_bytes(0, 128) == 0
