@@ -43,6 +43,7 @@ struct Bound {
     int count;
     void *address;
     PyObject *fallback;
+    PyObject *weak;  // weak references
 };
 
 PyObject *g_check = nullptr, *g_raw_stream = nullptr, *g_device = nullptr;  // binding._check, torch's two stream calls
@@ -354,21 +355,40 @@ PyObject *bound_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObj
 void bound_dealloc(PyObject *self)
 {
     Bound *b = (Bound *)self;
+    if (b->weak) PyObject_ClearWeakRefs(self);
     for (int i = 0; i < b->count; ++i) Py_XDECREF(b->names[i]);
     Py_XDECREF(b->fallback);
     Py_TYPE(self)->tp_free(self);
 }
 
+// Everything a program may do with a Python function besides calling it: its attributes, __class__ among them, are those
+// of the Python form and are set there, it binds as a method, and is pickled and copied by its name.
 PyObject *bound_getattro(PyObject *self, PyObject *name)
 {
-    // __doc__, __name__, __signature__ .. : those of the Python form
     if (PyUnicode_Check(name)) {
         const char *s = PyUnicode_AsUTF8(name);
         if (!s) return nullptr;
-        if (strcmp(s, "__class__") != 0) return PyObject_GetAttr(((Bound *)self)->fallback, name);
+        if (strcmp(s, "__reduce_ex__") == 0 || strcmp(s, "__reduce__") == 0 || strcmp(s, "__get__") == 0) return PyObject_GenericGetAttr(self, name);
     }
-    return PyObject_GenericGetAttr(self, name);
+    return PyObject_GetAttr(((Bound *)self)->fallback, name);
 }
+
+int bound_setattro(PyObject *self, PyObject *name, PyObject *value) { return PyObject_SetAttr(((Bound *)self)->fallback, name, value); }
+
+PyObject *bound_descr_get(PyObject *self, PyObject *object, PyObject *)
+{
+    if (object == nullptr || object == Py_None) {
+        Py_INCREF(self);
+        return self;
+    }
+    return PyMethod_New(self, object);
+}
+
+PyObject *bound_repr(PyObject *self) { return PyObject_Repr(((Bound *)self)->fallback); }
+
+PyObject *bound_reduce(PyObject *self, PyObject *) { return PyObject_GetAttrString(((Bound *)self)->fallback, "__qualname__"); }
+
+PyMethodDef kBoundMethods[] = {{"__reduce_ex__", bound_reduce, METH_O, nullptr}, {"__reduce__", bound_reduce, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
 
 PyTypeObject BoundType = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
@@ -383,7 +403,7 @@ PyObject *bind(PyObject *, PyObject *args)
         if (PyErr_Occurred()) return nullptr;
         Bound *b = PyObject_New(Bound, &BoundType);
         if (!b) return nullptr;
-        b->call = bound_call, b->spec = &s, b->count = 0, b->address = address, b->fallback = fallback;
+        b->call = bound_call, b->spec = &s, b->count = 0, b->address = address, b->fallback = fallback, b->weak = nullptr;
         Py_INCREF(fallback);
         for (; s.params[b->count]; ++b->count) {
             b->names[b->count] = PyUnicode_InternFromString(s.params[b->count]);
@@ -459,6 +479,11 @@ PyMODINIT_FUNC PyInit__bwta_native(void)
     BoundType.tp_call = PyVectorcall_Call;
     BoundType.tp_vectorcall_offset = offsetof(Bound, call);
     BoundType.tp_getattro = bound_getattro;
+    BoundType.tp_setattro = bound_setattro;
+    BoundType.tp_descr_get = bound_descr_get;
+    BoundType.tp_repr = bound_repr;
+    BoundType.tp_methods = kBoundMethods;
+    BoundType.tp_weaklistoffset = offsetof(Bound, weak);
     BoundType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL;
     if (PyType_Ready(&BoundType) < 0) return nullptr;
     return PyModule_Create(&kModule);

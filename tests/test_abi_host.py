@@ -284,6 +284,45 @@ def test_native_marshalling_knows_the_python_forms():
         B._native.bind("bwta_nothing", 0, print)
 
 
+def test_native_calls_are_used_like_python_functions():
+    """What programs do with a function besides calling it: attributes, methods, weak references, pickles and copies,
+    inspection."""
+    import copy
+    import functools
+    import inspect
+    import pickle
+    import types
+    import weakref
+    calls = []
+
+    def bwta_linear(A, s_a, wsign, s_w, out, workspace, *, M, N, K, lda=None):
+        """a docstring"""
+        calls.append((A, M))
+
+    f = B._native.bind("bwta_linear", 0, bwta_linear)
+    assert f.__name__ == "bwta_linear" and f.__doc__ == "a docstring" and f.__module__ == __name__ and repr(f) == repr(bwta_linear)
+    assert isinstance(f, types.FunctionType) and inspect.isfunction(f) and inspect.signature(f) == inspect.signature(bwta_linear)
+    f.note = 5
+    assert f.note == 5 and getattr(functools.wraps(f)(lambda: 0), "note") == 5
+    del f.note
+    assert not hasattr(f, "note")
+
+    class Layer:
+        linear = f
+
+    layer = Layer()
+    layer.linear(None, None, None, None, None, M=1, N=2, K=3)
+    Layer.linear(None, None, None, None, None, None, M=4, N=5, K=6)
+    assert calls == [(layer, 1), (None, 4)]
+    r = weakref.ref(f)
+    assert r() is f
+    for g in (copy.copy(B.bwta_linear), copy.deepcopy({"f": B.bwta_linear})["f"], pickle.loads(pickle.dumps(B.bwta_linear)), pickle.loads(pickle.dumps(B.bwta_linear, 0))):
+        assert g is B.bwta_linear
+    Layer.linear = None
+    del f, layer
+    assert r() is None
+
+
 def _package_copy(tmp_path):
     """The package's Python files and built libraries in a folder of their own: what a child interpreter imports."""
     import shutil
