@@ -2,15 +2,16 @@
 // E2M1): the kernel for long K.  Same operands, same exact sums as the kernels with blocks of 32 x 32
 // (kernels_gemm_fp4.hip); other instruction, larger wavefront tiles, K split inside the workgroup.
 //
-//   * Why 16 x 16.  A large product is held back by the clock, which drops under the power of toggling operands.
-//     Per multiply-accumulate this instruction updates its accumulators half as often as the 32 x 32 one: on random
-//     operands a loop of nothing but MFMAs runs at 9.05 PFLOP/s and 2.26 GHz against 7.70 and 1.93 (on zeros both
-//     9.84 at 2.4).  The weights are the first operand (A first: 8.64), and the token blocks are walked there and back
-//     so that neighbouring instructions share an operand (9.20).
+//   * Why 16 x 16.  The clock of a large product drops under the power of toggling operands.  Per multiply-accumulate
+//     this instruction updates its accumulators half as often as the 32 x 32 one: on random operands a loop of nothing
+//     but MFMAs runs at 9.05 PFLOP/s and 2.26 GHz against 7.70 and 1.93 (on zeros both 9.84 at 2.4).  The weights are the
+//     first operand (A first: 8.64), and the token blocks are walked there and back so that neighbouring instructions
+//     share an operand (9.20).
 //   * A wavefront owns 64 tokens x 128 channels: 32 blocks, 128 accumulators.  Its activation fragments come
-//     straight from global memory (L2) into registers, four steps of 128 k ahead; nobody else in the workgroup
-//     needs them.  Lane (r16, q4) takes of a step the pieces (step q4 / 2, half q4 % 2) of its row in the fragment
-//     layout of the 32 x 32 kernels, four runs of 256 bytes per load.
+//     straight from global memory (L2) into registers, four steps of 128 k ahead.  With one wavefront across the
+//     channels (the tiles of 128) nobody else in the workgroup needs them; with two (128 x 256) both fetch them.
+//     Lane (r16, q4) takes of a step the pieces (step q4 / 2, half q4 % 2) of its row in the fragment layout of the
+//     32 x 32 kernels, four runs of 256 bytes per load.
 //   * Weights, 1 bit each, go to LDS by direct loads for a pair of slabs (512 k, 64 bytes per channel) at a time,
 //     one pair ahead, and from there to registers one step ahead of use.  A direct load lays lane l at 16 l, so the
 //     four lanes of a row fetch its pieces in the order that leaves piece c of row r at slot c ^ (r / 4 % 4): the
@@ -23,10 +24,13 @@
 //     wavefronts also where it gets one tile of 64 x KS.. outputs and not two; in the end every group keeps 64 / KS
 //     tokens and hands the others' sums over through LDS, in fp32 (whole numbers, exact in any order).  Which
 //     token blocks a group keeps is settled by the order in which it loads them, so the code is the same for all.
-//   * Out-of-range rows and words of the weights arrive as zeros (buffer loads); their results are not stored.
-//   * What bounds it now: power.  2048 x 4096 x 11008 on random operands 33.9 us at 1.9 GHz, on zeros 29.8 at 2.37;
-//     fragments from one cache line instead of the L2 30.4, weights that do not change 28.7.  Then, for short K, what
-//     stands around the loop: 1.5 us until the first MFMA, 3.4 us of results (5 TB/s).
+//   * Rows past the last arrive as zeros (buffer loads) and their results are not stored; words past a row's end are the
+//     next row's and meet fragments of zeros.
+//   * What bounds it now: waiting more than power.  Of the clocks that a compute unit is busy the matrix pipes are so for
+//     67 % at 2048 x 4096 x 11008, 62 % at 2048 x 11008 x 4096, 51 % at 2048 x 4096 x 4096.  The first takes 33.9 us on
+//     random operands at 1.9 GHz and 29.8 on zeros at 2.37, that is 4 us for the clock; its MFMAs are 19.0 us at 2.37
+//     GHz, the time until the first one 1.5, the results 3.4 (5 TB/s): some 6 us are stalls of the loop.  With fragments
+//     from one cache line instead of the L2 it takes 30.4, with weights that do not change 28.7.
 //     us on ready fragments, random operands, the 32 x 32 kernels / this one: 2048 x 4096 x 4096 16.6 / 15.5 (KS = 2),
 //     2048 x 4096 x 11008 38.4 / 34.3, 2048 x 11008 x 4096 40.9 / 38.2 (KS = 1), 512 x 4096 x 11008 15.6 / 13.7 (KS = 4).
 //   * Tried: shifting the words of two channel blocks at once (v_lshlrev_b64: -1 % for KS = 2, +1 % for KS = 1); eight

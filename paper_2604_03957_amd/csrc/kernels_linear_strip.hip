@@ -257,12 +257,14 @@ static int strip_blocks(const GemmArgs &g)
 //   4096 15.3 / 14.2, 1024 x 3072 x 11008 28.3 / 32.0); beyond K = 8192 only with narrow matrices (2048 x 1536 x 11008 31.5 /
 //   33.5, 4096 x 768 x 11008 39.1 / 33.2).
 // From K = 3073 to 12288 the two kernels end in the product of 16 x 16 blocks with K split inside the workgroup, which
-// leaves this kernel what is cheap to ternarise often or too narrow for it (strip_keeps_long_k; two kernels / one, us):
-//   NB = 1 up to K = 5120 (256 x 768 x 5000 11.4 / 11.4, 1024 x 512 x 4096 10.9 / 9.7; many outputs 256 x 4096 x 5000 12.0 /
-//   13.0), to 7168 from 641 tokens (777 x 768 x 6500 15.1 / 13.6; 512 x 2048 x 6000 12.0 / 14.2), beyond only tall and narrow
-//   (2048 x 512 x 11008 24.9 / 24.2; 777 x 2048.. and wider behind, 256 x 4096 x 11008 16.4 / 21.9).
+// leaves this kernel what is cheap to ternarise often or too narrow for it (strip_keeps_long_k; two kernels / one, us; up
+// to K = 6144 shapes of at most 256 workgroups of 16 tokens x 128 channels are the strips of 16 tokens' and not meant):
+//   NB = 1 up to K = 5120 (1024 x 1000 x 4096 12.1 / 10.3, 777 x 1152 x 4096 11.6 / 10.1, 512 x 2048 x 4096 10.6 / 10.0; few
+//   tokens against wide matrices are behind, 256 x 4096 x 5000 11.8 / 13.1), to 7168 from 641 tokens (777 x 768 x 6500
+//   16.1 / 14.4, 1500 x 600 x 6500 18.2 / 15.8; 512 x 2048 x 6000 12.0 / 14.2), beyond only tall and narrow
+//   (2048 x 512 x 11008 23.6 / 22.7; 777 x 2048.. and wider behind, 256 x 4096 x 11008 16.4 / 21.9).
 //   NB = 2 up to K = 4608 for N <= 1536 (1300 x 1152 x 4096 14.4 / 13.9; 1024 x 2048 x 4096 13.2 / 14.3), to 7168 for N <= 768
-//   (2048 x 768 x 5000 17.8 / 16.5; 777 x 1536 x 6000 14.2 / 16.3), beyond for N <= 512 (4096 x 512 x 11008 33.1 / 28.6).
+//   (2048 x 768 x 5000 17.8 / 16.5; 777 x 1536 x 6000 14.2 / 16.3), beyond for N <= 512 (4096 x 512 x 11008 32.0 / 28.4; mixed at fewer tokens, 2221 x 407 x 9643 23.3 / 27.2).
 //   NB = 3 beyond 8192 for N <= 768 (4096 x 768 x 11008 37.8 / 32.6; 2048 x 1152 x 11008 29.3 / 31.8).
 // Longer K and N below 256 were not swept again.
 static bool strip_keeps_long_k(const GemmArgs &g, int nb)
