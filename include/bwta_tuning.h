@@ -83,6 +83,9 @@ int bwta_set_tile(int tile);
 int bwta_planned_wide(int M, int N, int K);
 int bwta_planned_wide_prepared(int M, int N, int K);
 int bwta_planned_tile(int M, int N, int K);
+/* How many blocks of channel tiles a workgroup of the matrix-core decode kernel (BWTA_KERNEL_GEMV_FP4) walks one after the
+ * other in a launch of `count` problems of one shape: 1, 2, 4 or 8; 0 where another kernel takes the shape. */
+int bwta_planned_decode_blocks(int M, int N, int K, int count);
 #ifdef __cplusplus
 }
 #endif

@@ -39,7 +39,7 @@ EXPORTS = ["bwta_plane_row_words", "bwta_workspace_bytes", "bwta_quantize_pack_a
            "bwta_pack_weights", "bwta_gemm", "bwta_linear", "bwta_linear_static", "bwta_static_scratch_bytes",
            "bwta_static_scratch_init", "bwta_strerror", "bwta_last_hip_error",
            "bwta_build_id", "bwta_set_path", "bwta_get_path", "bwta_auto_path", "bwta_linear_launches", "bwta_linear_call", "bwta_version",
-           "bwta_set_tile", "bwta_planned_tile", "bwta_planned_wide", "bwta_planned_wide_prepared", "bwta_planned_rows",
+           "bwta_set_tile", "bwta_planned_tile", "bwta_planned_wide", "bwta_planned_wide_prepared", "bwta_planned_rows", "bwta_planned_decode_blocks",
            "bwta_prepared_bytes", "bwta_prepared_format", "bwta_planned_kernel", "bwta_prepare_act", "bwta_gemm_prepared", "bwta_gemm_grouped",
            "bwta_quantize_pack_bool", "bwta_matmul_tt", "bwta_prepare_weights", "bwta_act_scale",
            "bwta_prepare_act_autoscale", "bwta_matmul_bool_prepared"]
@@ -135,6 +135,8 @@ _lib.bwta_planned_wide.restype = _c.c_int
 _lib.bwta_planned_wide.argtypes = [_c.c_int, _c.c_int, _c.c_int]
 _lib.bwta_planned_wide_prepared.restype = _c.c_int
 _lib.bwta_planned_wide_prepared.argtypes = [_c.c_int, _c.c_int, _c.c_int]
+_lib.bwta_planned_decode_blocks.restype = _c.c_int
+_lib.bwta_planned_decode_blocks.argtypes = [_c.c_int, _c.c_int, _c.c_int, _c.c_int]
 _lib.bwta_set_tile.restype = _c.c_int
 _lib.bwta_set_tile.argtypes = [_c.c_int]
 
@@ -338,6 +340,10 @@ def planned_rows(M, N, K):
 
 def planned_wide(M, N, K, prepared=False):
     return int((_lib.bwta_planned_wide_prepared if prepared else _lib.bwta_planned_wide)(M, N, K))
+
+
+def planned_decode_blocks(M, N, K, count):
+    return int(_lib.bwta_planned_decode_blocks(M, N, K, count))
 
 
 def prepared_format(M, K):

@@ -628,6 +628,14 @@ int bwta_planned_wide_prepared(int M, int N, int K)
     return bwta::fp4_planned_wide(M, N, K, true);
 }
 
+int bwta_planned_decode_blocks(int M, int N, int K, int count)
+{
+    if (M <= 0 || N <= 0 || K <= 0 || count <= 0) return 0;
+    bwta::GemmArgs g{};
+    g.M = M, g.N = N, g.K = K, g.rw = (int)bwta_plane_row_words(K);
+    return plan_from_planes(g, true) == BWTA_KERNEL_GEMV_FP4 ? bwta::gemv_fp4_planned_blocks(M, N, K, count) : 0;
+}
+
 int bwta_version(void) { return 2; }
 
 #ifndef BWTA_BUILD_ID

@@ -52,6 +52,7 @@ hipError_t launch_gemv_popc_grouped(const GemmArgs *gs, int count, hipStream_t s
 bool gemv_fp4_supported(const GemmArgs &g);
 hipError_t launch_gemv_fp4(const GemmArgs &g, hipStream_t st);
 hipError_t launch_gemv_fp4_grouped(const GemmArgs *gs, int count, hipStream_t st);
+int gemv_fp4_planned_blocks(int M, int N, int K, int count);
 void set_gemv_fp4_tile(int rpw, int t, int pf);
 bool gemm_mfma_supported(const GemmArgs &g);
 hipError_t launch_gemm_mfma(const GemmArgs &g, hipStream_t st);

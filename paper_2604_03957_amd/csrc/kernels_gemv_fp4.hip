@@ -360,12 +360,16 @@ size_t decode_lds_bytes(int RPW, int KW, int T, int U)
 //  - one token group, blocks of 8 tiles as it is and 7 or 8 wavefronts of two or four chunks: level (0.99 to 1.03 of the
 //    time; with three, K = 9217 .. 12288, 0 to 4 % ahead),
 //  - blocks of 4 tiles do not fit the LDS: blocks of 2 from 9 wavefronts on, or for several token groups (one group,
-//    K = 16384: 3 to 17 % behind).
+//    K = 16384: 3 to 17 % behind),
+//  - 6 or 8 wavefronts, whose workgroups load the SIMDs evenly as they are, in more than one and a half rounds of 4 or 8
+//    blocks and up to two (30 shapes: 1.02 of the time, 44 x 12160 x 8432, 6 problems, 41.8 / 45.8),
+//  - a workgroup had 6 tiles (8 wavefronts of four chunks) and would get 4 blocks of 2 (18 shapes: 1.04, 82 x 12105 x 14867,
+//    2, +11 %), or 8 of them with a fifth missing in the last round, except where the matrix then rounds up to a tenth
+//    fewer tiles (50 x 1024 x 16164, 39, -29 %).
 // Up to 4 wavefronts (K <= 4096) the five or four workgroups of a compute unit hide each other's ends: level.
 // us, one block / this: 16 x 2048 x 11008, count 16, -28 %; 40 x 4096 x 11008, count 16, 37.8 / 32.7; 16 x 4096 x 8192, count
 // 16, 16.1 / 14.4; 40 x 4096 x 8192, count 64, 109 / 88; 16 x 4096 x 11008, count 64, 74.7 / 73.3 (4.9 TB/s); 128 x 4096 x
-// 11008 -28 %; 4 x 4096 x 20480, count 8, -24 %.  Over 417 shapes that it takes, K from 4500 to 20480: 0.83 of the time, none
-// behind by 2 %.
+// 11008 -28 %; 4 x 4096 x 20480, count 8, -24 %.
 int blocks_per_workgroup(const DecodeShape &sh, int count, int RPW, int KW, int T, int *T2)
 {
     const int G = (sh.M + 15) / 16, tiles = (sh.N + 15) / 16;
@@ -376,6 +380,7 @@ int blocks_per_workgroup(const DecodeShape &sh, int count, int RPW, int KW, int 
     const int t = decode_lds_bytes(RPW, KW, 4, 2) <= 64 * 1024 ? 4 : 2;
     if (t == 2 && KW <= 8 && G == 1) return 1;
     int best = 1;
+    bool left_out = false;  // a choice in several rounds that is not ahead
     for (int u = 2; u <= 8; u *= 2) {
         if (t * u <= T) continue;
         const size_t lds = decode_lds_bytes(RPW, KW, t, u);
@@ -385,10 +390,13 @@ int blocks_per_workgroup(const DecodeShape &sh, int count, int RPW, int KW, int 
         // percent of the compute units' workgroups that are there in the fullest round of the chip
         const int64_t q = n <= fit ? 256 : fit, full = n < 256 ? (2 * n == fit ? 100 : 100 * n / 256) : 100 * n / ((n + q - 1) / q * q);
         if (n <= fit) {
-            if (full >= ((T == 8 && KW >= 7) || best > 1 ? 90 : 74)) best = u;
+            if (full >= ((T >= 6 && KW >= 7) || best > 1 || left_out ? 90 : 74)) best = u;
             break;
         }
-        if (G > 1 && full >= 74) best = u;
+        if (G == 1 || full < 74) continue;
+        const bool fewer = 10 * n * t * u < 9 * workgroups(T) * T;  // tiles, those past the matrix's last included
+        left_out = (2 * n > 3 * fit && n <= 2 * fit && u >= 4 && (KW == 6 || KW == 8)) || (T == 6 && !fewer && (u < 8 || full < 80));
+        if (!left_out) best = u;
     }
     if (best == 1) return 1;
     *T2 = t;
@@ -418,7 +426,7 @@ hipError_t launch_cfg(const DecodeBatch &b, int count, DecodeShape sh, hipStream
                 BWTA_DEC_GO(8);
                 return hipGetLastError();
             }
-            if constexpr (RPW == 4) {  // launch_shape keeps fewer chunks to 8 wavefronts
+            if constexpr (RPW == 4) {  // plan_shape keeps fewer chunks to 8 wavefronts
                 BWTA_DEC_GO(16);
                 return hipGetLastError();
             }
@@ -438,7 +446,11 @@ hipError_t launch_cfg(const DecodeBatch &b, int count, DecodeShape sh, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_shape(const DecodeBatch &b, int count, DecodeShape sh, hipStream_t st)
+struct DecodePlan {
+    int RPW, PF, T, U;
+};
+
+DecodePlan plan_shape(const DecodeShape &sh, int count)
 {
     const int chunks = (sh.P + 3) / 4;
     const int tiles = (sh.N + 15) / 16;
@@ -466,9 +478,15 @@ hipError_t launch_shape(const DecodeBatch &b, int count, DecodeShape sh, hipStre
         else if (PF == 2) PF = T = 1;
         else break;
     }
-    sh.T = T;
-    sh.U = f_rpw ? 1 : blocks_per_workgroup(sh, count, RPW, KW, T, &sh.T);
-#define BWTA_DEC(R_, P_) if (RPW == R_ && PF == P_) return launch_cfg<R_, P_>(b, count, sh, st);
+    const int U = f_rpw ? 1 : blocks_per_workgroup(sh, count, RPW, KW, T, &T);
+    return {RPW, PF, T, U};
+}
+
+hipError_t launch_shape(const DecodeBatch &b, int count, DecodeShape sh, hipStream_t st)
+{
+    const DecodePlan p = plan_shape(sh, count);
+    sh.T = p.T, sh.U = p.U;
+#define BWTA_DEC(R_, P_) if (p.RPW == R_ && p.PF == P_) return launch_cfg<R_, P_>(b, count, sh, st);
     BWTA_DEC(1, 1) BWTA_DEC(1, 2) BWTA_DEC(1, 3) BWTA_DEC(1, 4)
     BWTA_DEC(2, 1) BWTA_DEC(2, 2) BWTA_DEC(2, 3) BWTA_DEC(2, 4)
     BWTA_DEC(3, 1) BWTA_DEC(3, 2) BWTA_DEC(3, 3)
@@ -520,6 +538,13 @@ hipError_t launch_gemv_fp4_grouped(const GemmArgs *gs, int count, hipStream_t st
 }
 
 hipError_t launch_gemv_fp4(const GemmArgs &g, hipStream_t st) { return launch_gemv_fp4_grouped(&g, 1, st); }
+
+// blocks of channel tiles that a workgroup of such a launch walks (count: the problems of one launch, at most DecodeBatch::MAX)
+int gemv_fp4_planned_blocks(int M, int N, int K, int count)
+{
+    const int rw = (int)(4 * (((int64_t)K + 127) / 128));
+    return plan_shape(DecodeShape{M, N, rw, 0, 0, rw / 4, 0, 1, N, 1}, count < DecodeBatch::MAX ? count : DecodeBatch::MAX).U;
+}
 
 bool gemv_fp4_tuning_forced() { return g_force_rpw.load(std::memory_order_relaxed) != 0; }
 

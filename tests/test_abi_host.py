@@ -181,6 +181,20 @@ def test_planned_kernel_of_long_products():
         B.set_tile(0)
 
 
+def test_planned_decode_blocks():
+    """How many blocks of channel tiles a decode workgroup walks: the shapes measured on both sides of the rule."""
+    b = B.planned_decode_blocks
+    assert [b(16, 2041, 4500, 24), b(2, 4090, 5000, 32), b(3, 4096, 4500, 64), b(40, 4096, 11008, 16), b(16, 4096, 11008, 64)] == [2, 4, 8, 4, 8]
+    assert b(40, 4096, 8192, 64) == 8 and b(4, 5000, 8192, 1) == b(16, 4096, 4096, 64) == b(16, 4096, 16384, 64) == 1
+    # 6 or 8 wavefronts in one and a half to two rounds of 4 or 8 blocks, 4 blocks of 2 tiles for 6: one block each (or 4 in more rounds)
+    assert [b(44, 12160, 8432, 6), b(20, 6144, 12285, 17), b(75, 1394, 7273, 20), b(82, 12105, 14867, 2), b(35, 2313, 16193, 25)] == [1] * 5
+    assert b(59, 3456, 9118, 29) == b(40, 4096, 11008, 16) == b(50, 1024, 16164, 39) == 4 and b(28, 8058, 15744, 41) == 8
+    # 5, 7, 9 and 10 wavefronts, and two blocks, keep two rounds
+    assert [b(28, 8064, 4864, 12), b(59, 1880, 12821, 28), b(42, 589, 12906, 37), b(28, 4089, 19466, 14)] == [4, 4, 2, 8]
+    assert b(1, 4096, 11008, 64) == b(129, 4096, 11008, 1) == b(16, 0, 8, 1) == b(16, 8, 8, 0) == 0  # other kernels, nothing
+    assert b(16, 4096, 11008, 200) == b(16, 4096, 11008, 64)                                          # at most 64 to a launch
+
+
 def _code(fn, *a, **k):
     with pytest.raises(B.BwtaError) as e:
         fn(*a, **k)
