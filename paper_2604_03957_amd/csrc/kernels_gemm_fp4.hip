@@ -819,7 +819,9 @@ static int fp4_tile_for(const GemmArgs &g)
 //   Up to K = 3072 it is level (0.95 to 1.03 of the others' time).
 //   257 to 512 of them: over 4 where the pairs come out even (K = 4096: 0.90 to 0.95, 8192: 0.85 to 0.92), else over 2 (K =
 //   5000: 0.95, 6500: 0.96), from six pairs (K = 2816: 0.96 to 1.01, 3072: 0.95 to 1.0); except where tiles of 64 x 128
-//   of the other kernel just fill two rounds (1300 x 3001 x 3072 15.3 / 17.4).
+//   of the other kernel just fill two rounds (1300 x 3001 x 3072 15.3 / 17.4), and up to nine pairs where tiles of
+//   128 x 96 make one round and divide N (bwta_gemm: 7680 x 384 x 3601 19.6 / 20.9, 333 x 7296 x 3360 12.3 / 13.0, 356 x 6432 x
+//   4291 13.8 / 14.5; over 47 shapes 1.01 to 1.05 of their time; where they do not divide it 0.91 to 0.97).
 //   Beyond, up to 768 tiles of 128 x 128 (three per compute unit): over 2, from six pairs on (K = 2816: 0.96 to 0.98, 4096:
 //   0.91 to 0.95, 11008: 0.85 to 0.94), not with seven, where one group idles for an eighth of the time (K = 3500: 0.98 to
 //   1.03).
@@ -832,7 +834,7 @@ static int fp4_tile_for(const GemmArgs &g)
 //   ternarisation and three products, the others / this one: 305 x 65 x 3075 23.3 / 24.9, 492 x 1447 x 3326 25.0 / 26.3,
 //   309 x 89 x 4287 27.8 / 28.9; with one product this one is 0.3 to 0.9 ahead).
 //   257 to 512, while tiles of 128 x 96 make one round: seven pairs are left to them (312 x 6988 x 3105 34.7 / 38.1, 568 x
-//   4009 x 3325 35.9 / 37.0), eight over 2 (1397 x 1536 x 3631, those / over 4 / over 2 37.0 / 39.7 / 37.0; of 50 shapes over 4 0.98
+//   4009 x 3325 35.9 / 37.0), eight over 2 (308 x 7120 x 3817, those / over 4 / over 2 36.9 / 38.4 / 35.3; of 50 shapes over 4 0.98
 //   and over 2 0.96 of their time).
 static int fp4_wide_for(const GemmArgs &g, bool prepared)
 {
@@ -842,9 +844,11 @@ static int fp4_wide_for(const GemmArgs &g, bool prepared)
     if (prepared) {
         const bool half_pair = (8 * pairs - g.rw / 2) >= 4;
         if (tiles64 <= 128 && (pairs == 7 || pairs == 9) && half_pair) return 0;
-        const int64_t tiles96 = ((int64_t)g.M + 127) / 128 * (((int64_t)g.N + 95) / 96);
-        if (tiles64 > 256 && tiles64 <= 512 && tiles128 > 128 && tiles96 <= 256 && (pairs == 7 || pairs == 8)) return pairs == 7 ? 0 : 521;
     }
+    const int64_t tiles96 = ((int64_t)g.M + 127) / 128 * (((int64_t)g.N + 95) / 96);
+    const bool one_round_of_96 = tiles64 > 256 && tiles64 <= 512 && tiles128 > 128 && tiles96 <= 256;
+    if (one_round_of_96 && pairs <= 9 && g.N % 96 == 0) return 0;
+    if (one_round_of_96 && prepared && (pairs == 7 || pairs == 8)) return pairs == 7 ? 0 : 521;
     if (tiles64 <= 256) return pairs >= 7 ? 611 : 0;
     if (tiles64 <= 512 && pairs >= 7 && (pairs % 4 == 0 || pairs % 4 == 3)) return 611;
     if (tiles128 <= 768) {

@@ -165,7 +165,10 @@ def test_planned_kernel_of_long_products():
     assert p(512, 2049, 3073) == p(512, 2049, 4097) == 611                                   # 136 tiles
     assert [(w(513, 4096, K), p(513, 4096, K)) for K in (3073, 3584, 3585, 4096, 4097, 5633)] == \
         [(611, 0), (611, 0), (611, 521), (611, 521), (521, 521), (611, 611)]
-    assert p(513, 4896, 3073) == 0 and p(513, 4897, 3073) == 611                             # 255, 260 tiles of 128 x 96
+    assert p(513, 4895, 3073) == 0 and p(513, 4897, 3073) == 611                             # 255, 260 tiles of 128 x 96
+    # .. and, whoever reads it, where these divide N
+    assert [(w(1397, 1536, K), p(1397, 1536, K)) for K in (2560, 2561, 3073, 4608, 4609)] == [(0, 0), (0, 0), (0, 0), (0, 0), (521, 521)]
+    assert w(1397, 1535, 3073) == w(7680, 480, 4000) == 611 and w(7680, 384, 4000) == 0
     assert all(w(M, N, K) == p(M, N, K) for M, N, K in ((512, 4096, 3073), (300, 11007, 3073), (2048, 4096, 4096), (2048, 11008, 4096)))
     one = [B.planned_kernel(B.OPERAND_FP16, *s) == B.KERNEL_LINEAR_STRIP for s in
            ((256, 4096, 5120), (256, 4096, 5121), (641, 768, 7168), (640, 768, 7168), (641, 768, 7169), (1280, 512, 12288), (1280, 513, 12288),

@@ -1015,10 +1015,10 @@ def test_short_products_by_tile(M, N, K, tile):
 
 
 @pytest.mark.parametrize("M,N,K,fresh,kept", [(300, 515, 3100, 611, 0), (140, 700, 4200, 611, 0), (513, 1990, 3329, 611, 611), (1030, 2050, 3300, 611, 0),
-                                             (1397, 1536, 3631, 611, 521)])
+                                             (1397, 1530, 3631, 611, 521), (1397, 1536, 3631, 0, 0)])
 def test_products_of_an_operand_that_is_kept(M, N, K, fresh, kept):
-    """Where a product on an operand prepared by its own call takes another tile than bwta_gemm on the same planes: both
-    against the oracle."""
+    """Around where a product on an operand prepared by its own call takes another tile than bwta_gemm on the same planes:
+    both against the oracle."""
     _say("kept operand", M, N, K, fresh, kept)
     assert (B.planned_wide(M, N, K), B.planned_wide(M, N, K, prepared=True)) == (fresh, kept)
     t, w, s_a, s_w = _gemm_case(7050 + M, M, N, K, p0=0.5)
