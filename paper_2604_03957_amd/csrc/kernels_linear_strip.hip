@@ -262,7 +262,9 @@ static int strip_blocks(const GemmArgs &g)
 //   NB = 1 up to K = 5120 (1024 x 1000 x 4096 12.1 / 10.3, 777 x 1152 x 4096 11.6 / 10.1, 512 x 2048 x 4096 10.6 / 10.0; few
 //   tokens against wide matrices are behind, 256 x 4096 x 5000 11.8 / 13.1), to 7168 from 641 tokens (777 x 768 x 6500
 //   16.1 / 14.4, 1500 x 600 x 6500 18.2 / 15.8; 512 x 2048 x 6000 12.0 / 14.2), beyond only tall and narrow
-//   (2048 x 512 x 11008 23.6 / 22.7; 777 x 2048.. and wider behind, 256 x 4096 x 11008 16.4 / 21.9).
+//   (2048 x 512 x 11008 23.6 / 22.7; 777 x 2048.. and wider behind, 256 x 4096 x 11008 16.4 / 21.9).  With an odd number of
+//   pairs of slabs, 11 and 13 from 513 tokens (627 x 605 x 6576 15.1 / 13.9), 15 from 769 (1057 x 512 x 7236 17.1 / 15.9), 17
+//   from 897 (1142 x 406 x 8478 19.1 / 18.1; 23 shapes in these windows 1.03 of its time).
 //   NB = 2 up to K = 4608 for N <= 1536 (1300 x 1152 x 4096 14.4 / 13.9; 1024 x 2048 x 4096 13.2 / 14.3), to 7168 for N <= 768
 //   (2048 x 768 x 5000 17.8 / 16.5; 777 x 1536 x 6000 14.2 / 16.3), beyond for N <= 512 (4096 x 512 x 11008 32.0 / 28.4; mixed at fewer tokens, 2221 x 407 x 9643 23.3 / 27.2).
 //   NB = 3 beyond 8192 for N <= 768 (4096 x 768 x 11008 37.8 / 32.6; 2048 x 1152 x 11008 29.3 / 31.8).
@@ -270,7 +272,11 @@ static int strip_blocks(const GemmArgs &g)
 static bool strip_keeps_long_k(const GemmArgs &g, int nb)
 {
     if (g.K <= 3072 || g.K > 12288 || g.N < 256) return true;
-    if (nb == 1) return g.K <= 5120 || (g.M > 640 && g.K <= 7168) || (g.M >= 1280 && g.N <= 512);
+    if (nb == 1) {
+        const int pairs = (g.K + 511) / 512;  // odd: a group of wavefronts of the other kernel idles for one
+        if (pairs % 2 == 1 && pairs <= 17 && g.M > (pairs <= 13 ? 512 : pairs == 15 ? 768 : 896)) return true;
+        return g.K <= 5120 || (g.M > 640 && g.K <= 7168) || (g.M >= 1280 && g.N <= 512);
+    }
     if (nb == 2) return g.N <= (g.K <= 4608 ? 1536 : g.K <= 7168 ? 768 : 512);
     return g.K <= 8192 || g.N <= 768;
 }

@@ -175,6 +175,11 @@ def test_planned_kernel_of_long_products():
             (1300, 1536, 4096), (1024, 2048, 4096), (2048, 768, 7168), (2048, 768, 7169), (4096, 512, 11008), (4096, 768, 11008),
             (2048, 1152, 11008), (2048, 1152, 8192))]
     assert one == [True, False, True, False, False, True, False, True, False, True, False, True, True, False, True]
+    # .. an odd number of pairs of slabs (512 k) leaves more to the slab kernel where it has one channel block per wavefront
+    odd = [B.planned_kernel(B.OPERAND_FP16, *s) == B.KERNEL_LINEAR_STRIP for s in
+           ((513, 1900, 5632), (512, 1900, 5632), (600, 1100, 6144), (600, 1100, 6145), (600, 1100, 6656), (600, 1100, 6657), (769, 500, 7680),
+            (768, 500, 7680), (769, 500, 7681), (897, 600, 8704), (896, 600, 8704), (897, 600, 8705), (1200, 600, 9728))]
+    assert odd == [True, False, False, True, True, False, True, False, False, True, False, False, False]
     try:
         B.set_tile(243)
         assert w(2048, 11008, 4096) == 0 and B.planned_tile(2048, 11008, 4096) == 243

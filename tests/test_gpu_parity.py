@@ -512,7 +512,7 @@ def test_linear_one_token_tall_matrices(passes, K):
                                    (777, 1500, 2560), (2050, 383, 1800), (2048, 1536, 1030), (2300, 1100, 2049),
                                    (33, 5000, 900), (128, 5200, 3072), (65, 10100, 2999), (70, 4000, 2500), (520, 1100, 16390),
                                    (2, 33001, 1537), (31, 17000, 1536), (4111, 100, 1537), (300, 1900, 2047), (250, 4096, 1290),
-                                   (200, 70, 13003), (513, 1900, 1301), (33, 17000, 900)])
+                                   (200, 70, 13003), (513, 1900, 1301), (33, 17000, 900), (531, 1850, 5629), (930, 300, 8651)])
 @pytest.mark.parametrize("scales", ["vector", "scalar", "none"])
 def test_linear_slabs_one_launch(M, N, K, scales):
     """The one-launch linear that walks K in slabs of 512: one, two and three channel blocks per wavefront, tokens
